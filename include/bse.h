@@ -105,7 +105,9 @@ bse_status bse_interpolate_W(int32_t n_aux, int32_t n_R, const void* W_R,
  * it (about n_q * n_R > 10^6: 16 bytes per phase plus 36 per q and R) return
  * BSE_ESHAPE before any HIP call.  Every call on a GPU shares that GPU's array:
  * calls that overlap on one GPU (other streams or host threads) race; calls
- * on one stream are ordered.  The host tables are copied with
+ * on one stream are ordered.  Where q_frac is a product grid (last axis
+ * fastest) and R lies in a box of at most 7 x 7 x 7 the sum needs no table and
+ * leaves the array untouched; otherwise the host tables are copied to it with
  * hipMemcpyAsync from the caller's host memory. */
 bse_status bse_interpolate_W_noalloc(int32_t n_aux, int32_t n_R, const void* W_R,
                                      const int32_t* R, const double* w_R,

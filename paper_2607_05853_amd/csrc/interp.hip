@@ -1,8 +1,10 @@
 // Dual-k-mesh Fourier interpolation of the screened interaction (Sec. III.B):
 //   W_q[q] = sum_R w_R W_R[R] exp(+2 pi i q.R)
-// as one complex GEMM  [n_q x n_R] (phases) x [n_R x n_aux^2] (W_R)  on the FP64
-// matrix cores, and its conjugate transpose for gradients.
+// and its conjugate transpose for gradients: one axis at a time where q is a product
+// grid and R lies in a small box (fourier.hip), otherwise as one complex GEMM
+// [n_q x n_R] (phases) x [n_R x n_aux^2] (W_R) on the FP64 matrix cores.
 #include "bse_internal.h"
+#include "fourier.h"
 
 namespace bse {
 namespace {
@@ -59,6 +61,15 @@ bse_status make_phases(const Ws& t, int n_R, const int32_t* R, const double* w_R
   return BSE_OK;
 }
 
+// A dense mesh (any product grid of q) with R in a small box is summed one axis at a time; other q lists, larger
+// boxes, an R listed twice and buffers not aligned to an element go through the phase table and the GEMM.
+bool separable(FtArgs* ax, int n_q, const double* q, int n_R, const int32_t* R, const double* w, const void* in,
+               const void* out, bool out_f64) {
+  const uintptr_t mask = out_f64 ? 15 : 7;
+  if (((uintptr_t)in & 15) || ((uintptr_t)out & mask)) return false;
+  return ft_axes(ax, n_q, q, n_R, R, w);
+}
+
 // a workspace allocated on the stream and freed stream-ordered after the work that uses it
 struct StreamBuf {
   void* p = nullptr;
@@ -77,6 +88,9 @@ size_t interp_scratch_bytes(int n_q, int n_R) {
 
 bse_status interp_forward_ws(int n_aux, int n_R, const double* W_R, const int32_t* R, const double* w_R,
                              int n_q, const double* q, void* W_q, bool out_f64, void* ws, hipStream_t st) {
+  FtArgs ax;
+  if (separable(&ax, n_q, q, n_R, R, w_R, W_R, W_q, out_f64))
+    return ft_spread_launch(ax, 1.0, W_R, (long long)n_aux * n_aux, 0, 1, 1, 0, out_f64 ? 0 : 1, W_q, nullptr, st);
   const Ws t = carve(ws, n_q, n_R);
   BSE_TRY(make_phases(t, n_R, R, w_R, n_q, q, st));
   const long long a2 = (long long)n_aux * n_aux;
@@ -98,6 +112,9 @@ bse_status interp_forward_ws(int n_aux, int n_R, const double* W_R, const int32_
 
 bse_status interp_forward(int n_aux, int n_R, const double* W_R, const int32_t* R, const double* w_R,
                           int n_q, const double* q, void* W_q, bool out_f64, hipStream_t st) {
+  FtArgs ax;
+  if (separable(&ax, n_q, q, n_R, R, w_R, W_R, W_q, out_f64))
+    return ft_spread_launch(ax, 1.0, W_R, (long long)n_aux * n_aux, 0, 1, 1, 0, out_f64 ? 0 : 1, W_q, nullptr, st);
   StreamBuf buf;
   buf.st = st;
   BSE_HIP(hipMallocAsync(&buf.p, interp_scratch_bytes(n_q, n_R), st));
@@ -106,6 +123,9 @@ bse_status interp_forward(int n_aux, int n_R, const double* W_R, const int32_t* 
 
 bse_status interp_adjoint(int n_aux, int n_R, const int32_t* R, const double* w_R, int n_q,
                           const double* q, const double* g_Wq, double* g_WR, hipStream_t st) {
+  FtArgs ax;
+  if (separable(&ax, n_q, q, n_R, R, w_R, g_Wq, g_WR, true))
+    return ft_gather_launch(ax, -1.0, g_Wq, (long long)n_aux * n_aux, 0, g_WR, st);
   StreamBuf buf;
   buf.st = st;
   BSE_HIP(hipMallocAsync(&buf.p, interp_scratch_bytes(n_q, n_R), st));
