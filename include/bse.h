@@ -232,6 +232,15 @@ bse_status bse_plan_fused(const bse_plan* plan, int32_t* fused);
  * at plan creation keeps the row layout.  Host pointer. */
 bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
 
+/* *n_R > 0 when bse_apply to nb vectors sums over that many lattice vectors R
+ * instead of forming blocks of pairs (k, k'): on BSE_F64 plans with k-independent
+ * C^mu, W_q(-q) = conj W_q(q) and without BSE_ALL_PAIRS, plan creation recovers
+ * W(R) from W_q and checks that at most 256 R with components up to 3 give it back to 1e-14 (a
+ * W_q interpolated from a coarse mesh of up to 7 points per axis); the sum over k'
+ * then separates and its work grows with n_R nb instead of N_k^2.  Taken where
+ * that needs less work; 0 otherwise.  Host pointer. */
+bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R);
+
 /* Device bytes held by the plan (copies, halves and workspaces). */
 bse_status bse_plan_bytes(const bse_plan* plan, uint64_t* bytes);
 

@@ -55,6 +55,7 @@ _SIGS = {
     "bse_plan_conduction": [_vp, ctypes.POINTER(ctypes.c_int32)],
     "bse_plan_fused": [_vp, ctypes.POINTER(ctypes.c_int32)],
     "bse_plan_frag": [_vp, ctypes.POINTER(ctypes.c_int32)],
+    "bse_plan_lattice": [_vp, _i32, ctypes.POINTER(ctypes.c_int32)],
     "bse_offset_spectrum": [_vp, _vp, _vp, _i32, _i32, _i32, _vp, _i32, ctypes.c_double, _vp, _vp, _vp],
     "bse_offset_set": [ctypes.POINTER(ctypes.c_int32), _vp, _vp],
     "bse_apply": [_vp, _vp, _vp, _i32, _vp],
@@ -273,6 +274,12 @@ class Plan:
         v = ctypes.c_int32()
         _check("bse_plan_frag", lib().bse_plan_frag(self._ptr, ctypes.byref(v)))
         return bool(v.value)
+
+    def lattice(self, nb=None):
+        """Lattice vectors an apply to nb vectors sums over (0: it forms blocks of k pairs)."""
+        v = ctypes.c_int32()
+        _check("bse_plan_lattice", lib().bse_plan_lattice(self._ptr, int(nb or self.max_nb), ctypes.byref(v)))
+        return int(v.value)
 
     @property
     def bytes(self):

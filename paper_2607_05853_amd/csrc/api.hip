@@ -368,6 +368,7 @@ void destroy_plan(Plan* p) {
   (void)collect_stage_times(p);
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
   p->ev_pool.clear();
+  lattice_free(p);
   for (auto& b : p->owned) dfree(b.p);
   p->owned.clear();
 }
@@ -798,6 +799,7 @@ bse_status build_plan(Plan* p, const bse_dims* d, const double* eps_qp, const vo
     BSE_TRY(plan_alloc(p, (void**)&p->xu, 16 * (size_t)na * max_nb));
   }
   BSE_TRY(plan_alloc(p, (void**)&p->txp, 16 * (size_t)TX_CHUNKS * p->N * max_nb));
+  if (f64 && !tc && p->herm_half) BSE_TRY(lattice_build(p, C, W_q, st));
   return BSE_OK;
 }
 
@@ -1006,6 +1008,15 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag) {
   return BSE_OK;
 }
 
+bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R) {
+  if (!plan || nb <= 0 || bad_ptr(n_R)) {
+    set_error("bse_plan_lattice: invalid argument");
+    return BSE_EINVAL;
+  }
+  *n_R = lattice_size(&plan->impl, nb);
+  return BSE_OK;
+}
+
 bse_status bse_plan_destroy(bse_plan* plan) {
   if (!plan) return BSE_OK;
   destroy_plan(&plan->impl);
@@ -1090,6 +1101,7 @@ bse_status bse_apply(bse_plan* plan, const void* X, void* Y, int32_t nb, void* h
     return BSE_EINVAL;
   }
   hipStream_t st = S(hip_stream);
+  if (lattice_applies(p, nb)) return lattice_apply(p, (const double*)X, (double*)Y, nb, st);
   BSE_TRY(apply_diag(p, (const double*)X, (double*)Y, nb, st));
   BSE_TRY(apply_exchange(p, (const double*)X, (double*)Y, nb, st));
   BSE_TRY(apply_direct(p, (const double*)X, (double*)Y, nb, st));

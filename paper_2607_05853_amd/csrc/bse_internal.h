@@ -129,6 +129,8 @@ struct DevBuf {
 // q chunks of the T.X stage (each block sums its chunk; a second pass adds the chunks in order)
 constexpr int TX_CHUNKS = 16;
 
+struct Lattice;  // lattice.hip
+
 struct Plan {
   bse_dims d{};
   int Nk = 0, nt = 0, nbnd = 0;
@@ -203,6 +205,8 @@ struct Plan {
   double* fra = nullptr;
   double* frb = nullptr;
 
+  Lattice* lat = nullptr;     // the application over lattice vectors (FP64 plans whose W_q is a short sum over R)
+
   // exchange / misc workspaces (FP64)
   double* xt = nullptr;       // c128 split-K partials [nsplit][n_aux][max_nb]
   double* xu = nullptr;       // c128 [n_aux][max_nb]
@@ -252,6 +256,13 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
 bse_status direct_u_b3(Plan* p, int q0, int nq, const int* kq, hipStream_t st);
 bse_status adjoint_eps(Plan* p, const double* Ybar, const double* X, int nb, double* geps, bool acc,
                        hipStream_t st);
+// the application over lattice vectors (lattice.hip): built at plan creation where W_q allows it, chosen per
+// application by its operation count
+bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st);
+void lattice_free(Plan* p);
+bool lattice_applies(const Plan* p, int nb);
+int lattice_size(const Plan* p, int nb);  // lattice vectors of such an application, 0 for the pair route
+bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_t st);
 // the dense-mesh k list of a plan (fractional coordinates, host)
 std::vector<double> plan_kfrac(const Plan* p);
 

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
   double2* const p2 = p1 + n1 * FT_MAXR;
   double2* const p3 = p2 + n2 * NS;
   const long long e0 = (long long)blockIdx.x * te;
-#pragma unroll 16
+#pragma unroll 8
   for (int t = threadIdx.x; t < a.nR * te; t += blockDim.x) {
     const int r = t / te;
     const long long e = e0 + t % te;
@@ -142,6 +142,7 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
     if (e < E) {
       if (planar) {
         const double* s = in + 2 * (long long)r * E + (e / group) * 2 * group + e % group;
+#pragma unroll 8
         for (int q = 0; q < nsplit; ++q) {
           v.x += s[q * split_stride];
           v.y += s[q * split_stride + group];
@@ -319,7 +320,7 @@ bse_status spread_go(const FtArgs& a, double sign, const double* in, long long E
   // 32 e per block (512-byte rows) while the tile leaves room for two blocks on a CU, 16 for the larger R sets
   // and while 32 would leave CUs without a block
   const int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
-  const int bs = std::max(64, std::min(256, te * ((a.n[0] * te + 63) / 64 * 64 / te)));
+  const int bs = 256;
   const size_t lds = 16 * ((size_t)(a.nR + 1) * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * NS);
   if (lds > 64 * 1024)
     BSE_HIP(hipFuncSetAttribute((const void*)ft_spread<NS, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -354,7 +355,7 @@ bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long
   const int ns = ft_square(a);
   // as the spread: 32 e per block while that leaves every CU two blocks
   const int te = E >= 32 * 512 ? 32 : 16;
-  const int bs = std::max(64, std::min(256, te * ((a.n[0] * te + 63) / 64 * 64 / te)));
+  const int bs = 256;
   const size_t lds = 16 * ((size_t)(bs / te) * ns * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ns);
   const dim3 grid((unsigned)((E + te - 1) / te)), block(bs);
   if (ns <= 3)

@@ -1,0 +1,756 @@
+// The TDA Hamiltonian over lattice vectors (FP64 plans with k-independent C^mu and real W(R)).
+//
+// With W(q) = sum_R W(R) exp(2 pi i q.R) on a short set of R and M^mu_ij(k, k') = psi_i(k)^H C^mu psi_j(k'), the
+// sum over k' of the direct term separates:
+//   D(k)_tt'   = sum_v'c' conj(psi_v'(k)_t) psi_c'(k)_t' X(k)_c'v'
+//   D(R)       = sum_k exp(2 pi i k.R) D(k)
+//   U^nu_ts'   = sum_t' C^nu_s't' D(R)_tt'          per R
+//   V^mu_ts'   = sum_nu W(R)_munu U^nu_ts'          per R, real W
+//   F(R)_ss'   = sum_mu,t C^mu_ts V^mu_ts'          per R
+//   F(k)       = sum_R exp(-2 pi i k.R) F(R)
+//   Y(k)_cv    = (E_c - E_v) X - (1/N_k) sum_ss' conj(psi_c(k)_s') psi_v(k)_s F(k)_ss'
+// Its work grows with N_R n_b instead of N_k^2.  The exchange term is a change of V at R = 0,
+//   t^nu = sum_tt' C^nu_tt' D(0)_tt' = sum_t U^nu_tt(0),   V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu.
+// All three contractions are FP64 matrix-core GEMMs on planar (re, im) operands.  One application, pair route ->
+// this one: 8x8x8, N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors 83.7 -> 38.3 ms (2.15 TFLOP of matrix work at
+// 56 TFLOP/s in the three GEMMs; a large FP64 library product reaches 72 on this card); 5x6x7, N_ao 30, N_aux 90,
+// 27 R, 5 vectors 2.19 -> 0.39 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors 0.305 -> 0.086 ms (nine launches).
+#include "bse_internal.h"
+#include "fourier.h"
+#include "mfma_common.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstdlib>
+#include <new>
+
+namespace bse {
+
+struct Lattice {
+  FtArgs ax;                 // the active R on the dense mesh, unit weights
+  int nR = 0, r0 = 0;        // r0: index of R = 0
+  double* Wr = nullptr;      // [nR][n_aux][n_aux]
+  // constants with padded rows: n_aux n_ao doubles is often a power of two, whose rows all start in one L2 channel
+  long long ldc = 0;
+  double* C1 = nullptr;      // [2][t'][ldc]: (nu, s') = C^nu_s't'
+  double* C3 = nullptr;      // [2][s][ldc]:  (t, mu)  = C^mu_ts
+  int nbc = 0, rc = 0;       // vectors and R per pass
+  double* D = nullptr;       // c128 [Nk][n_ao][nbc][n_ao], later F(k) as [Nk][nbc][n_ao][n_ao]
+  double* DR = nullptr;      // [nR][2][n_ao][nbc][n_ao]
+  double* U = nullptr;       // [rc][n_ao][nbc][2][n_aux][n_ao]
+  double* V = nullptr;       // same
+  double* F = nullptr;       // [split][nR][nbc][2][n_ao][n_ao]
+  long long f_doubles = 0;
+  double* t = nullptr;       // c128 [n_aux][nbc]
+};
+
+namespace {
+
+// ----------------------------------------------------------------------------
+// FP64 GEMM on planar operands: C[m][n] = sum_k A[m][k] B[k][n], real, or complex with re and im planes
+// ----------------------------------------------------------------------------
+struct LatGemm {
+  int M, N, K, Z;                       // Z batch entries
+  const double* A;                      // row m at m lda, k contiguous
+  long long lda, a_ps, a_z;
+  const double* B;                      // row k at (k / kd) rs1 + (k % kd) rs0, column n at (n / nd) cs1 + n % nd
+  int kd, nd;
+  long long rs1, rs0, cs1, b_ps, b_z;
+  double* C;                            // row m at m ldc, column n at (n / nd) cc1 + n % nd
+  long long ldc, cc1, c_ps, c_z;
+  int nsplit, klen;                     // split of K: part s covers [s klen, ..) and writes C + s c_split
+  long long c_split;
+};
+
+// 256 threads as 2 x 2 waves on a BM x BN tile, BK deep stages in two LDS buffers with the next stage's loads in
+// flight during the products.  The 16x16x4 FP64 instruction takes 64 cycles and two 8-byte LDS reads feed it, so
+// the tiles only have to keep the matrix cores busy: real 128 x 128 (64 x 64 per wave), complex 64 x 128 (32 x 64
+// per wave and plane), both 128 accumulator registers and two blocks per CU; the half-size tiles serve operands
+// that would leave CUs without a block.  LDS rows are padded so that a fragment's 64 lanes spread over the banks.
+// VEC: 16-byte loads (even strides and sizes).
+template <bool CPLX, int BM, int BN, int BK, bool VEC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_gemm(LatGemm g) {
+  constexpr int NP = CPLX ? 2 : 1;
+  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+  constexpr int SA = BK + 2, SB = BN + 16;
+  constexpr int NA = BM * BK / 2 * NP / 256, NB = BK * BN / 2 * NP / 256;  // pairs per thread and stage
+  constexpr int ASZ = NP * BM * SA, BSZ = NP * BK * SB;
+  __shared__ double sm[2][ASZ + BSZ];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l4 = lane >> 4, l16 = lane & 15, wm = wave >> 1, wn = wave & 1;
+  // block -> (group, m tile), a group being one n tile of one batch entry and K part: the m tiles of a group follow
+  // each other on one XCD, which then reads the B panel once, and the groups go round the eight XCDs
+  const int mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
+  const unsigned id = blockIdx.x;
+  const int m0 = (int)((id >> 3) % mt) * BM;
+  const unsigned grp = (id >> 3) / mt * 8 + (id & 7);
+  if (grp >= (unsigned)nt * g.Z * g.nsplit) return;
+  const int n0 = (int)(grp % nt) * BN;
+  const int z = (int)(grp / nt % g.Z), sp = (int)(grp / nt / g.Z);
+  const int kbeg = sp * g.klen, kend = min(g.K, kbeg + g.klen);
+  const double* A = g.A + z * g.a_z;
+  const double* B = g.B + z * g.b_z;
+  double* C = g.C + z * g.c_z + sp * g.c_split;
+
+  // addresses of rows, columns or k outside the operands point at an element inside; lstore writes zeros there
+  double2 ra[NA], rb[NB];
+  long long ao[NA], bo[NB], bd[NB];
+  int ak[NA], bk[NB], bkq[NB], bkr[NB];
+  bool aok[NA], bok[NB], bok1[NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int t = tid + 256 * i, pl = t / (BM * BK / 2), u = t % (BM * BK / 2);
+    const int row = m0 + u / (BK / 2);
+    ak[i] = 2 * (u % (BK / 2));
+    aok[i] = row < g.M;
+    ao[i] = pl * g.a_ps + (aok[i] ? row : 0) * g.lda;
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int t = tid + 256 * i, pl = t / (BK * BN / 2), u = t % (BK * BN / 2);
+    const int col = n0 + 2 * (u % (BN / 2));
+    bk[i] = u / (BN / 2);
+    bok[i] = col < g.N;
+    bok1[i] = col + 1 < g.N;
+    const int c = bok[i] ? col : 0, c1 = bok1[i] ? col + 1 : 0;
+    bo[i] = pl * g.b_ps + (long long)(c / g.nd) * g.cs1 + c % g.nd;
+    bd[i] = pl * g.b_ps + (long long)(c1 / g.nd) * g.cs1 + c1 % g.nd;
+    bkq[i] = (kbeg + bk[i]) / g.kd;  // k = bkq kd + bkr, advanced by BK per stage
+    bkr[i] = (kbeg + bk[i]) % g.kd;
+  }
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int k = k0 + ak[i];
+      if constexpr (VEC) {
+        ra[i] = *reinterpret_cast<const double2*>(A + ao[i] + (k < kend ? k : kbeg));
+      } else {
+        ra[i].x = A[ao[i] + (k < kend ? k : kbeg)];
+        ra[i].y = A[ao[i] + (k + 1 < kend ? k + 1 : kbeg)];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const bool ok = k0 + bk[i] < kend;
+      const long long ro = ok ? bkq[i] * g.rs1 + bkr[i] * g.rs0 : 0;
+      if constexpr (VEC) {
+        rb[i] = *reinterpret_cast<const double2*>(B + bo[i] + ro);
+      } else {
+        rb[i].x = B[bo[i] + ro];
+        rb[i].y = B[bd[i] + ro];
+      }
+      bkr[i] += BK;
+      while (bkr[i] >= g.kd) {
+        bkr[i] -= g.kd;
+        ++bkq[i];
+      }
+    }
+  };
+  const double2 zero2 = {0.0, 0.0};
+  auto lstore = [&](double* s, int k0) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int t = tid + 256 * i, pl = t / (BM * BK / 2), u = t % (BM * BK / 2);
+      const bool ok = aok[i] && k0 + ak[i] < kend;
+      double2 v = ok ? ra[i] : zero2;
+      if (!VEC && !(k0 + ak[i] + 1 < kend)) v.y = 0.0;
+      *reinterpret_cast<double2*>(s + pl * BM * SA + (u / (BK / 2)) * SA + ak[i]) = v;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int t = tid + 256 * i, pl = t / (BK * BN / 2), u = t % (BK * BN / 2);
+      const bool ok = k0 + bk[i] < kend;
+      double2 v = ok && bok[i] ? rb[i] : zero2;
+      if (!VEC && !bok1[i]) v.y = 0.0;
+      *reinterpret_cast<double2*>(s + ASZ + pl * BK * SB + bk[i] * SB + 2 * (u % (BN / 2))) = v;
+    }
+  };
+
+  d4v acc[NP][TM][TN];
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[p][i][j] = d4v{0, 0, 0, 0};
+
+  int cur = 0;
+  if (kbeg < kend) gload(kbeg);
+  if (kbeg < kend) lstore(sm[0], kbeg);
+  __syncthreads();
+  for (int k0 = kbeg; k0 < kend; k0 += BK) {
+    const bool more = k0 + BK < kend;
+    if (more) gload(k0 + BK);
+    const double* sa = sm[cur] + (wm * WM + l16) * SA + l4;
+    const double* sb = sm[cur] + ASZ + l4 * SB + wn * WN + l16;
+#pragma unroll
+    for (int kk = 0; kk < BK / 4; ++kk) {
+      double av[NP][TM], bv[NP][TN];
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) av[p][i] = sa[p * BM * SA + i * 16 * SA + 4 * kk];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) bv[p][j] = sb[p * BK * SB + 4 * kk * SB + j * 16];
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[0][i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[0][i], bv[0][j], acc[0][i][j], 0, 0, 0);
+          if constexpr (CPLX) {
+            acc[1][i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[0][i], bv[1][j], acc[1][i][j], 0, 0, 0);
+            acc[0][i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[1][i], bv[1][j], acc[0][i][j], 0, 0, 0);
+            acc[1][i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[1][i], bv[0][j], acc[1][i][j], 0, 0, 0);
+          }
+        }
+    }
+    if (more) lstore(sm[cur ^ 1], k0 + BK);
+    cur ^= 1;
+    __syncthreads();
+  }
+  // register q of a lane holds column l16 of tile row 4 q + l4
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn * WN + j * 16 + l16;
+    if (n >= g.N) continue;
+    double* c = C + (long long)(n / g.nd) * g.cc1 + n % g.nd;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = m0 + wm * WM + i * 16 + 4 * q + l4;
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) c[p * g.c_ps + m * g.ldc] = acc[p][i][j][q];
+      }
+  }
+}
+
+template <bool CPLX, int BM, int BN, int BK>
+bse_status lat_gemm_go(const LatGemm& g, bool vec, hipStream_t st) {
+  const int mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
+  const long long groups = (long long)nt * g.Z * g.nsplit;
+  const dim3 grid((unsigned)((groups + 7) / 8 * 8 * mt));
+  if (vec)
+    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, true>), grid, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, false>), grid, dim3(256), 0, st, g);
+  BSE_CHECK_LAUNCH();
+  return BSE_OK;
+}
+
+long long tiles(const LatGemm& g, int bm, int bn) {
+  return (long long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.Z * g.nsplit;
+}
+
+// full-size tiles once they give most CUs a block (a second round of half-size tiles costs more than the idle
+// CUs), half-size tiles below and for operands of few rows
+template <bool CPLX>
+bse_status lat_gemm_run(const LatGemm& g, hipStream_t st) {
+  auto even = [](long long x) { return (x & 1) == 0; };
+  const bool vec = even(g.lda) && even(g.a_ps) && even(g.a_z) && even(g.K) && even(g.klen) && even(g.N) && even(g.nd) &&
+                   even(g.rs0) && even(g.rs1) && even(g.cs1) && even(g.b_ps) && even(g.b_z);
+  if constexpr (CPLX) {
+    if (g.M > 32 && tiles(g, 64, 128) >= 192) return lat_gemm_go<true, 64, 128, 8>(g, vec, st);
+    return lat_gemm_go<true, 32, 64, 16>(g, vec, st);
+  } else {
+    if (g.M > 64 && tiles(g, 128, 128) >= 384) return lat_gemm_go<false, 128, 128, 16>(g, vec, st);
+    if (tiles(g, 64, 128) >= 192) return lat_gemm_go<false, 64, 128, 16>(g, vec, st);
+    return lat_gemm_go<false, 64, 64, 32>(g, vec, st);
+  }
+}
+
+// ----------------------------------------------------------------------------
+// D(k) and Y(k): one block per (k, vector)
+// ----------------------------------------------------------------------------
+__device__ __forceinline__ double2 cmadd(double2 a, double2 x, double2 y) {  // a + x y
+  return double2{fma(x.x, y.x, fma(-x.y, y.y, a.x)), fma(x.x, y.y, fma(x.y, y.x, a.y))};
+}
+__device__ __forceinline__ double2 cmaddc(double2 a, double2 x, double2 y) {  // a + conj(x) y
+  return double2{fma(x.x, y.x, fma(x.y, y.y, a.x)), fma(x.x, y.y, fma(-x.y, y.x, a.y))};
+}
+
+// D[k][t][b][t'] = sum_v conj(psi_v(k)_t) Z_v t', Z_v t' = sum_c psi_c(k)_t' X(k)_cv (kept in LDS); bound by
+// writing D
+__global__ __launch_bounds__(256) void lat_outer(int nv, int nc, int no, int nb, int b0, int nbc,
+                                                 const double* __restrict__ psi, const double* __restrict__ X,
+                                                 double* __restrict__ D) {
+  extern __shared__ double2 lsm[];
+  const int k = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, nt = nv * nc;
+  double2* const Zs = lsm;            // [nv][no]
+  double2* const Xs = Zs + nv * no;   // [nc][nv]
+  const double2* pk = reinterpret_cast<const double2*>(psi) + (long long)k * (nv + nc) * no;
+  for (int i = tid; i < nt; i += 256) {
+    const double* x = X + 2 * (((long long)k * nt + i) * nb + b0 + b);
+    Xs[i] = double2{x[0], x[1]};
+  }
+  __syncthreads();
+  for (int i = tid; i < nv * no; i += 256) {
+    const int v = i / no, t = i % no;
+    double2 s = {0.0, 0.0};
+    for (int c = 0; c < nc; ++c) s = cmadd(s, pk[(nv + c) * no + t], Xs[c * nv + v]);
+    Zs[i] = s;
+  }
+  __syncthreads();
+  double2* Dk = reinterpret_cast<double2*>(D) + ((long long)k * no * nbc + b) * no;
+  for (int i = tid; i < no * no; i += 256) {
+    const int t = i / no, tp = i % no;
+    double2 s = {0.0, 0.0};
+    for (int v = 0; v < nv; ++v) s = cmaddc(s, pk[v * no + t], Zs[v * no + tp]);
+    Dk[(long long)t * nbc * no + tp] = s;
+  }
+}
+
+// Y[k][c][v][b] = (E_c - E_v) X - (1/N_k) sum_ss' conj(psi_c s') psi_v s F[k][b][s][s']: H_v s' = sum_s psi_v s F
+// by 256 / n_ao groups of s, then one wave per (c, v); bound by reading F
+__global__ __launch_bounds__(256) void lat_project(int nv, int nc, int no, int nb, int b0, int nbc, int groups,
+                                                   double scale, const double* __restrict__ eps,
+                                                   const double* __restrict__ psi, const double* __restrict__ F,
+                                                   const double* __restrict__ X, double* __restrict__ Y) {
+  extern __shared__ double2 lsm[];
+  const int k = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, nt = nv * nc;
+  double2* const H = lsm;  // [groups][nv][no]
+  const double2* pk = reinterpret_cast<const double2*>(psi) + (long long)k * (nv + nc) * no;
+  const double2* Fk = reinterpret_cast<const double2*>(F) + ((long long)k * nbc + b) * no * no;
+  const int gr = tid / no;
+  if (groups > 1 ? gr < groups : true) {
+    for (int sp = groups > 1 ? tid % no : tid; sp < no; sp += 256) {
+      const int s0 = groups > 1 ? gr : 0;
+      for (int v0 = 0; v0 < nv; v0 += 4) {
+        double2 h[4] = {};
+        for (int s = s0; s < no; s += groups) {
+          const double2 f = Fk[(long long)s * no + sp];
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (v0 + v < nv) h[v] = cmadd(h[v], pk[(v0 + v) * no + s], f);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (v0 + v < nv) H[(s0 * nv + v0 + v) * no + sp] = h[v];
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < nv * no; i += 256) {
+    double2 s = H[i];
+    for (int q = 1; q < groups; ++q) {
+      const double2 h = H[q * nv * no + i];
+      s.x += h.x;
+      s.y += h.y;
+    }
+    H[i] = s;
+  }
+  __syncthreads();
+  const int lane = tid & 63;
+  for (int o = tid >> 6; o < nt; o += 4) {
+    const int c = o / nv, v = o % nv;
+    double2 s = {0.0, 0.0};
+    for (int sp = lane; sp < no; sp += 64) s = cmaddc(s, pk[(nv + c) * no + sp], H[v * no + sp]);
+    for (int w = 32; w > 0; w >>= 1) {
+      s.x += __shfl_down(s.x, w);
+      s.y += __shfl_down(s.y, w);
+    }
+    if (lane == 0) {
+      const long long i = 2 * (((long long)k * nt + o) * nb + b0 + b);
+      const double d = eps[(long long)k * (nv + nc) + nv + c] - eps[(long long)k * (nv + nc) + v];
+      Y[i] = d * X[i] - scale * s.x;
+      Y[i + 1] = d * X[i + 1] - scale * s.y;
+    }
+  }
+}
+
+// ----------------------------------------------------------------------------
+// exchange term
+// ----------------------------------------------------------------------------
+__device__ __forceinline__ void wave_sum(double2& s) {
+  for (int w = 32; w > 0; w >>= 1) {
+    s.x += __shfl_down(s.x, w);
+    s.y += __shfl_down(s.y, w);
+  }
+}
+
+// t^nu = sum_t U^nu_tt(0), block (nu, b) of one wave
+__global__ __launch_bounds__(64) void lat_ex_t(int na, int no, int nbc, const double* __restrict__ U0,
+                                               double* __restrict__ t) {
+  const int nu = blockIdx.x, b = blockIdx.y;
+  const long long pl = (long long)na * no;
+  double2 s = {0.0, 0.0};
+  for (int a = threadIdx.x; a < no; a += 64) {
+    const double* u = U0 + ((long long)a * nbc + b) * 2 * pl + (long long)nu * no + a;
+    s.x += u[0];
+    s.y += u[pl];
+  }
+  wave_sum(s);
+  if (threadIdx.x == 0) {
+    t[2 * (nu * nbc + b)] = s.x;
+    t[2 * (nu * nbc + b) + 1] = s.y;
+  }
+}
+
+// V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu; block (mu, b) of one wave.  DIRECT: t summed here from U (small
+// n_aux n_ao, one launch less)
+template <bool DIRECT>
+__global__ __launch_bounds__(64) void lat_ex_v(int na, int no, int nbc, double alpha, const double* __restrict__ vbar,
+                                               const double* __restrict__ U0, const double* __restrict__ t,
+                                               double* __restrict__ V0) {
+  const int mu = blockIdx.x, b = blockIdx.y;
+  const long long pl = (long long)na * no;
+  double2 s = {0.0, 0.0};
+  for (int nu = threadIdx.x; nu < na; nu += 64) {
+    const double* v = vbar + 2 * ((long long)mu * na + nu);
+    double2 x = {0.0, 0.0};
+    if constexpr (DIRECT) {
+#pragma unroll 8
+      for (int a = 0; a < no; ++a) {
+        const double* u = U0 + ((long long)a * nbc + b) * 2 * pl + (long long)nu * no + a;
+        x.x += u[0];
+        x.y += u[pl];
+      }
+    } else {
+      x = double2{t[2 * (nu * nbc + b)], t[2 * (nu * nbc + b) + 1]};
+    }
+    s = cmadd(s, double2{v[0], v[1]}, x);
+  }
+  wave_sum(s);
+  s.x = __shfl(s.x, 0);
+  s.y = __shfl(s.y, 0);
+  for (int a = threadIdx.x; a < no; a += 64) {
+    double* v = V0 + ((long long)a * nbc + b) * 2 * pl + (long long)mu * no + a;
+    v[0] -= alpha * s.x;
+    v[pl] -= alpha * s.y;
+  }
+}
+
+// ----------------------------------------------------------------------------
+// plan construction
+// ----------------------------------------------------------------------------
+// max |re| and max |im| of each matrix of Wb [nbox][n] c128, as bits of non-negative doubles
+__global__ void lat_absmax(long long n, const double* __restrict__ W, unsigned long long* __restrict__ out) {
+  const double2* w = reinterpret_cast<const double2*>(W) + blockIdx.y * n;
+  double mr = 0.0, mi = 0.0;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const double2 v = w[i];
+    if (!(fabs(v.x) <= mr)) mr = fabs(v.x);
+    if (!(fabs(v.y) <= mi)) mi = fabs(v.y);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double a = __shfl_down(mr, o), b = __shfl_down(mi, o);
+    if (!(a <= mr)) mr = a;
+    if (!(b <= mi)) mi = b;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicMax(&out[2 * blockIdx.y], (unsigned long long)__double_as_longlong(mr));
+    atomicMax(&out[2 * blockIdx.y + 1], (unsigned long long)__double_as_longlong(mi));
+  }
+}
+
+// Wr[j] = Re W[idx[j]] and the same with a zero imaginary part in place (for the check)
+__global__ void lat_take_real(long long n, const int* __restrict__ idx, const double* __restrict__ W,
+                              double* __restrict__ Wr, double* __restrict__ Wc) {
+  const int j = blockIdx.y;
+  const double2* w = reinterpret_cast<const double2*>(W) + idx[j] * n;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const double v = w[i].x;
+    Wr[j * n + i] = v;
+    reinterpret_cast<double2*>(Wc)[j * n + i] = double2{v, 0.0};
+  }
+}
+
+__global__ void lat_pack_C(int na, int no, long long ldc, const double* __restrict__ C, double* __restrict__ C1,
+                           double* __restrict__ C3) {
+  const long long n = (long long)na * no * no;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    // C[mu][s][t]; C1[t'][nu][s'] = C^nu_s't', C3[s][t][mu] = C^mu_ts
+    const int t = (int)(i % no), s = (int)((i / no) % no), mu = (int)(i / ((long long)no * no));
+    const long long i1 = t * ldc + (long long)mu * no + s, i3 = t * ldc + (long long)s * na + mu;
+    const double re = C[2 * i], im = C[2 * i + 1];
+    C1[i1] = re;
+    C1[no * ldc + i1] = im;
+    C3[i3] = re;
+    C3[no * ldc + i3] = im;
+  }
+}
+
+size_t lds_outer(const Plan* p) { return 16 * ((size_t)p->d.nv * p->d.n_ao + (size_t)p->nt); }
+int project_groups(const Plan* p) { return p->d.n_ao <= 256 ? 256 / p->d.n_ao : 1; }
+size_t lds_project(const Plan* p) { return 16 * (size_t)project_groups(p) * p->d.nv * p->d.n_ao; }
+
+struct Tmp {
+  void* p = nullptr;
+  ~Tmp() { dfree(p); }
+};
+
+// operations of one application over R and over pairs of k
+double flops_lattice(const Plan* p, int nb) {
+  const double na = p->d.n_aux, no = p->d.n_ao;
+  return (double)nb * p->lat->nR * (16.0 * na * no * no * no + 4.0 * na * na * no * no);
+}
+double flops_pairs(const Plan* p) {
+  const double na = p->d.n_aux, no = p->d.n_ao, nv = p->d.nv, nc = p->d.nc;
+  return 8.0 * p->Nk * p->nhalf * (na * no * (nv * nv + nc * nc) + na * na * nv * nv + na * nv * nv * nc * nc);
+}
+
+}  // namespace
+
+void lattice_free(Plan* p) {
+  delete p->lat;
+  p->lat = nullptr;
+}
+
+// Whether an application to nb vectors goes over R: by the matrix work of the two routes, the pair route counted
+// 1.5 times because its GEMMs of a few rows per pair run at 33 TFLOP/s (8x8x8 workload) against 56 here
+bool lattice_applies(const Plan* p, int nb) {
+  return p->lat && flops_lattice(p, nb) < 1.5 * flops_pairs(p);
+}
+
+// Finds the R set of W_q: W(R) on a box of at most 7 x 7 x 7 around R = 0 by the inverse sum, the R whose matrix is
+// not rounding noise, and a check that they give W_q back to 1e-14 of its largest element (a W_q that is no such sum
+// keeps the pair route).  Called for FP64 plans whose W_q has the pair symmetry, i.e. real W(R).
+bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st) {
+  const bse_dims& d = p->d;
+  const int Nk = p->Nk, na = d.n_aux, no = d.n_ao;
+  const long long n2 = (long long)na * na, nc1 = (long long)na * no * no;
+  if (lds_outer(p) > 64 * 1024 || lds_project(p) > 64 * 1024 || na > 3000) return BSE_OK;
+  std::vector<int32_t> R;
+  int lo[3], hi[3];
+  for (int x = 0; x < 3; ++x) {
+    const int n = d.nk[x];
+    if (n > FT_MAXQ) return BSE_OK;
+    lo[x] = n >= 7 ? -3 : -(n - 1) / 2;
+    hi[x] = n >= 7 ? 3 : n / 2;
+  }
+  for (int a = lo[0]; a <= hi[0]; ++a)
+    for (int b = lo[1]; b <= hi[1]; ++b)
+      for (int c = lo[2]; c <= hi[2]; ++c) {
+        R.push_back(a);
+        R.push_back(b);
+        R.push_back(c);
+      }
+  const int nbox = (int)R.size() / 3;
+  // worth looking at only if a small set would win for one vector
+  {
+    const double one = std::min(nbox, 7) * (16.0 * na * (double)no * no * no + 4.0 * na * (double)na * no * no);
+    if (one > 1.5 * flops_pairs(p)) return BSE_OK;
+  }
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    return BSE_OK;
+  }
+  const size_t budget = std::min<size_t>((size_t)16 << 30, free_b / 5);
+  if (32 * (size_t)nbox * n2 > budget) return BSE_OK;
+
+  std::vector<double> q = plan_kfrac(p);
+  // the inverse sum over the whole box (the kernels' R list is limited to FT_MAXNR, so one R1 at a time)
+  Tmp box, red, idx, chk;
+  BSE_TRY(dmalloc(&box.p, 16 * (size_t)nbox * n2));
+  BSE_TRY(dmalloc(&red.p, 8 * (2 * (size_t)nbox + 1)));
+  BSE_TRY(zero_fill(red.p, 8 * (2 * (size_t)nbox + 1), st));
+  const int per = nbox / (hi[0] - lo[0] + 1);
+  const std::vector<double> w(nbox, 1.0 / Nk);
+  for (int i = 0; i < nbox; i += per) {
+    FtArgs ax;
+    if (!ft_axes(&ax, Nk, q.data(), per, R.data() + 3 * (size_t)i, w.data())) return BSE_OK;
+    BSE_TRY(ft_gather_launch(ax, -1.0, (const double*)W_q, n2, 0, (double*)box.p + 2 * (size_t)i * n2, st));
+  }
+  hipLaunchKernelGGL(lat_absmax, dim3(8, nbox), dim3(256), 0, st, n2, (const double*)box.p, (unsigned long long*)red.p);
+  BSE_CHECK_LAUNCH();
+  std::vector<double> mx(2 * (size_t)nbox);
+  BSE_HIP(hipMemcpyAsync(mx.data(), red.p, 16 * (size_t)nbox, hipMemcpyDeviceToHost, st));
+  BSE_HIP(hipStreamSynchronize(st));
+  double top = 0.0;
+  for (double v : mx) top = std::max(top, v);
+  if (!(top > 0.0) || !std::isfinite(top)) return BSE_OK;
+  std::vector<int32_t> act, ids;
+  for (int r = 0; r < nbox; ++r) {
+    const bool zero = R[3 * r] == 0 && R[3 * r + 1] == 0 && R[3 * r + 2] == 0;
+    if (!(mx[2 * r] > 2e-15 * top || mx[2 * r + 1] > 2e-15 * top) && !zero) continue;
+    ids.push_back(r);
+    act.insert(act.end(), {R[3 * r], R[3 * r + 1], R[3 * r + 2]});
+  }
+  const int nR = (int)ids.size();
+  FtArgs ax;
+  if (!ft_axes(&ax, Nk, q.data(), nR, act.data(), nullptr)) return BSE_OK;
+  Lattice* L = new (std::nothrow) Lattice();
+  if (!L) return BSE_ENOMEM;
+  p->lat = L;
+  L->ax = ax;
+  L->nR = nR;
+  for (int r = 0; r < nR; ++r)
+    if (act[3 * r] == 0 && act[3 * r + 1] == 0 && act[3 * r + 2] == 0) L->r0 = r;
+  if (!lattice_applies(p, 1)) {
+    lattice_free(p);
+    return BSE_OK;
+  }
+  BSE_TRY(plan_alloc(p, (void**)&L->Wr, 8 * (size_t)nR * n2));
+  BSE_TRY(dmalloc(&idx.p, 4 * (size_t)nR));
+  BSE_TRY(dmalloc(&chk.p, 16 * (size_t)nR * n2));
+  BSE_HIP(hipMemcpyAsync(idx.p, ids.data(), 4 * (size_t)nR, hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(lat_take_real, dim3(64, nR), dim3(256), 0, st, n2, (const int*)idx.p, (const double*)box.p, L->Wr,
+                     (double*)chk.p);
+  BSE_CHECK_LAUNCH();
+  double* const dmax = (double*)red.p + 2 * (size_t)nbox;
+  BSE_TRY(ft_spread_launch(ax, 1.0, (const double*)chk.p, n2, 0, 1, 1, 0, 2, dmax, (const double*)W_q, st));
+  double off = 0.0;
+  BSE_HIP(hipMemcpyAsync(&off, dmax, 8, hipMemcpyDeviceToHost, st));
+  BSE_HIP(hipStreamSynchronize(st));
+  // |W_q| <= sum_R |W(R)|; the largest W(R) element is a lower bound of max |W_q| up to cancellation, so the
+  // comparison with it is the stricter one
+  if (!(off <= 1e-14 * top * std::sqrt((double)nR))) {
+    lattice_free(p);
+    return BSE_OK;
+  }
+  L->ldc = ((long long)na * no + 15) / 16 * 16 + 16;
+  BSE_TRY(plan_alloc(p, (void**)&L->C1, 16 * (size_t)(no * L->ldc)));
+  BSE_TRY(plan_alloc(p, (void**)&L->C3, 16 * (size_t)(no * L->ldc)));
+  hipLaunchKernelGGL(lat_pack_C, dim3(2048), dim3(256), 0, st, na, no, L->ldc, (const double*)C, L->C1, L->C3);
+  BSE_CHECK_LAUNCH();
+  // workspaces: all max_nb vectors at once and R in passes of about 4 GiB of U and V, fewer vectors when D(k) and
+  // the R arrays would not fit; 8 partial F(R) for the split of the last contraction, 32 of small ones
+  size_t room = budget;
+  if (const char* e = std::getenv("BSE_WORKSPACE_GB")) room = (size_t)(std::atof(e) * (double)(1ull << 30));
+  const size_t no2 = (size_t)no * no;
+  int nbc = p->max_nb;
+  auto fixed = [&](int b) { return 16 * no2 * b * ((size_t)Nk + 10 * (size_t)nR); };
+  while (nbc > 1 && fixed(nbc) > room / 2) nbc = (nbc + 1) / 2;
+  L->nbc = nbc;
+  const size_t per_r = 32 * (size_t)nc1 * nbc;
+  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / per_r));
+  const size_t f1 = 2 * no2 * nbc * (size_t)nR;
+  L->f_doubles = (long long)(f1 * (f1 > ((size_t)1 << 22) ? 8 : 32));
+  BSE_TRY(plan_alloc(p, (void**)&L->D, 16 * no2 * nbc * (size_t)Nk));
+  BSE_TRY(plan_alloc(p, (void**)&L->DR, 16 * no2 * nbc * (size_t)nR));
+  BSE_TRY(plan_alloc(p, (void**)&L->U, per_r / 2 * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->V, per_r / 2 * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
+  BSE_TRY(plan_alloc(p, (void**)&L->t, 16 * (size_t)na * nbc));
+  return BSE_OK;
+}
+
+int lattice_size(const Plan* p, int nb) { return lattice_applies(p, nb) ? p->lat->nR : 0; }
+
+bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_t st) {
+  const bse_dims& d = p->d;
+  Lattice* L = p->lat;
+  const int Nk = p->Nk, na = d.n_aux, no = d.n_ao, nR = L->nR;
+  const long long no2 = (long long)no * no, nu = (long long)na * no;
+  for (int b0 = 0; b0 < nb; b0 += L->nbc) {
+    const int w = std::min(L->nbc, nb - b0);
+    const long long E = no2 * w;
+    {
+      StageMark sm_(p, BSE_STAGE_PAIRDENS_V, st);
+      hipLaunchKernelGGL(lat_outer, dim3(Nk, w), dim3(256), lds_outer(p), st, d.nv, d.nc, no, nb, b0, w, p->psi64, X,
+                         L->D);
+      BSE_CHECK_LAUNCH();
+      BSE_TRY(ft_gather_launch(L->ax, 1.0, L->D, E, 1, L->DR, st));
+    }
+    // split of the last contraction's (t, mu) sum: enough parts for 1024 blocks of its tiles, at least 64 deep
+    const int rc = std::min(L->rc, nR);
+    const long long t3 = (long long)((no + 63) / 64) * ((no * w + 127) / 128) * rc;
+    const long long cap = std::min<long long>(L->f_doubles / (2 * E * nR), std::max<long long>(1, (long long)no * na / 64));
+    const int nsplit = (int)std::max<long long>(1, std::min<long long>(cap, (1024 + t3 - 1) / t3));
+    for (int r = 0; r < nR; r += rc) {
+      const int n = std::min(rc, nR - r);
+      LatGemm g{};
+      {
+        StageMark sm_(p, BSE_STAGE_PAIRDENS_C, st);
+        g.M = no * w;
+        g.N = na * no;
+        g.K = no;
+        g.Z = n;
+        g.A = L->DR + 2 * E * r;
+        g.lda = no;
+        g.a_ps = E;
+        g.a_z = 2 * E;
+        g.B = L->C1;
+        g.kd = no;
+        g.rs0 = L->ldc;
+        g.nd = na * no;
+        g.b_ps = no * L->ldc;
+        g.C = L->U;
+        g.ldc = 2 * nu;
+        g.c_ps = nu;
+        g.c_z = 2 * nu * no * w;
+        g.nsplit = 1;
+        g.klen = no;
+        BSE_TRY(lat_gemm_run<true>(g, st));
+      }
+      g = LatGemm{};
+      {
+        StageMark sm_(p, BSE_STAGE_WSTEP, st);
+        g.M = na;
+        g.N = 2 * no * w * no;
+        g.K = na;
+        g.Z = n;
+        g.A = L->Wr + (long long)r * na * na;
+        g.lda = na;
+        g.a_z = (long long)na * na;
+        g.B = L->U;
+        g.kd = na;
+        g.rs0 = no;
+        g.nd = no;
+        g.cs1 = nu;
+        g.b_z = 2 * nu * no * w;
+        g.C = L->V;
+        g.ldc = no;
+        g.cc1 = nu;
+        g.c_z = 2 * nu * no * w;
+        g.nsplit = 1;
+        g.klen = na;
+        BSE_TRY(lat_gemm_run<false>(g, st));
+      }
+      if (d.alpha != 0.0 && r <= L->r0 && L->r0 < r + n) {
+        StageMark sm_(p, BSE_STAGE_EXCHANGE, st);
+        const long long o = 2 * nu * no * w * (L->r0 - r);
+        if (nu <= 2048) {
+          hipLaunchKernelGGL(lat_ex_v<true>, dim3(na, w), dim3(64), 0, st, na, no, w, d.alpha, p->vbar, L->U + o,
+                             nullptr, L->V + o);
+        } else {
+          hipLaunchKernelGGL(lat_ex_t, dim3(na, w), dim3(64), 0, st, na, no, w, L->U + o, L->t);
+          hipLaunchKernelGGL(lat_ex_v<false>, dim3(na, w), dim3(64), 0, st, na, no, w, d.alpha, p->vbar, nullptr,
+                             L->t, L->V + o);
+        }
+        BSE_CHECK_LAUNCH();
+      }
+      g = LatGemm{};
+      {
+        StageMark sm_(p, BSE_STAGE_DBLOCK, st);
+        g.M = no;
+        g.N = w * no;
+        g.K = no * na;
+        g.Z = n;
+        g.A = L->C3;
+        g.lda = L->ldc;
+        g.a_ps = no * L->ldc;
+        g.B = L->V;
+        g.kd = na;
+        g.rs0 = no;
+        g.rs1 = 2 * nu * w;
+        g.nd = no;
+        g.cs1 = 2 * nu;
+        g.b_ps = nu;
+        g.b_z = 2 * nu * no * w;
+        g.C = L->F + 2 * E * r;
+        g.ldc = no;
+        g.cc1 = 2 * no2;
+        g.c_ps = no2;
+        g.c_z = 2 * E;
+        g.nsplit = nsplit;
+        g.klen = ((no * na + nsplit - 1) / nsplit + 15) / 16 * 16;
+        g.c_split = 2 * E * nR;
+        BSE_TRY(lat_gemm_run<true>(g, st));
+      }
+    }
+    {
+      StageMark sm_(p, BSE_STAGE_TX, st);
+      BSE_TRY(ft_spread_launch(L->ax, -1.0, L->F, E, 1, no2, nsplit, 2 * E * nR, 0, L->D, nullptr, st));
+      hipLaunchKernelGGL(lat_project, dim3(Nk, w), dim3(256), lds_project(p), st, d.nv, d.nc, no, nb, b0, w,
+                         project_groups(p), 1.0 / (double)Nk, p->eps, p->psi64, L->D, X, Y);
+      BSE_CHECK_LAUNCH();
+    }
+  }
+  return BSE_OK;
+}
+
+}  // namespace bse
