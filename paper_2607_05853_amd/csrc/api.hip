@@ -278,7 +278,7 @@ hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 // workspace bytes per q of a batch: Gv, P, T, and the conduction pair densities Mc unless the plan is
 // split (the BF16x3 apply never forms them; its adjoint allocates them on first use)
 size_t per_q_bytes(const Plan* p) {
-  const long long Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
+  const long long Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->given_aux;
   const size_t tc = p->two_centre ? (size_t)(p->prec == BSE_F64 ? 16 : 8) * 2 * (size_t)(Nk * (nv * nv + nc * nc) * na)
                                   : 0;
   return p->esz * (size_t)(Nk * nv * nv * na * 2 + (p->mc_direct ? Nk * nc * nc * na : 0) + Nk * nc * nc * nv * nv) +
@@ -421,10 +421,12 @@ struct TwoCentreIn {
   const double* kf = nullptr;   // host f64 [2][Nk][3]: k of the valence bands, then of the conduction bands
 };
 
-bse_status build_plan(Plan* p, const bse_dims* d, const double* eps_qp, const void* psi, const void* C,
+bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const double* eps_qp, const void* psi, const void* C,
                       const TwoCentreIn* tc, const void* Vbar, const void* W_q, bse_prec prec, int max_nb,
                       uint32_t flags, hipStream_t st) {
   p->d = *d;
+  p->given_ao = given->n_ao;
+  p->given_aux = given->n_aux;
   p->two_centre = tc ? 1 : 0;
   p->Nk = d->nk[0] * d->nk[1] * d->nk[2];
   p->nbnd = d->nv + d->nc;
@@ -740,7 +742,8 @@ bse_status build_plan(Plan* p, const bse_dims* d, const double* eps_qp, const vo
 
   // conduction side of the direct term
   if (p->split) {
-    const bool u_ok = (long long)nv * nv <= 128 && no <= 128;
+    // (by the sizes as given: the rounding chooses kernels, never the order of the contractions)
+    const bool u_ok = (long long)nv * nv <= 128 && given->n_ao <= 128;
     if (p->two_centre) {
       p->mc_direct = 1;  // the second centre puts mu on the psi_c'(k') side: no B_c(k) contraction
     } else if (flags & BSE_CONDUCTION_U) {
@@ -748,11 +751,12 @@ bse_status build_plan(Plan* p, const bse_dims* d, const double* eps_qp, const vo
     } else if (flags & BSE_CONDUCTION_MC) {
       p->mc_direct = 1;
     } else {
-      p->mc_direct = (!u_ok || prefer_mc(*d)) ? 1 : 0;
+      p->mc_direct = (!u_ok || prefer_mc(*given)) ? 1 : 0;
     }
   }
 
-  p->fused_wt = (p->split && p->mc_direct && nv == 8 && nc == 8 && na % 256 == 0 && Nk % 2 == 0) ? 1 : 0;
+  p->fused_wt =
+      (p->split && p->mc_direct && nv == 8 && nc == 8 && p->given_aux % 256 == 0 && Nk % 2 == 0) ? 1 : 0;
 
   // direct-term workspaces: at least 12 GiB, more where 16 q per batch need it and 40 % of the free
   // device memory allows (short q batches leave the pair-density tiles mostly empty)
@@ -803,7 +807,129 @@ bse_status build_plan(Plan* p, const bse_dims* d, const double* eps_qp, const vo
   return BSE_OK;
 }
 
+// out[i][r][c] = in[i][r][c] inside rows x cols, 0 outside, of elements of `words` doubles ([n][R][C] <- [n][rows][cols])
+__global__ void pad_matrices(long long n, int rows, int cols, int R, int C, int words, const double* __restrict__ in,
+                             double* __restrict__ out) {
+  const long long tot = n * R * C * words;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (long long)gridDim.x * blockDim.x) {
+    const int w = (int)(i % words);
+    const long long e = i / words;
+    const int c = (int)(e % C), r = (int)((e / C) % R);
+    const long long m = e / ((long long)C * R);
+    out[i] = r < rows && c < cols ? in[((m * rows + r) * cols + c) * words + w] : 0.0;
+  }
+}
+
+// out[i][r][c] = in[i][r][c], c128 [n][rows][cols] <- [n][R][C] with R, C the larger
+__global__ void crop_matrices(long long n, int rows, int cols, int R, int C, const double* __restrict__ in,
+                              double* __restrict__ out) {
+  const long long tot = n * rows * cols;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (long long)gridDim.x * blockDim.x) {
+    const int c = (int)(i % cols), r = (int)((i / cols) % rows);
+    const long long o = ((i / ((long long)cols * rows)) * R + r) * C + c;
+    out[2 * i] = in[2 * o];
+    out[2 * i + 1] = in[2 * o + 1];
+  }
+}
+
+// The sizes a BF16x3 plan stores.  Every k step of the direct-to-LDS kernels is 16 deep, so n_ao and n_aux
+// are rounded up to 16; other sizes ran on the register-staged kernels, which take 1.3 to 5 times as long (BF16x3
+// apply at 6x6x6: N_ao 71, N_aux 159 6.9 ms, 80 and 160 1.7 ms; 40 and 88 2.0 ms, 48 and 96 1.25 ms).  N_ao from 97
+// is taken to 128 (streaming pair densities; 112 and 240: 11.3 ms, 128 and 256: 10.3 ms) and N_aux within 16 of a
+// multiple of 256 to it (W step on whole 256-column tiles).  The added functions are zero and add exact zeros at the
+// end of each sum, so the results are those of the given sizes bit for bit.  FP32 plans keep theirs: their aligned
+// kernels sum in another order.
+bse_dims rounded_dims(const bse_dims* d) {
+  bse_dims r = *d;
+  r.n_ao = (d->n_ao + 15) / 16 * 16;
+  if (r.n_ao > 96 && r.n_ao < 128) r.n_ao = 128;
+  r.n_aux = (d->n_aux + 15) / 16 * 16;
+  if (r.n_aux % 256 == 240) r.n_aux += 16;
+  return r;
+}
+
+// build_plan on the rounded sizes, from zero-padded copies of the inputs; on the sizes as given where they are
+// round, on the other precisions, and where the copies would not fit comfortably
+bse_status build_rounded(Plan* p, const bse_dims* d, const double* eps_qp, const void* psi, const void* C,
+                         const TwoCentreIn* tc, const void* Vbar, const void* W_q, bse_prec prec, int max_nb,
+                         uint32_t flags, hipStream_t st) {
+  const bse_dims r = rounded_dims(d);
+  const long long Nk = (long long)d->nk[0] * d->nk[1] * d->nk[2];
+  bool same = prec != BSE_BF16X3 || (r.n_ao == d->n_ao && r.n_aux == d->n_aux);
+  const size_t n_psi = (size_t)Nk * (d->nv + d->nc) * r.n_ao, n_c = (size_t)r.n_aux * r.n_ao * r.n_ao,
+               n_w = (size_t)r.n_aux * r.n_aux;
+  if (!same) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
+    const size_t need = 16 * (n_psi + n_c * (tc ? (size_t)tc->nR : 1) + n_w * (Nk + 1));
+    same = need > free_b / 4;
+  }
+  if (same) return build_plan(p, d, d, eps_qp, psi, C, tc, Vbar, W_q, prec, max_nb, flags, st);
+  struct Copy {
+    double* p = nullptr;
+    ~Copy() { dfree(p); }
+  } psi_r, c_r, v_r, w_r;
+  auto pad = [&](Copy& to, const void* in, long long n, int rows, int cols, int R, int Cc, int words) -> bse_status {
+    BSE_TRY(dmalloc((void**)&to.p, 8 * (size_t)n * R * Cc * words));
+    hipLaunchKernelGGL(pad_matrices, dim3(4096), dim3(256), 0, st, n, rows, cols, R, Cc, words, (const double*)in, to.p);
+    BSE_CHECK_LAUNCH();
+    return BSE_OK;
+  };
+  const int no = d->n_ao, na = d->n_aux, nb = d->nv + d->nc;
+  BSE_TRY(pad(psi_r, psi, Nk, nb, no, nb, r.n_ao, 2));
+  BSE_TRY(pad(v_r, Vbar, 1, na, na, r.n_aux, r.n_aux, 2));
+  BSE_TRY(pad(w_r, W_q, Nk, na, na, r.n_aux, r.n_aux, 2));
+  TwoCentreIn tcr;
+  if (tc) {
+    // [nR][na][no][no] real: the AO pair first, then whole [no][no] matrices of added auxiliary functions
+    Copy ao;
+    BSE_TRY(pad(ao, tc->C_R, (long long)tc->nR * na, no, no, r.n_ao, r.n_ao, 1));
+    BSE_TRY(pad(c_r, ao.p, tc->nR, na, r.n_ao * r.n_ao, r.n_aux, r.n_ao * r.n_ao, 1));
+    BSE_HIP(hipStreamSynchronize(st));
+    tcr = *tc;
+    tcr.C_R = c_r.p;
+  } else {
+    BSE_TRY(dmalloc((void**)&c_r.p, 16 * n_c));
+    BSE_TRY(zero_fill(c_r.p, 16 * n_c, st));
+    hipLaunchKernelGGL(pad_matrices, dim3(4096), dim3(256), 0, st, (long long)na, no, no, r.n_ao, r.n_ao, 2,
+                       (const double*)C, c_r.p);
+    BSE_CHECK_LAUNCH();
+  }
+  const bse_status s = build_plan(p, &r, d, eps_qp, psi_r.p, tc ? nullptr : c_r.p, tc ? &tcr : nullptr, v_r.p, w_r.p,
+                                  prec, max_nb, flags, st);
+  (void)hipStreamSynchronize(st);  // the copies are released here
+  return s;
+}
+
 }  // namespace
+
+bse_status adjoint_buffer(Plan* p, void* g_Wq, double** gq) {
+  *gq = (double*)g_Wq;
+  const size_t na = p->d.n_aux, ga = p->given_aux;
+  if (!*gq || ga != na) {
+    if (!p->gq_acc) BSE_TRY(plan_alloc(p, (void**)&p->gq_acc, 16 * (size_t)p->Nk * na * na));
+    *gq = p->gq_acc;
+  }
+  if (!g_Wq && ga != na && !p->gq_crop) BSE_TRY(plan_alloc(p, (void**)&p->gq_crop, 16 * (size_t)p->Nk * ga * ga));
+  return BSE_OK;
+}
+
+bse_status adjoint_outputs(Plan* p, double* gq, void* g_Wq, void* g_WR, hipStream_t st) {
+  const int na = p->d.n_aux, ga = p->given_aux;
+  if (ga != na) {
+    double* out = g_Wq ? (double*)g_Wq : p->gq_crop;
+    hipLaunchKernelGGL(crop_matrices, dim3(4096), dim3(256), 0, st, (long long)p->Nk, ga, ga, na, na, gq, out);
+    BSE_CHECK_LAUNCH();
+    gq = out;
+  }
+  if (g_WR) {
+    const int nR = (int)p->wR.size();
+    const std::vector<double> q = plan_kfrac(p);
+    BSE_TRY(interp_adjoint(ga, nR, p->R.data(), p->wR.data(), p->Nk, q.data(), gq, (double*)g_WR, st));
+  }
+  return BSE_OK;
+}
+
 }  // namespace bse
 
 using namespace bse;
@@ -936,7 +1062,7 @@ bse_status plan_create(const char* fn, const bse_dims* d, const double* eps_qp, 
     set_error(f + ": host allocation failed");
     return BSE_ENOMEM;
   }
-  bse_status s = build_plan(&h->impl, d, eps_qp, psi, C, tc, Vbar, W_q, prec, max_nb, flags, S(hip_stream));
+  bse_status s = build_rounded(&h->impl, d, eps_qp, psi, C, tc, Vbar, W_q, prec, max_nb, flags, S(hip_stream));
   if (s != BSE_OK) {
     destroy_plan(&h->impl);
     delete h;
@@ -1127,19 +1253,10 @@ bse_status bse_apply_adjoint(bse_plan* plan, const void* Ybar, const void* X, in
   hipStream_t st = S(hip_stream);
   if (g_eps) BSE_TRY(adjoint_eps(p, (const double*)Ybar, (const double*)X, nb, g_eps, false, st));
   if (!g_WR && !g_Wq) return BSE_OK;
-  const int na = p->d.n_aux;
-  double* gq = (double*)g_Wq;
-  if (!gq) {
-    if (!p->gq_acc) BSE_TRY(plan_alloc(p, (void**)&p->gq_acc, 16 * (size_t)p->Nk * na * na));
-    gq = p->gq_acc;
-  }
+  double* gq = nullptr;
+  BSE_TRY(adjoint_buffer(p, g_Wq, &gq));
   BSE_TRY(adjoint_direct(p, (const double*)Ybar, (const double*)X, nb, gq, false, st));
-  if (g_WR) {
-    const int nR = (int)p->wR.size();
-    const std::vector<double> q = plan_kfrac(p);
-    BSE_TRY(interp_adjoint(na, nR, p->R.data(), p->wR.data(), p->Nk, q.data(), gq, (double*)g_WR, st));
-  }
-  return BSE_OK;
+  return adjoint_outputs(p, gq, g_Wq, g_WR, st);
 }
 
 bse_status bse_density_start(const bse_plan* plan, const void* psi, void* P, void* hip_stream) {
@@ -1151,7 +1268,7 @@ bse_status bse_density_start(const bse_plan* plan, const void* psi, void* P, voi
   const Plan* p = &plan->impl;
   hipStream_t st = S(hip_stream);
   hipLaunchKernelGGL(density_kernel, dim3((unsigned)((p->N + 255) / 256)), dim3(256), 0, st, p->N, p->d.nv,
-                     p->d.nc, p->d.n_ao, (const double*)psi, (double*)P);
+                     p->d.nc, p->given_ao, (const double*)psi, (double*)P);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_error(std::string("bse_density_start: ") + hipGetErrorString(e));

@@ -1416,7 +1416,7 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
   const Arith ar = arith_of(p->prec);
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
-  const bool tn = p->split && (nv * nv) % 8 == 0 && na % 8 == 0;
+  const bool tn = p->split && (nv * nv) % 8 == 0 && p->given_aux % 8 == 0;
   if (!p->Mc) BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->qb * Nk * nc * nc * na));
   if (tn && p->herm_half) {
     // pair symmetry of the gradient: with Hermitian C^mu the pairs (k, k - q) of g_W(-q) carry the pair

@@ -132,7 +132,10 @@ constexpr int TX_CHUNKS = 16;
 struct Lattice;  // lattice.hip
 
 struct Plan {
+  // sizes of the stored problem: as given on FP64 and FP32 plans; on BF16x3 plans n_ao and n_aux rounded up so
+  // that the direct-to-LDS kernels take every product, the added functions zero (given_ao, given_aux: as given)
   bse_dims d{};
+  int given_ao = 0, given_aux = 0;
   int Nk = 0, nt = 0, nbnd = 0;
   long long N = 0;
   bse_prec prec = BSE_F64;
@@ -217,6 +220,7 @@ struct Plan {
   std::vector<int32_t> R;
   std::vector<double> wR;
   double* gq_acc = nullptr;   // c128 [Nk][n_aux][n_aux]
+  double* gq_crop = nullptr;  // c128 [Nk][given_aux][given_aux] where that is smaller
 
   std::vector<DevBuf> owned;
   size_t bytes = 0;
@@ -254,6 +258,10 @@ bse_status apply_diag(Plan* p, const double* X, double* Y, int nb, hipStream_t s
 bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, double* gWq, bool acc,
                           hipStream_t st);
 bse_status direct_u_b3(Plan* p, int q0, int nq, const int* kq, hipStream_t st);
+// the W(q) and W(R) gradients asked for, from g_W(q) accumulated in the plan's sizes: the caller's buffer (or the
+// plan's) to accumulate in, then the outputs
+bse_status adjoint_buffer(Plan* p, void* g_Wq, double** gq);
+bse_status adjoint_outputs(Plan* p, double* gq, void* g_Wq, void* g_WR, hipStream_t st);
 bse_status adjoint_eps(Plan* p, const double* Ybar, const double* X, int nb, double* geps, bool acc,
                        hipStream_t st);
 // the application over lattice vectors (lattice.hip): built at plan creation where W_q allows it, chosen per

@@ -447,7 +447,8 @@ bse_status direct_u_b3(Plan* p, int q0, int nq, const int* kq, hipStream_t st) {
   u.T = (float*)p->T;
   u.psis = (const __bf16*)p->psi;
   u.ps_psi = p->ps_psi;
-  u.mfma_epi = nv2 <= 64 && d.n_ao % 8 == 0 && p->ps_psi % 8 == 0 &&
+  // by the sizes as given (the epilogue on the matrix cores splits U once more, the vector-unit one does not)
+  u.mfma_epi = nv2 <= 64 && p->given_ao % 8 == 0 && p->given_aux % 16 == 0 && p->ps_psi % 8 == 0 &&
                (reinterpret_cast<uintptr_t>(p->psi) & 15) == 0;
   const dim3 grid((unsigned)((long long)((nq + u.qg - 1) / u.qg) * d.nc * p->Nk));
   const bool dma = d.n_aux % 16 == 0 && u.ps_BcT % 8 == 0 && u.ps_P % 8 == 0 &&

@@ -393,11 +393,8 @@ extern "C" bse_status bse_haydock_vjp(bse_plan* plan, const void* basis, const d
   BSE_TRY(wk.get(&Yp, 16 * (size_t)N * chunk));
   BSE_TRY(wk.get(&cy, 16 * (size_t)m * chunk));
   BSE_TRY(wk.get(&cyt, 16 * (size_t)m * chunk));
-  double* gq = (double*)g_Wq;
-  if (!gq && g_WR) {
-    if (!p->gq_acc) BSE_TRY(plan_alloc(p, (void**)&p->gq_acc, 16 * (size_t)p->Nk * na * na));
-    gq = p->gq_acc;
-  }
+  double* gq = nullptr;
+  if (g_Wq || g_WR) BSE_TRY(adjoint_buffer(p, g_Wq, &gq));
   const bool want_w = gq != nullptr;
   if (want_w) BSE_TRY(zero_fill(gq, 16 * (size_t)p->Nk * na * na, st));
   if (g_eps) BSE_TRY(zero_fill(g_eps, 8 * (size_t)p->Nk * p->nbnd, st));
@@ -443,11 +440,7 @@ extern "C" bse_status bse_haydock_vjp(bse_plan* plan, const void* basis, const d
       BSE_HIP(hipStreamSynchronize(st));
     }
   }
-  if (g_WR) {
-    const std::vector<double> q = plan_kfrac(p);
-    BSE_TRY(interp_adjoint(na, (int)p->wR.size(), p->R.data(), p->wR.data(), p->Nk, q.data(), gq,
-                           (double*)g_WR, st));
-  }
+  if (want_w) BSE_TRY(adjoint_outputs(p, gq, g_Wq, g_WR, st));
   return BSE_OK;
 }
 
