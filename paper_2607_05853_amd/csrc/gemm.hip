@@ -1214,6 +1214,128 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 }
 
+// 128 x 64 tiles of the same product with a c64 / c128 result, for per-pair products of 65 rows and more and at
+// most 64 columns (the direct block T = M_c P^T at n_c > 8: 100 x 36 at the 12x12x12 workload, where a 128 x 128
+// tile is 22 % full: direct blocks 245 -> 182 ms per apply): four waves of 32 x 64, 48 KiB of LDS, three blocks per CU, so that the operands of three
+// tiles stream in at once (the product reads its operands once and is bound by that).  A's four and B's two
+// 32-row DMA blocks go to waves 0..3 and 0..1.  Each accumulator receives the same MFMA sequence as in
+// cgemm_b3_dma, so the results are identical.
+template <int CJA, int CJB, typename TC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void cgemm_b3_dma_n64(GemmArgs g) {
+  constexpr int BM = 128, BN = 64, BK = 16;
+  constexpr int PA = BM * BK, PB = BN * BK;  // bf16 per plane per stage
+  constexpr int STAGE = 4 * (PA + PB);
+  constexpr int RBA = BM / 32, RB = (BM + BN) / 32;
+  __shared__ __attribute__((aligned(1024))) __bf16 smem[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nK = g.K / BK;
+  const int gyn = (g.M + BM - 1) / BM;
+  long long bl, t;
+  xcd_map(blockIdx.x, gyn, g.batch, bl, t);
+  const int b = (int)bl, m0 = (int)t * BM;
+  // DMA slot of 32-row block rb as in cgemm_b3_dma_m64; rows past the edge re-load a valid row
+  auto slot = [&](int rb, const __bf16*& src, int& lo, long long& ps, int& pstride) {
+    const bool isA = rb < RBA;
+    const int r = 32 * (isA ? rb : rb - RBA) + (lane >> 1);
+    const int chunk = (lane & 1) ^ ((r >> 3) & 1);
+    if (isA) {
+      const int arow = (m0 + r < g.M) ? m0 + r : m0;
+      src = (const __bf16*)g.A + off_of(g.a_tab, g.a_tab_pb, g.a_sb, g.a_si, b, g.M, arow) + 8 * chunk;
+      lo = 32 * rb * BK;
+      ps = g.a_ps;
+      pstride = PA;
+    } else {
+      const int bcol = r < g.N ? r : 0;
+      src = (const __bf16*)g.B + off_of(g.b_tab, g.b_tab_pb, g.b_sb, g.b_sj, b, g.N, bcol) + 8 * chunk;
+      lo = 4 * PA + 32 * (rb - RBA) * BK;
+      ps = g.b_ps;
+      pstride = PB;
+    }
+  };
+  const __bf16 *src0 = nullptr, *src1 = nullptr;
+  int lo0 = 0, lo1 = 0, pst0 = 0, pst1 = 0;
+  long long ps0 = 0, ps1 = 0;
+  slot(wave, src0, lo0, ps0, pst0);
+  const bool two = wave + 4 < RB;
+  if (two) slot(wave + 4, src1, lo1, ps1, pst1);
+  auto issue = [&](int kt) {
+    __bf16* st = smem + (kt & 1) * STAGE;
+    const int kb = kt * BK;
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl)
+      __builtin_amdgcn_global_load_lds((const void*)(src0 + pl * ps0 + kb),
+                                       (__attribute__((address_space(3))) void*)(st + lo0 + pl * pst0), 16, 0, 0);
+    if (two) {
+#pragma unroll
+      for (int pl = 0; pl < 4; ++pl)
+        __builtin_amdgcn_global_load_lds((const void*)(src1 + pl * ps1 + kb),
+                                         (__attribute__((address_space(3))) void*)(st + lo1 + pl * pst1), 16, 0, 0);
+    }
+  };
+  f16v accR[2], accI[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      accR[j][r] = 0.f;
+      accI[j][r] = 0.f;
+    }
+  const bool rows = m0 + 32 * wave < g.M, wide = g.N > 32;  // sub-tiles that hold part of the result
+  issue(0);
+  const int ch = lane >> 5;
+  for (int kt = 0; kt < nK; ++kt) {
+    vm_lds_barrier<0>();
+    if (kt + 1 < nK) issue(kt + 1);
+    if (!rows) continue;
+    const __bf16* sa = smem + (kt & 1) * STAGE;
+    const __bf16* sb = sa + 4 * PA;
+    bf8v a[4], bb[2][4];
+    {
+      const int row = 32 * wave + (lane & 31);
+      const int o = row * BK + 8 * (ch ^ ((row >> 3) & 1));
+#pragma unroll
+      for (int pl = 0; pl < 4; ++pl) a[pl] = *reinterpret_cast<const bf8v*>(sa + pl * PA + o);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = j * 32 + (lane & 31);
+      const int o = col * BK + 8 * (ch ^ ((col >> 3) & 1));
+#pragma unroll
+      for (int pl = 0; pl < 4; ++pl) bb[j][pl] = *reinterpret_cast<const bf8v*>(sb + pl * PB + o);
+      if (CJB) {
+        bb[j][2] = neg8(bb[j][2]);
+        bb[j][3] = neg8(bb[j][3]);
+      }
+    }
+    if (CJA) {
+      a[2] = neg8(a[2]);
+      a[3] = neg8(a[3]);
+    }
+    const bf8v nih = neg8(a[2]), nil = neg8(a[3]);
+    cmma_b3(a, nih, nil, bb[0], accR[0], accI[0]);
+    if (wide) cmma_b3(a, nih, nil, bb[1], accR[1], accI[1]);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = m0 + 32 * wave + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (row >= g.M) continue;
+    const long long ro = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, row);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = j * 32 + (lane & 31);
+      if (col >= g.N) continue;
+      TC* o = (TC*)g.C + 2 * (ro + (long long)col * g.c_sj);
+      double vr = g.alpha * (double)accR[j][r], vi = g.alpha * (double)accI[j][r];
+      if (g.beta) {
+        vr += (double)o[0];
+        vi += (double)o[1];
+      }
+      o[0] = (TC)vr;
+      o[1] = (TC)vi;
+    }
+  }
+}
+
 // 128 x 256 tiles of the same product with the result written pre-split, for long-K products with a wide
 // B (the W step: K = N = N_aux).  Eight waves of 64 x 64 (two per SIMD, one block per CU) and three LDS
 // stages of 48 KiB: the loads of stage kt + 2 are issued while stage kt is multiplied, so two k steps of
@@ -1235,18 +1357,19 @@ constexpr int WB_STAGE = 4 * (WB_BM + WB_BN) * WB_BK;  // bf16 per stage
 constexpr size_t WB_LDS = (size_t)WB_NS * WB_STAGE * sizeof(__bf16);  // 144 KiB
 
 // The main loop of the wide tile: rows m0 .. m0 + 127, columns n0 .. n0 + 255 of batch entry b, all of K.
-// Wave (wm, wn) = (wave / 4, wave % 4) ends with the 64 x 64 block at rows 64 wm, columns 64 wn of the
-// tile in accR / accI ([i][j]: 32 x 32 sub-tiles); every wave has finished with LDS on return.
-template <int CJA, int CJB>
+// Wave (wm, wn) = (wave / (BN / 64), wave % (BN / 64)) ends with the 64 x 64 block at rows 64 wm, columns 64 wn
+// of the tile in accR / accI ([i][j]: 32 x 32 sub-tiles); every wave has finished with LDS on return.
+template <int CJA, int CJB, int BM = WB_BM, int BN = WB_BN>
 __device__ __forceinline__ void wide_tile_kloop(const GemmArgs& g, __bf16* smem, int b, int m0, int n0,
                                                 f16v (&accR)[2][2], f16v (&accI)[2][2]) {
-  constexpr int BM = WB_BM, BN = WB_BN, BK = WB_BK, NS = WB_NS;
+  constexpr int BK = WB_BK, NS = WB_NS;
+  static_assert(BM * BN == WB_BM * WB_BN && BM + BN == WB_BM + WB_BN, "128 x 256 or 256 x 128");
   constexpr int PA = BM * BK, PB = BN * BK;  // bf16 per plane per stage
   constexpr int STAGE = WB_STAGE;
   constexpr int RBA = BM / 32, RB = (BM + BN) / 32;
   static_assert(RB <= 16 && RB > 8, "two DMA blocks at most per wave");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / (BN / 64), wn = wave % (BN / 64);
   const int nK = g.K / BK;
   // DMA slot of 32-row block rb: lane -> row 32 rb' + lane / 2, 16-byte chunk (lane % 2) ^ bit 3 of the
   // row; rows past the matrix edge re-load a valid row (their products are never stored)
@@ -1401,13 +1524,14 @@ __device__ __forceinline__ void wide_tile_kloop(const GemmArgs& g, __bf16* smem,
   vm_lds_barrier<0>();  // every wave is done with the stages before the caller reuses LDS
 }
 
-template <int CJA, int CJB>
+// BM x BN = 128 x 256, or 256 x 128 where N leaves a 256-column tile half empty (N_aux = 384: the W step of the
+// 12x12x12 workload)
+template <int CJA, int CJB, int BM = WB_BM, int BN = WB_BN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void cgemm_b3_dma_w(GemmArgs g) {
-  constexpr int BM = WB_BM, BN = WB_BN;
   extern __shared__ __attribute__((aligned(1024))) __bf16 smem_w[];
   __bf16* smem = smem_w;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / (BN / 64), wn = wave % (BN / 64);
   const int gxn = (g.N + BN - 1) / BN, gyn = (g.M + BM - 1) / BM;
   const long long per_batch = (long long)gxn * gyn;
   long long bl, t;
@@ -1416,9 +1540,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int m0, n0;
   tile_of(t, gxn, gyn, BM, BN, m0, n0);
   f16v accR[2][2], accI[2][2];
-  wide_tile_kloop<CJA, CJB>(g, smem, b, m0, n0, accR, accI);
+  wide_tile_kloop<CJA, CJB, BM, BN>(g, smem, b, m0, n0, accR, accI);
   // the real parts, then the imaginary parts, of the whole tile through LDS as two planes (hi, lo) of
-  // [128][256], then 16-byte stores; the real accumulators are dead before the imaginary ones are staged
+  // [BM][BN], then 16-byte stores; the real accumulators are dead before the imaginary ones are staged
   static_assert(2 * BM * BN <= WB_NS * WB_STAGE, "epilogue staging must fit in the stages");
   __bf16* sC = smem;
   const float al = (float)g.alpha;
@@ -1441,7 +1565,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll 2
     for (int it = 0; it < 16; ++it) {
       const int id = tid + 512 * it;
-      const int c8 = id & 31, row = (id >> 5) & 127, pl = id >> 12;
+      const int c8 = id % (BN / 8), row = (id / (BN / 8)) % BM, pl = id / (BN / 8 * BM);
       const int grow = m0 + row, gcol = n0 + c8 * 8;
       if (grow < g.M && gcol < g.N) {
         const long long ro = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, grow);
@@ -1490,7 +1614,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wm = wave >> 2, wn = wave & 3;
   const int gyn = g.M / BM;
   long long bl, t;
-  xcd_map(blockIdx.x, gyn, g.batch, bl, t);
+  xcd_map<true>(blockIdx.x, gyn, g.batch, bl, t);
   const int b = (int)bl;
   const int m0 = (int)t * BM, k0 = m0 / 64;
   const int na = g.N;
@@ -2350,6 +2474,20 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
       BSE_CHECK_LAUNCH();
       return BSE_OK;
     }
+    if (!c_split && g.M > 64 && g.N <= 64) {  // taller per-pair products: 128 x 64 tiles
+      const long long tiles = (long long)((g.M + 127) / 128) * g.batch;
+      if (tiles < (1LL << 31)) {
+        auto go = [&](auto kern) -> bse_status {
+          hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), 0, st, g);
+          BSE_CHECK_LAUNCH();
+          return BSE_OK;
+        };
+        if (g.conjA && g.conjB) return out_f64 ? go(cgemm_b3_dma_n64<1, 1, double>) : go(cgemm_b3_dma_n64<1, 1, float>);
+        if (g.conjA) return out_f64 ? go(cgemm_b3_dma_n64<1, 0, double>) : go(cgemm_b3_dma_n64<1, 0, float>);
+        if (g.conjB) return out_f64 ? go(cgemm_b3_dma_n64<0, 1, double>) : go(cgemm_b3_dma_n64<0, 1, float>);
+        return out_f64 ? go(cgemm_b3_dma_n64<0, 0, double>) : go(cgemm_b3_dma_n64<0, 0, float>);
+      }
+    }
     if (c_split && g.K <= 64) {  // short K: 64 x 64 tiles, five blocks per CU
       const long long tiles = (long long)((g.N + 63) / 64) * ((g.M + 63) / 64) * g.batch;
       if (tiles < (1LL << 31)) {
@@ -2364,8 +2502,11 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
       return g.K == 64 ? launch_stream<4, false>(g, st) : launch_stream<8, false>(g, st);
     }
     if (c_split && g.K >= WB_MIN_K && g.N >= 256 && g.M >= 128 && wide_tiles_enabled()) {
-      // long K and a wide B (the W step): 128 x 256 tiles, three LDS stages
-      const long long tiles = (long long)((g.N + WB_BN - 1) / WB_BN) * ((g.M + WB_BM - 1) / WB_BM) * g.batch;
+      // long K and a wide B (the W step): 128 x 256 tiles, three LDS stages; 256 x 128 where the last 256 columns
+      // would be at most half full (12x12x12, N = 384: W step 243 -> 200 ms per apply)
+      const bool tall = (g.N - 1) % WB_BN < WB_BN / 2 && g.M >= WB_BN;
+      const int bm = tall ? WB_BN : WB_BM, bn = tall ? WB_BM : WB_BN;
+      const long long tiles = (long long)((g.N + bn - 1) / bn) * ((g.M + bm - 1) / bm) * g.batch;
       if (tiles < (1LL << 31)) {
         const dim3 grid((unsigned)tiles), block(512);
         auto go = [&](auto kern) -> bse_status {
@@ -2374,6 +2515,12 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
           BSE_CHECK_LAUNCH();
           return BSE_OK;
         };
+        if (tall) {
+          if (g.conjA && g.conjB) return go(cgemm_b3_dma_w<1, 1, WB_BN, WB_BM>);
+          if (g.conjA) return go(cgemm_b3_dma_w<1, 0, WB_BN, WB_BM>);
+          if (g.conjB) return go(cgemm_b3_dma_w<0, 1, WB_BN, WB_BM>);
+          return go(cgemm_b3_dma_w<0, 0, WB_BN, WB_BM>);
+        }
         if (g.conjA && g.conjB) return go(cgemm_b3_dma_w<1, 1>);
         if (g.conjA) return go(cgemm_b3_dma_w<1, 0>);
         if (g.conjB) return go(cgemm_b3_dma_w<0, 1>);

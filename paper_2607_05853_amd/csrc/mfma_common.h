@@ -39,10 +39,15 @@ __device__ __forceinline__ long long off_of(const long long* tab, int pb, long l
 // deals consecutive workgroups round-robin to the 8 XCDs (each with its own
 // L2); this maps the j-th block landing on XCD x to batch x + 8 (j / per_batch)
 // so every block of one batch entry (which share operand panels) runs on the
-// same XCD, back to back.  Falls back to the identity when nbatch % 8 != 0.
+// same XCD, back to back.  The last nbatch % 8 entries go round the XCDs block by
+// block (W step of 5x6x5 k, N_aux 256, 76 q: apply 1.74 -> 1.54 ms); with WHOLE the
+// identity is taken when nbatch % 8 != 0, which suits a kernel whose blocks share
+// only the smaller operand (the fused W step on 29 q: 62.5 ms against 64.0).
+template <bool WHOLE = false>
 __device__ __forceinline__ void xcd_map(long long L, long long per_batch, long long nbatch, long long& bt,
                                         long long& t) {
-  if ((nbatch & 7) == 0) {
+  const long long whole = WHOLE && (nbatch & 7) ? 0 : (nbatch & ~7LL) * per_batch;
+  if (L < whole) {
     const long long x = L & 7, j = L >> 3;
     bt = x + 8 * (j / per_batch);
     t = j % per_batch;
