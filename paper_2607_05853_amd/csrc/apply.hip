@@ -679,7 +679,7 @@ bse_status tc_combine(Plan* p, int nq, int na_, int nb_, int q0, const int* kq, 
 //   (the second centre's term, C^mu(k') acting on psi(k'), is the first centre's term of the reversed
 //   pair because C(R) is real)
 bse_status form_pair_densities(Plan* p, int q0, int nq, bool need_c, const int* kq, hipStream_t st,
-                                 bool c_split = false) {
+                                 bool c_split = false, bool need_v = true) {
   const bse_dims& d = p->d;
   const int Nk = p->Nk, nv = d.nv, nc = d.nc, na = d.n_aux, no = d.n_ao;
   const Arith ar = arith_of(p->prec);
@@ -695,7 +695,7 @@ bse_status form_pair_densities(Plan* p, int q0, int nq, bool need_c, const int* 
                          p->tab_psi_v, p->tab_psi_c, p->tab_mv, p->tab_mc);
       BSE_CHECK_LAUNCH();
     }
-    {
+    if (need_v) {
       StageMark sm_(p, BSE_STAGE_PAIRDENS_V, st);
       GemmArgs g;
       g.batch = Nk;
@@ -1330,15 +1330,10 @@ bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t
   return BSE_OK;
 }
 
-// One q batch of the k-major BF16x3 adjoint: Z = Gm conj(Mc) (or, for the partner, Z' = G' Mc) written
-// pre-split into P, then g_W of the batch's q = -(1/N_k) sum over pairs of Gv^T Z (conj(Gv)^T Z'), stored
-// at the W-gradient index given by dst (plan-order q -> dense-mesh q) or at q0 + i without a table
-bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int* kq, const int* dst,
-                           const double* Ybar, const double* X, int nb, double* gWq, bool acc, hipStream_t st) {
-  const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
-  const long long pair_v = (long long)nv * nv * na, pair_c = (long long)nc * nc * na;
-  const long long nt2 = (long long)nc * nc * nv * nv;
-  __bf16* G = (__bf16*)p->T + (long long)i0 * Nk * nt2;
+// Gm (swap: G') of the nq q from q0 on, k-major and split, at plane stride ps
+bse_status adjoint_gm(Plan* p, int q0, int nq, bool swap, const int* kq, const double* Ybar, const double* X, int nb,
+                      __bf16* G, long long ps, hipStream_t st) {
+  const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc;
   // two padded slices: 2 nt (nb + 1) complex, <= 64 KiB + 32 nt bytes since nv nc max_nb <= 2048
   const size_t gsh = 2 * (size_t)nc * nv * (nb + 1) * 16;
   static bool gsh_attr = false;
@@ -1350,12 +1345,57 @@ bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int
     gsh_attr = true;
   }
   if (swap)
-    hipLaunchKernelGGL(adj_gmT_split_kernel<true>, dim3(nq * Nk), dim3(256), gsh, st, Nk, nq, q0 + i0, nv, nc, nb, kq,
-                       Ybar, X, G, p->ps_T);
+    hipLaunchKernelGGL(adj_gmT_split_kernel<true>, dim3(nq * Nk), dim3(256), gsh, st, Nk, nq, q0, nv, nc, nb, kq,
+                       Ybar, X, G, ps);
   else
-    hipLaunchKernelGGL(adj_gmT_split_kernel<false>, dim3(nq * Nk), dim3(256), gsh, st, Nk, nq, q0 + i0, nv, nc, nb,
-                       kq, Ybar, X, G, p->ps_T);
+    hipLaunchKernelGGL(adj_gmT_split_kernel<false>, dim3(nq * Nk), dim3(256), gsh, st, Nk, nq, q0, nv, nc, nb,
+                       kq, Ybar, X, G, ps);
   BSE_CHECK_LAUNCH();
+  return BSE_OK;
+}
+
+// gWq[q][mu][nu] = -(1/N_k) sum_{(k v' v)} Gv[(k v' v)][mu] Z[(k v' v)][nu] of nq q from batch-local q i0 on
+// (conj(Gv) for the partners, swap)
+bse_status adjoint_gw(Plan* p, int q0, int i0, int nq, bool swap, const int* dst, const __bf16* Z, double* gWq, bool acc,
+                      hipStream_t st) {
+  const int Nk = p->Nk, nv = p->d.nv, na = p->d.n_aux;
+  const long long pair_v = (long long)nv * nv * na;
+  GemmArgs g;
+  g.batch = nq;
+  g.M = na;
+  g.N = na;
+  g.K = Nk * nv * nv;
+  g.A = (const __bf16*)p->Mv + (long long)i0 * Nk * pair_v;
+  g.a_sb = (long long)Nk * pair_v;
+  g.a_si = 1;
+  g.a_sk = na;
+  g.a_ps = p->ps_Mv;
+  g.conjA = swap ? 1 : 0;
+  g.B = Z + (long long)i0 * Nk * pair_v;
+  g.b_sb = (long long)Nk * pair_v;
+  g.b_sk = na;
+  g.b_sj = 1;
+  g.b_ps = p->ps_Mv;
+  g.C = dst ? gWq : gWq + 2 * (long long)(q0 + i0) * na * na;
+  g.c_bidx = dst ? dst + q0 + i0 : nullptr;
+  g.c_sb = (long long)na * na;
+  g.c_si = na;
+  g.c_sj = 1;
+  g.alpha = -1.0 / (double)Nk;
+  g.beta = acc ? 1 : 0;
+  return cgemm_split(g, true, true, false, true, st);
+}
+
+// One q batch of the k-major BF16x3 adjoint: Z = Gm conj(Mc) (or, for the partner, Z' = G' Mc) written
+// pre-split into P, then g_W of the batch's q = -(1/N_k) sum over pairs of Gv^T Z (conj(Gv)^T Z'), stored
+// at the W-gradient index given by dst (plan-order q -> dense-mesh q) or at q0 + i without a table
+bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int* kq, const int* dst,
+                           const double* Ybar, const double* X, int nb, double* gWq, bool acc, hipStream_t st) {
+  const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
+  const long long pair_v = (long long)nv * nv * na, pair_c = (long long)nc * nc * na;
+  const long long nt2 = (long long)nc * nc * nv * nv;
+  __bf16* G = (__bf16*)p->T + (long long)i0 * Nk * nt2;
+  BSE_TRY(adjoint_gm(p, q0 + i0, nq, swap, kq, Ybar, X, nb, G, p->ps_T, st));
   {  // Z[(v'v)][nu] = sum_{c'c} Gm[(v'v)][(c'c)] conj(Mc[(c'c)][nu]); the partner: Z' = sum G'[.][(c c')] Mc[(c c')]
     GemmArgs g;
     g.batch = nq * Nk;
@@ -1380,31 +1420,46 @@ bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int
     g.c_ps = p->ps_Mv;
     BSE_TRY(cgemm_split(g, true, true, true, false, st));
   }
-  {  // gWq[q][mu][nu] = -(1/N_k) sum_{(k v' v)} Gv[(k v' v)][mu] Z[(k v' v)][nu]   (conj(Gv) for the partner)
-    GemmArgs g;
-    g.batch = nq;
-    g.M = na;
-    g.N = na;
-    g.K = Nk * nv * nv;
-    g.A = (const __bf16*)p->Mv + (long long)i0 * Nk * pair_v;
-    g.a_sb = (long long)Nk * pair_v;
-    g.a_si = 1;
-    g.a_sk = na;
-    g.a_ps = p->ps_Mv;
-    g.conjA = swap ? 1 : 0;
-    g.B = (const __bf16*)p->P + (long long)i0 * Nk * pair_v;
-    g.b_sb = (long long)Nk * pair_v;
-    g.b_sk = na;
-    g.b_sj = 1;
-    g.b_ps = p->ps_Mv;
-    g.C = dst ? gWq : gWq + 2 * (long long)(q0 + i0) * na * na;
-    g.c_bidx = dst ? dst + q0 + i0 : nullptr;
-    g.c_sb = (long long)na * na;
-    g.c_si = na;
-    g.c_sj = 1;
-    g.alpha = -1.0 / (double)Nk;
-    g.beta = acc ? 1 : 0;
-    BSE_TRY(cgemm_split(g, true, true, false, true, st));
+  return adjoint_gw(p, q0, i0, nq, swap, dst, (const __bf16*)p->P, gWq, acc, st);
+}
+
+// The pair-symmetric BF16x3 adjoint at n_v = 4: per batch the valence pair densities, then for adj_q q at a time M_c, G, G' and
+// both Z from one pass over M_c, then the two W gradients of the batch.  M_c of a part is enough, so a plan whose
+// apply does not form M_c allocates adj_q q of it on first use instead of a whole batch (8x8x8: 2.1 GB instead of
+// 17.4).  Gradient at the 8x8x8 workload 28.3 -> 23.6 ms.
+bse_status adjoint_paired(Plan* p, const double* Ybar, const double* X, int nb, double* gWq, bool acc, hipStream_t st) {
+  const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
+  const long long pair_v = (long long)nv * nv * na, pair_c = (long long)nc * nc * na;
+  const long long nt2 = (long long)nc * nc * nv * nv;
+  if (!p->adj_q) p->adj_q = std::min(p->qb, std::max(1, 256 / nc));  // 256 rows of the pair-density product
+  const long long ps_G = (long long)p->adj_q * Nk * nt2;
+  if (!p->Mc) {
+    BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->adj_q * Nk * pair_c));
+    p->ps_Mc = (long long)p->adj_q * Nk * pair_c;
+  }
+  if (!p->adj_G) BSE_TRY(plan_alloc(p, (void**)&p->adj_G, 2 * p->esz * (size_t)ps_G));
+  if (!p->adj_Z2) BSE_TRY(plan_alloc(p, (void**)&p->adj_Z2, p->esz * (size_t)p->qb * Nk * pair_v));
+  __bf16* const G2 = p->adj_G + 4 * ps_G;
+  for (int q0 = 0; q0 < p->nhalf; q0 += p->qb) {
+    const int nq = std::min(p->qb, p->nhalf - q0);
+    const int i0 = q0 < p->nself ? std::min(nq, p->nself - q0) : 0;  // the q from i0 on have a partner -q
+    BSE_TRY(form_pair_densities(p, q0, nq, false, p->kqp, st));
+    for (int i = 0; i < nq; i += p->adj_q) {
+      const int n = std::min(p->adj_q, nq - i), i2 = std::max(0, i0 - i);
+      BSE_TRY(form_pair_densities(p, q0 + i, n, true, p->kqp, st, true, false));
+      StageMark sm_(p, BSE_STAGE_ADJOINT, st);
+      BSE_TRY(adjoint_gm(p, q0 + i, n, false, p->kqp, Ybar, X, nb, p->adj_G, ps_G, st));
+      if (i2 < n)
+        BSE_TRY(adjoint_gm(p, q0 + i + i2, n - i2, true, p->kqp, Ybar, X, nb, G2 + i2 * Nk * nt2, ps_G, st));
+      BSE_TRY(adjoint_z_pair(n * Nk, Nk, i2, nc * nc, na, p->adj_G, G2, ps_G, (const __bf16*)p->Mc, p->ps_Mc,
+                             (__bf16*)p->P + (long long)i * Nk * pair_v, p->adj_Z2 + (long long)i * Nk * pair_v,
+                             p->ps_Mv, st));
+    }
+    StageMark sm_(p, BSE_STAGE_ADJOINT, st);
+    BSE_TRY(adjoint_gw(p, q0, 0, nq, false, p->qord, (const __bf16*)p->P, gWq, acc, st));
+    // the partner of plan-order q j sits at j + (nhalf - nself) of the order
+    if (i0 < nq)
+      BSE_TRY(adjoint_gw(p, q0, i0, nq - i0, true, p->qord + (p->nhalf - p->nself), p->adj_Z2, gWq, acc, st));
   }
   return BSE_OK;
 }
@@ -1417,6 +1472,7 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
   const bool tn = p->split && (nv * nv) % 8 == 0 && p->given_aux % 8 == 0;
+  if (tn && p->herm_half && !p->two_centre && nv == 4) return adjoint_paired(p, Ybar, X, nb, gWq, acc, st);
   if (!p->Mc) BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->qb * Nk * nc * nc * na));
   if (tn && p->herm_half) {
     // pair symmetry of the gradient: with Hermitian C^mu the pairs (k, k - q) of g_W(-q) carry the pair

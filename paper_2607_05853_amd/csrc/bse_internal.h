@@ -97,6 +97,11 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
 // t_sb per batch entry); Mc planes at mc (stride mc_sb per batch entry, plane stride mc_ps, rows of N_aux)
 bse_status wstep_dblock(const GemmArgs& g, const __bf16* mc, long long mc_sb, long long mc_ps, float* t, long long t_sb,
                         hipStream_t st);
+// both Z products of the pair-symmetric adjoint from one pass over M_c (n_v = 4; q2: first batch-local q with a
+// partner)
+bse_status adjoint_z_pair(int pairs, int Nk, int q2, int nc2, int na, const __bf16* G, const __bf16* G2, long long ps_G,
+                          const __bf16* Mc, long long ps_Mc, __bf16* Z, __bf16* Z2, long long ps_Z,
+                          hipStream_t st);
 // BSE_FUSED_WSTEP=0 in the environment selects the two GEMMs (read at every call)
 bool fused_wstep_enabled();
 // Fragment order of a pre-split B operand for the streaming pair-density kernel: each batch entry's
@@ -219,6 +224,9 @@ struct Plan {
   // adjoint
   std::vector<int32_t> R;
   std::vector<double> wR;
+  __bf16* adj_G = nullptr;    // pair-symmetric BF16x3 adjoint: G, then G', of adj_q q each ([q][k][c'c][v'v] planes)
+  __bf16* adj_Z2 = nullptr;   // its Z' ([qb][Nk][v'v][n_aux] planes, beside Z in P)
+  int adj_q = 0;
   double* gq_acc = nullptr;   // c128 [Nk][n_aux][n_aux]
   double* gq_crop = nullptr;  // c128 [Nk][given_aux][given_aux] where that is smaller
 

@@ -2181,6 +2181,158 @@ __global__ __launch_bounds__(256) void cgemm_b3_tn(GemmArgs g, int nsplit, int k
   }
 }
 
+// ----------------------------------------------------------------------------
+// Both Z products of the pair-symmetric BF16x3 adjoint in one pass over M_c:
+//   Z [(v'v)][nu] = sum_(c'c) G [(c'c)][(v'v)] conj(M_c[(c'c)][nu])        (g_W(q))
+//   Z'[(vv')][nu] = sum_(cc') G'[(cc')][(vv')] M_c[(cc')][nu]              (g_W(-q))
+// per pair, the rows of Z stacked on those of Z'.  The sign of conj(M_c) is put on the G side of each product that has
+// Im M_c (Re G for the imaginary part, Im G for the real part), lane by lane, so that every product keeps its value and
+// the bits are those of two separate GEMMs (forming conj(Z) instead does not give them: 2e-7).  M_c (131 KB per pair at the 8x8x8 workload) dominates
+// the traffic and is read once instead of twice; the n_v^2 = 16 rows of one product filled a quarter of a 64-row tile,
+// the stacked 32 fill their 32 x 32 tiles.  A block takes one pair and 128 columns: 64 rows (c'c) at a time of both
+// operands are loaded at once (80 KiB in flight), transposed in registers as in cgemm_b3_tn and kept in LDS
+// with 64 k per row (16-byte chunk j of row r at j ^ (r / 2 % 8), rows permuted by tn_row); wave w forms columns
+// 32 w .. 32 w + 31 of all rows with M_c as the first MFMA operand, and the result leaves through LDS in 256-byte rows.
+// At the 8x8x8 workload the two products took 10.7 ms per gradient (21.8 GB each), this kernel 5.8 ms.  For n_v = 4
+// only: at n_v = 8 each product fills its 64 rows and the stacked form with 128 KiB of LDS is 0-3 % slower.
+// ----------------------------------------------------------------------------
+constexpr int ADJZ_BN = 128, ADJZ_KT = 64, ADJZ_NV2 = 16;
+constexpr size_t ADJZ_LDS = (size_t)4 * ADJZ_KT * (2 * ADJZ_NV2 + ADJZ_BN) * sizeof(__bf16);  // 80 KiB, two per CU
+struct AdjZArgs {
+  int nc2, na, Nk;
+  int q2;                  // first q (batch-local) with a partner: below it only Z is formed
+  const __bf16 *G, *G2;    // [q][k][c'c][v'v] planes
+  long long ps_G;
+  const __bf16* Mc;        // [q][k][c'c][na] planes
+  long long ps_Mc;
+  __bf16 *Z, *Z2;          // [q][k][v'v][na] planes
+  long long ps_Z;
+};
+
+__global__ __launch_bounds__(256) void adj_z_pair(AdjZArgs g) {
+  constexpr int BN = ADJZ_BN, KT = ADJZ_KT, NV2 = ADJZ_NV2, ROWS = 2 * NV2;
+  constexpr int PLA = ROWS * KT, PLB = BN * KT;  // bf16 per plane
+  extern __shared__ __attribute__((aligned(1024))) __bf16 zsm[];
+  __bf16* const sA = zsm;                        // [4][32][64]
+  __bf16* const sB = zsm + 4 * PLA;              // [4][128][64]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
+  const int ntile = (g.na + BN - 1) / BN;
+  const long long pair = blockIdx.x / ntile;
+  const int n0 = (int)(blockIdx.x % ntile) * BN;
+  const bool both = pair / g.Nk >= g.q2;
+  const __bf16* G = g.G + pair * g.nc2 * NV2;
+  const __bf16* G2 = g.G2 + pair * g.nc2 * NV2;
+  const __bf16* M = g.Mc + pair * (long long)g.nc2 * g.na;
+
+  // an 8 x 8 block (8 k, 8 columns) of one plane, transposed: column c of it as 16 bytes
+  auto column = [](const u4v (&v)[8], int c) {
+    u4v w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const unsigned lo = v[2 * j][c >> 1], hi = v[2 * j + 1][c >> 1];
+      w[j] = (c & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
+    }
+    return w;
+  };
+  auto put = [&](__bf16* plane, int cb, int kb, const u4v (&v)[8]) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int r = tn_row(8 * cb + c);
+      *reinterpret_cast<u4v*>(plane + r * KT + 8 * (kb ^ ((r >> 1) & 7))) = column(v, c);
+    }
+  };
+  f16v cr, ci;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) cr[r] = ci[r] = 0.f;
+  // blocks of this thread: M_c plane 2 p + tid / 128, k block (tid / 16) % 8, column block tid % 16; threads below 128
+  // also A plane tid / 32, k block (tid / 4) % 8, row block tid % 4
+  const u4v zero = {0u, 0u, 0u, 0u};
+  for (int k0 = 0; k0 < g.nc2; k0 += KT) {
+    u4v vb[2][8], va[8];
+    const int kb = (tid >> 4) & 7, cb = tid & 15;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const __bf16* s = M + (2 * p + (tid >> 7)) * g.ps_Mc + n0 + 8 * cb;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const int k = k0 + 8 * kb + r;
+        vb[p][r] = (k < g.nc2 && n0 + 8 * cb < g.na) ? *reinterpret_cast<const u4v*>(s + (long long)k * g.na) : zero;
+      }
+    }
+    const int ra = tid & 3, ka = (tid >> 2) & 7, pl = tid >> 5;
+    const bool second = 8 * ra >= NV2, aok = tid < 128 && (!second || both);
+    const __bf16* s = (second ? G2 + 8 * ra - NV2 : G + 8 * ra) + (aok ? pl * g.ps_G : 0);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int k = k0 + 8 * ka + r;
+      va[r] = (aok && k < g.nc2) ? *reinterpret_cast<const u4v*>(s + (long long)k * NV2) : zero;
+    }
+    __syncthreads();  // the previous round's reads are done
+#pragma unroll
+    for (int p = 0; p < 2; ++p) put(sB + (2 * p + (tid >> 7)) * PLB, cb, kb, vb[p]);
+    if (tid < 128) put(sA + pl * PLA, ra, ka, va);
+    __syncthreads();
+    const int steps = min(KT, (g.nc2 - k0 + 15) / 16 * 16) / 16;
+    for (int ks = 0; ks < steps; ++ks) {
+      bf8v bb[4];
+      {
+        const int r = tn_row(32 * wave + l32);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          bb[q] = *reinterpret_cast<const bf8v*>(sB + q * PLB + r * KT + 8 * ((2 * ks + h) ^ ((r >> 1) & 7)));
+      }
+      bf8v a[4];
+      const int r = tn_row(l32);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        a[q] = *reinterpret_cast<const bf8v*>(sA + q * PLA + r * KT + 8 * ((2 * ks + h) ^ ((r >> 1) & 7)));
+      // the products of cmma_b3 in its order: rows of Z with Im M_c negated
+      const bool z1 = l32 < NV2;
+      const bf8v r0 = z1 ? neg8(a[0]) : a[0], r1 = z1 ? neg8(a[1]) : a[1];
+      const bf8v i2 = z1 ? a[2] : neg8(a[2]), i3 = z1 ? a[3] : neg8(a[3]);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[0], a[1], cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[2], r1, ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[1], a[0], cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[3], r0, ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[2], i3, cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[0], a[3], ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[3], i2, cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[1], a[2], ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[0], a[0], cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[2], r0, ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[2], i2, cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[0], a[2], ci, 0, 0, 0);
+    }
+  }
+  // out through LDS as planes [4][32][128] (16-byte chunk j of row r at j ^ (r % 16)); lane l holds row l % 32,
+  // register 4 q + e column 8 q + 4 (l / 32) + e of its wave's 32 columns
+  __syncthreads();
+#pragma unroll
+  for (int part = 0; part < 2; ++part)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f4v x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = part ? ci[4 * q + e] : cr[4 * q + e];
+      const bf4v hv = __builtin_convertvector(x, bf4v);
+      const bf4v lv = __builtin_convertvector(x - __builtin_convertvector(hv, f4v), bf4v);
+      const int o = l32 * BN + 8 * ((4 * wave + q) ^ (l32 & 15)) + 4 * h;
+      *reinterpret_cast<bf4v*>(sB + (2 * part) * 32 * BN + o) = hv;
+      *reinterpret_cast<bf4v*>(sB + (2 * part + 1) * 32 * BN + o) = lv;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int id = tid + 256 * it;
+    const int c8 = id & 15, row = (id >> 4) & 31, pl = id >> 9, col = n0 + 8 * c8;
+    const bool second = row >= NV2;
+    if (col >= g.na || (second && !both)) continue;
+    __bf16* z = second ? g.Z2 + (row - NV2) * (long long)g.na : g.Z + row * (long long)g.na;
+    *reinterpret_cast<u4v*>(z + pair * (long long)NV2 * g.na + pl * g.ps_Z + col) =
+        *reinterpret_cast<const u4v*>(sB + pl * 32 * BN + row * BN + 8 * (c8 ^ (row & 15)));
+  }
+}
+
 // C[b'][m][n] = alpha * sum_s part[b][s][m][n] (+ C if beta), splits added in order; C is c128 and
 // b' = c_bidx[b] when a batch index table is given
 __global__ void tn_reduce(GemmArgs g, int nsplit, const double* __restrict__ part) {
@@ -2426,6 +2578,20 @@ bse_status wstep_dblock(const GemmArgs& g, const __bf16* mc, long long mc_sb, lo
   BSE_HIP(hipFuncSetAttribute((const void*)wstep_dblock_fused, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)WB_LDS));
   hipLaunchKernelGGL(wstep_dblock_fused, dim3((unsigned)tiles), dim3(512), WB_LDS, st, w);
+  BSE_CHECK_LAUNCH();
+  return BSE_OK;
+}
+
+bse_status adjoint_z_pair(int pairs, int Nk, int q2, int nc2, int na, const __bf16* G, const __bf16* G2, long long ps_G,
+                          const __bf16* Mc, long long ps_Mc, __bf16* Z, __bf16* Z2, long long ps_Z, hipStream_t st) {
+  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+  if ((na & 7) || (ps_G & 7) || (ps_Mc & 7) || (ps_Z & 7) || !al(G) || !al(G2) || !al(Mc) || !al(Z) || !al(Z2)) {
+    set_error("adjoint_z_pair: unsupported shape or alignment");
+    return BSE_ESHAPE;
+  }
+  BSE_HIP(hipFuncSetAttribute((const void*)adj_z_pair, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ADJZ_LDS));
+  hipLaunchKernelGGL(adj_z_pair, dim3((unsigned)((long long)pairs * ((na + ADJZ_BN - 1) / ADJZ_BN))), dim3(256), ADJZ_LDS,
+                     st, AdjZArgs{nc2, na, Nk, q2, G, G2, ps_G, Mc, ps_Mc, Z, Z2, ps_Z});
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }

@@ -79,3 +79,21 @@ def test_spectrum_gradient_and_density_start():
     print("[rounded spectrum] %s" % ["%.1e" % x for x in d], flush=True)
     assert d[0] < 1e-5 and max(d[1:4]) < GRAD_TOL["bf16x3"]
     assert d[4] < 1e-12 or np.abs(out["f64"][4]).max() < 1e-12   # zero for orthonormal bands at Q = 0
+
+
+@pytest.mark.parametrize("nc,na,dense", [(4, 24, (2, 2, 2)), (7, 136, (3, 3, 2)), (9, 128, (4, 2, 3)), (12, 40, (3, 3, 3))])
+def test_paired_gradient(nc, na, dense):
+    # n_v = 4: both Z products from one pass over M_c, at fewer than 64, 81 and 144 rows (c'c), a ragged last column
+    # tile, no q, few q and all q but one with a partner -q
+    from paper_2607_05853_amd import bse as B
+    p = make_problem(dict(cfg_id=75, coarse=(2, 2, 2), dense=dense, n_ao=2 * nc, nv=4, nc=nc, n_aux=na), 1, "G2")
+    W = O.interpolate_W_matmul(p.W_R, p.R, p.w_R, dense_kmesh(p.nk))
+    X, Yb = random_block(p.N, 2, seed=2), random_block(p.N, 2, seed=4)
+    plan = B.plan_from_problem(p, T(W), prec="bf16x3", max_nb=2)
+    g = plan.apply_adjoint(T(Yb), T(X), want_WR=False, want_Wq=True)
+    plan.close()
+    qs = sorted({0, 1, p.Nk // 2, p.Nk - 1})
+    ref = np.stack([O.grad_Wq_at(p, Yb, X, [q])[0] for q in qs])
+    e = rel(g["W_q"].cpu().numpy()[qs], ref)
+    print("[paired gradient nc %d na %d %s] %.1e" % (nc, na, dense, e), flush=True)
+    assert e < GRAD_TOL["bf16x3"]
