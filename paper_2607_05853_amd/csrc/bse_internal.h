@@ -114,6 +114,7 @@ bse_status split_planes_frag(const double* in, __bf16* out, int batch, int N, in
 // the plan stores its BF16X3 halves in fragment order when its shape allows it; BSE_FRAG_HALVES=0 in the
 // environment at plan creation keeps the row order
 bool frag_halves_enabled();
+bool stream_depth(int k);  // depths K of the streaming pair-density kernel
 // split c64 / c128 arrays into four bf16 planes (util.hip); n complex elements,
 // optionally transposing each of `batch` rows x cols matrices
 bse_status split_planes(const void* in, bool in_f64, __bf16* out, long long n, long long plane_stride,

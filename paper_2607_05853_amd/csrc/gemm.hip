@@ -1732,17 +1732,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // CU stay in flight) and writes its 128 x 32 result through a private 4 KiB LDS buffer with 16-byte stores:
 // no block barrier separates one tile from the next.  Each accumulator receives the MFMA sequence of
 // cgemm_b3_dma over k in order, so the results are identical to those of the other split kernels.
-// A in LDS as [plane][128 rows][K], 16-byte chunk c of row r stored at c ^ (r % (K / 8)).  FRAG: B in fragment
+// A in LDS as [plane][128 rows][K], 16-byte chunk c of row r stored at c ^ (r % (K / 8)); K = 96 has 12 chunks, which
+// no XOR permutes, and its rows get a thirteenth instead (208 bytes: 16 rows start in 16 different bank groups).
+// 32-row sub-tiles past the last row are skipped.  FRAG: B in fragment
 // order (split_planes_frag), so that each of a wave's fragment loads reads one contiguous KiB instead of 16
 // or 32 bytes of 32 different columns.
 constexpr int PD_BM = 128, PD_BN = 256, PD_KMAX = 128, PD_AHEAD = 2;
-constexpr size_t PD_LDS = (size_t)4 * PD_BM * PD_KMAX * sizeof(__bf16) + 8 * 4096;  // 160 KiB
+// CS = false writes c64 instead of planes (the gradient's M_c on plans without the k-major gradient).
+constexpr int pd_chunks(int k) { return (k / 8 & (k / 8 - 1)) == 0 ? k / 8 : k / 8 + 1; }  // stored per A row
+constexpr size_t pd_lds(int k) { return (size_t)4 * PD_BM * pd_chunks(k) * 16 + 8 * 4096; }  // K = 128: 160 KiB
 
-template <int NK, bool FRAG>
+template <int NK, bool FRAG, bool CS = true>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void cgemm_b3_stream(GemmArgs g) {
-  constexpr int K = 16 * NK, CPR = K / 8;  // k, 16-byte chunks per A row
-  constexpr int APL = PD_BM * K;           // bf16 per A plane
-  static_assert(K <= PD_KMAX && (CPR & (CPR - 1)) == 0, "K of 64 or 128");
+  constexpr int K = 16 * NK, CPR = K / 8, LCPR = pd_chunks(K);  // k, 16-byte chunks per A row, stored
+  constexpr bool SWZ = LCPR == CPR;
+  constexpr int APL = PD_BM * LCPR * 8;  // bf16 per A plane
+  static_assert(K <= PD_KMAX && (SWZ || K == 96) && PD_BM * LCPR % 64 == 0, "K of 64, 96 or 128");
   static_assert(NK % PD_AHEAD == 0, "the fragment ring restarts at slot 0 on every tile");
   extern __shared__ __attribute__((aligned(1024))) __bf16 smem_s[];
   __bf16* sA = smem_s;
@@ -1787,16 +1792,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // restage A: rows m0 .. m0 + 127 of batch entry b (a valid row past the edge); every wave is past its
       // last A read of the previous block of rows at the first barrier
       __syncthreads();
-      constexpr int RPI = 64 / CPR;  // rows per DMA instruction (1 KiB)
-      for (int ins = wave; ins < 4 * PD_BM / RPI; ins += 8) {
-        const int pl = ins / (PD_BM / RPI), r = (ins % (PD_BM / RPI)) * RPI + lane / CPR;
-        const int ph = lane % CPR, lc = ph ^ (r % CPR);
+      constexpr int NI = PD_BM * LCPR / 64;  // DMA instructions (1 KiB) per plane
+      for (int ins = wave; ins < 4 * NI; ins += 8) {
+        const int pl = ins / NI, c = (ins % NI) * 64 + lane, r = c / LCPR, ph = c % LCPR;
+        const int lc = SWZ ? ph ^ (r % CPR) : min(ph, CPR - 1);
         const int arow = (m0 + r < g.M) ? m0 + r : g.M - 1;
         const __bf16* src = (const __bf16*)g.A + off_of(g.a_tab, g.a_tab_pb, g.a_sb, g.a_si, b, g.M, arow) +
                             pl * g.a_ps + 8 * lc;
         __builtin_amdgcn_global_load_lds((const void*)src,
-                                         (__attribute__((address_space(3))) void*)(sA + pl * APL +
-                                                                                   (ins % (PD_BM / RPI)) * RPI * K),
+                                         (__attribute__((address_space(3))) void*)(sA + pl * APL + (ins % NI) * 512),
                                          16, 0, 0);
       }
       vm_lds_barrier<0>();
@@ -1811,6 +1815,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         accI[i][r] = 0.f;
       }
     // the next tile's fragments are requested as this tile's last k steps retire
+    const int mrem = g.M - m0;
     const __bf16* bn = (it + 1 < it1) ? bsrc(it + 1) : bs;
 #pragma unroll
     for (int kt = 0; kt < NK; ++kt) {
@@ -1823,8 +1828,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         load_b(bn, kt + PD_AHEAD - NK, bq[kt % PD_AHEAD]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        if (32 * i >= mrem) break;
         const int row = 32 * i + l32;
-        const int o = row * K + 8 * ((2 * kt + h) ^ (row % CPR));
+        const int o = SWZ ? row * K + 8 * ((2 * kt + h) ^ (row % CPR)) : (row * LCPR + 2 * kt + h) * 8;
         bf8v a[4];
 #pragma unroll
         for (int pl = 0; pl < 4; ++pl) a[pl] = *reinterpret_cast<const bf8v*>(sA + pl * APL + o);
@@ -1841,8 +1847,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // and the 16-byte reads once
     const float al = (float)g.alpha;
     const int col0 = n0 + 32 * wave;
+    if constexpr (!CS) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) {
+        const int grow = m0 + 32 * i + l32;
+        if (grow >= g.M) continue;
+        const long long ro = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, grow);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int gcol = col0 + 8 * (r >> 2) + 4 * h + (r & 3);
+          if (gcol < g.N)
+            reinterpret_cast<float2*>(g.C)[ro + gcol] = make_float2(al * accR[i][r], al * accI[i][r]);
+        }
+      }
+      continue;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (32 * i >= mrem) break;
 #pragma unroll
       for (int part = 0; part < 2; ++part) {
 #pragma unroll
@@ -1874,6 +1896,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           }
         }
       }
+    }
   }
 }
 
@@ -2596,19 +2619,22 @@ bse_status adjoint_z_pair(int pairs, int Nk, int q2, int nc2, int na, const __bf
   return BSE_OK;
 }
 
-template <int NK, bool FRAG>
+template <int NK, bool FRAG, bool CS = true>
 bse_status launch_stream(const GemmArgs& g, hipStream_t st) {
   int dev = 0, ncu = 0;
   BSE_HIP(hipGetDevice(&dev));
   BSE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   const long long items = (long long)g.batch * ((g.M + PD_BM - 1) / PD_BM) * ((g.N + PD_BN - 1) / PD_BN);
   const unsigned grid = (unsigned)std::max<long long>(1, std::min<long long>(items, ncu));
-  BSE_HIP(hipFuncSetAttribute((const void*)cgemm_b3_stream<NK, FRAG>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)PD_LDS));
-  hipLaunchKernelGGL((cgemm_b3_stream<NK, FRAG>), dim3(grid), dim3(512), PD_LDS, st, g);
+  BSE_HIP(hipFuncSetAttribute((const void*)cgemm_b3_stream<NK, FRAG, CS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)pd_lds(16 * NK)));
+  hipLaunchKernelGGL((cgemm_b3_stream<NK, FRAG, CS>), dim3(grid), dim3(512), pd_lds(16 * NK), st, g);
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }
+
+// the depths the streaming pair-density kernel is built for
+bool stream_depth(int k) { return k == 64 || k == 96 || k == 128; }
 
 bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_split, bool out_f64, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return BSE_OK;
@@ -2622,13 +2648,18 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
     return BSE_EINVAL;
   }
   if (g.b_frag) {  // a B operand in fragment order: only the streaming kernel reads that layout
-    if (!(a_split && b_split && c_split && dma_ok(g) && (g.K == 64 || g.K == 128) && g.N % 32 == 0 && !g.conjA &&
-          !g.conjB && !g.b_tab)) {
-      set_error("cgemm_split: a fragment-order B needs split operands and result, K of 64 or 128, N a multiple "
-                "of 32");
+    if (!(a_split && b_split && !out_f64 && dma_ok(g) && stream_depth(g.K) && g.N % 32 == 0 && !g.conjA && !g.conjB &&
+          !g.b_tab && g.c_sj == 1 && !g.beta)) {
+      set_error("cgemm_split: a fragment-order B needs split operands, K of 64, 96 or 128, N a multiple of 32");
       return BSE_EINVAL;
     }
-    return g.K == 64 ? launch_stream<4, true>(g, st) : launch_stream<8, true>(g, st);
+    if (c_split)
+      return g.K == 64   ? launch_stream<4, true>(g, st)
+             : g.K == 96 ? launch_stream<6, true>(g, st)
+                         : launch_stream<8, true>(g, st);
+    return g.K == 64   ? launch_stream<4, true, false>(g, st)
+           : g.K == 96 ? launch_stream<6, true, false>(g, st)
+                       : launch_stream<8, true, false>(g, st);
   }
   if (a_split && b_split && dma_ok(g)) {
     if (!c_split && g.M <= 64 && g.N <= 64) {  // small per-pair products: quarter-size tiles
@@ -2662,10 +2693,12 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
         return BSE_OK;
       }
     }
-    if (c_split && (g.K == 64 || g.K == 128) && g.M <= 2 * PD_BM && g.N >= 4 * PD_BN && !g.conjA && !g.conjB &&
+    if (c_split && stream_depth(g.K) && g.M <= 2 * PD_BM && g.N >= 4 * PD_BN && !g.conjA && !g.conjB &&
         stream_enabled()) {
       // short K, few rows, many columns (the pair densities): persistent streaming blocks, one per CU
-      return g.K == 64 ? launch_stream<4, false>(g, st) : launch_stream<8, false>(g, st);
+      return g.K == 64   ? launch_stream<4, false>(g, st)
+             : g.K == 96 ? launch_stream<6, false>(g, st)
+                         : launch_stream<8, false>(g, st);
     }
     if (c_split && g.K >= WB_MIN_K && g.N >= 256 && g.M >= 128 && wide_tiles_enabled()) {
       // long K and a wide B (the W step): 128 x 256 tiles, three LDS stages; 256 x 128 where the last 256 columns
