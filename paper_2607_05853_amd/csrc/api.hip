@@ -413,6 +413,29 @@ __global__ void permute_blocks(const unsigned short* __restrict__ in, unsigned s
   }
 }
 
+}  // namespace
+
+// the q-batch buffers of the direct term, each on its own so that a call after a failed allocation completes the set
+bse_status pair_workspace(Plan* p) {
+  const long long nq = p->qb, Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
+  auto get = [&](void** b, size_t bytes) -> bse_status { return *b ? BSE_OK : plan_alloc(p, b, bytes); };
+  BSE_TRY(get(&p->Mv, p->esz * (size_t)(nq * Nk * nv * nv * na)));
+  BSE_TRY(get(&p->P, p->esz * (size_t)(nq * Nk * nv * nv * na)));
+  if (p->mc_direct) BSE_TRY(get(&p->Mc, p->esz * (size_t)(nq * Nk * nc * nc * na)));
+  BSE_TRY(get(&p->T, p->esz * (size_t)(nq * Nk * nc * nc * nv * nv)));
+  if (p->two_centre) {
+    const size_t nn = (size_t)(p->prec == BSE_F64 ? 16 : 8) * (size_t)(nq * Nk * (nv * nv + nc * nc) * na);
+    BSE_TRY(get(&p->Nt, nn));
+    BSE_TRY(get(&p->Nt2, nn));
+  }
+  BSE_TRY(get((void**)&p->tab_psi_v, sizeof(long long) * (size_t)(nq * Nk * nv)));
+  BSE_TRY(get((void**)&p->tab_mv, sizeof(long long) * (size_t)(nq * Nk * nv)));
+  BSE_TRY(get((void**)&p->tab_psi_c, sizeof(long long) * (size_t)(nq * Nk * nc)));
+  return get((void**)&p->tab_mc, sizeof(long long) * (size_t)(nq * Nk * nc));
+}
+
+namespace {
+
 // two-centre LRI coefficients as given to plan creation
 struct TwoCentreIn {
   int nR = 0;
@@ -771,23 +794,9 @@ bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const d
     if (const char* e = std::getenv("BSE_QBATCH")) qb = std::atoll(e);
     qb = std::max(1LL, std::min<long long>(qb, Nk));
     p->qb = (int)qb;
-    const long long nq = qb;
-    BSE_TRY(plan_alloc(p, &p->Mv, p->esz * (size_t)(nq * Nk * nv * nv * na)));
-    p->ps_Mv = nq * Nk * nv * nv * na;
-    p->ps_Mc = nq * Nk * nc * nc * na;
-    p->ps_T = nq * Nk * nc * nc * nv * nv;
-    BSE_TRY(plan_alloc(p, &p->P, p->esz * (size_t)(nq * Nk * nv * nv * na)));
-    if (p->mc_direct) BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)(nq * Nk * nc * nc * na)));
-    BSE_TRY(plan_alloc(p, &p->T, p->esz * (size_t)(nq * Nk * nc * nc * nv * nv)));
-    if (p->two_centre) {
-      const size_t nn = (size_t)(f64 ? 16 : 8) * (size_t)(nq * Nk * (nv * nv + nc * nc) * na);
-      BSE_TRY(plan_alloc(p, &p->Nt, nn));
-      BSE_TRY(plan_alloc(p, &p->Nt2, nn));
-    }
-    BSE_TRY(plan_alloc(p, (void**)&p->tab_psi_v, sizeof(long long) * (size_t)(nq * Nk * nv)));
-    BSE_TRY(plan_alloc(p, (void**)&p->tab_mv, sizeof(long long) * (size_t)(nq * Nk * nv)));
-    BSE_TRY(plan_alloc(p, (void**)&p->tab_psi_c, sizeof(long long) * (size_t)(nq * Nk * nc)));
-    BSE_TRY(plan_alloc(p, (void**)&p->tab_mc, sizeof(long long) * (size_t)(nq * Nk * nc)));
+    p->ps_Mv = qb * Nk * nv * nv * na;
+    p->ps_Mc = qb * Nk * nc * nc * na;
+    p->ps_T = qb * Nk * nc * nc * nv * nv;
   }
   // exchange split-K: chunks of whole k points
   {
@@ -802,6 +811,9 @@ bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const d
   }
   BSE_TRY(plan_alloc(p, (void**)&p->txp, 16 * (size_t)TX_CHUNKS * p->N * max_nb));
   if (f64 && !tc && p->herm_half) BSE_TRY(lattice_build(p, C, W_q, st));
+  // the pair route's buffers now, unless every application goes over lattice vectors (then its gradient and coupling
+  // block allocate them on first use: 12 GiB less to allocate, 228 ms on memory the driver has yet to clear)
+  if (!lattice_applies(p, max_nb)) BSE_TRY(pair_workspace(p));
   return BSE_OK;
 }
 

@@ -421,6 +421,151 @@ __global__ __launch_bounds__(256) void direct_tx_mfma2(int Nk, int nq, int q0, i
   }
 }
 
+// The sums of direct_tx_mfma, element for element in its order, for the band counts direct_tx_mfma2 does not take
+// (n_c n_v not a multiple of 16): T' and X' are staged as there, but with real column c of the contraction at
+// position (c % 4) KG + c / 4 of its row, so that a lane's 16-byte reads hold its operands of four consecutive steps
+// (step ks contracts columns 4 ks .. 4 ks + 3 as direct_tx_mfma does, which reads 4 bytes per operand and step and
+// spends fifteen vector instructions on their index).  The place of every element of T and X in LDS depends on the
+// thread alone and is worked out once; the next item's T and X are loaded during the current products.  Rows, columns
+// and steps beyond the shape are zero.  At 12x12x12 (n_c n_v = 60, 8 vectors) T.X took 49 ms per apply, this kernel
+// 37 ms (the two reads of T: 20 ms).  TREG, XREG: elements of T and X per thread; MAXT: output tiles per wave.
+template <int TREG, int XREG, int MAXT>
+__global__ __launch_bounds__(256) void direct_tx_restaged(int Nk, int nq, int q0, int nv, int nc, int nb, int qlen,
+                                                          const int* __restrict__ kqp, const int* __restrict__ kqm,
+                                                          int nself, const float* __restrict__ T,
+                                                          const double* __restrict__ X, double* __restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) float txs[];
+  const int k = blockIdx.x, chunk = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l4 = lane >> 4, l16 = lane & 15;
+  const int nt = nc * nv, nt2 = nt * nt, nv2 = nv * nv, nx = nt * nb;
+  const int KG = ((2 * nt + 3) / 4 + 3) / 4 * 4, RS = 4 * KG + 4;
+  const int RT = (nt + 15) / 16, CT = (2 * nb + 15) / 16, ntile = RT * CT;
+  float* const Ta = txs;                 // [16 RT][RS]
+  float* const Xs = Ta + 16 * RT * RS;   // [16 CT][RS]
+  // place of complex column j in a row: its real part at pos(j), the imaginary part KG further on
+  auto pos = [&](int j) { return 2 * (j & 1) * KG + (j >> 1); };
+  // T element e = (c1 c2, v1 v2): first pass T'[(c2 v2)][(c1 v1)], partner pass T'[(c1 v1)][(c2 v2)]
+  int td0[TREG], td1[TREG], xd[XREG];
+#pragma unroll
+  for (int r = 0; r < TREG; ++r) {
+    const int e = tid + 256 * r, r1 = e / nv2, r2 = e % nv2;
+    const int a = (r1 / nc) * nv + r2 / nv, b = (r1 % nc) * nv + r2 % nv;
+    td0[r] = e < nt2 ? b * RS + pos(a) : -1;
+    td1[r] = e < nt2 ? a * RS + pos(b) : -1;
+  }
+#pragma unroll
+  for (int r = 0; r < XREG; ++r) {
+    const int e = tid + 256 * r;
+    xd[r] = e < nx ? 2 * (e % nb) * RS + pos(e / nb) : -1;
+  }
+  for (int e = tid; e < 16 * (RT + CT) * RS; e += 256) txs[e] = 0.f;
+  double acc[MAXT][4];
+#pragma unroll
+  for (int s = 0; s < MAXT; ++s)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[s][q] = 0.0;
+  const int qa = chunk * qlen, qe = min(nq, qa + qlen);
+  float2 tr[TREG];
+  double xr[XREG][2];
+  auto load = [&](int qi, int pass) {
+    const int j = q0 + qi;
+    const int km = pass == 0 ? 0 : kqm[(long long)k * Nk + j];
+    const float2* Tg = reinterpret_cast<const float2*>(T) + ((long long)qi * Nk + (pass == 0 ? k : km)) * nt2;
+    const double* Xg = X + 2 * (long long)(pass == 0 ? kqp[(long long)k * Nk + j] : km) * nx;
+#pragma unroll
+    for (int r = 0; r < TREG; ++r)
+      if (td0[r] >= 0) tr[r] = Tg[tid + 256 * r];
+#pragma unroll
+    for (int r = 0; r < XREG; ++r)
+      if (xd[r] >= 0) {
+        xr[r][0] = Xg[2 * (tid + 256 * r)];
+        xr[r][1] = Xg[2 * (tid + 256 * r) + 1];
+      }
+  };
+  int qi = qa, pass = 0;
+  if (qi < qe) load(qi, 0);
+  while (qi < qe) {
+    int nqi = qi, npass = pass + 1;
+    if (npass > (q0 + qi >= nself ? 1 : 0)) {
+      npass = 0;
+      ++nqi;
+    }
+    __syncthreads();  // the previous item's products are done (and the zero fill is)
+#pragma unroll
+    for (int r = 0; r < TREG; ++r)
+      if (td0[r] >= 0) {
+        float* d = Ta + (pass == 0 ? td0[r] : td1[r]);
+        d[0] = tr[r].x;
+        d[KG] = pass == 0 ? tr[r].y : -tr[r].y;
+      }
+#pragma unroll
+    for (int r = 0; r < XREG; ++r)
+      if (xd[r] >= 0) {
+        const float re = (float)xr[r][0], im = (float)xr[r][1];
+        float* d = Xs + xd[r];
+        d[0] = re;
+        d[KG] = -im;
+        d[RS] = im;
+        d[RS + KG] = re;
+      }
+    __syncthreads();
+    if (nqi < qe) load(nqi, npass);
+#pragma unroll
+    for (int s = 0; s < MAXT; ++s) {
+      const int t = wave + 4 * s;
+      if (t >= ntile) break;
+      const float* pa = Ta + (16 * (t / CT) + l16) * RS + KG * l4;
+      const float* pb = Xs + (16 * (t % CT) + l16) * RS + KG * l4;
+      f4v a4 = {0, 0, 0, 0};
+      for (int m = 0; m < KG; m += 4) {
+        const f4v av = *reinterpret_cast<const f4v*>(pa + m), bv = *reinterpret_cast<const f4v*>(pb + m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a4 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], a4, 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[s][q] += (double)a4[q];
+    }
+    qi = nqi;
+    pass = npass;
+  }
+#pragma unroll
+  for (int s = 0; s < MAXT; ++s) {
+    const int t = wave + 4 * s;
+    if (t >= ntile) break;
+    const int cc = (t % CT) * 16 + l16;
+    if (cc >= 2 * nb) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 16 * (t / CT) + 4 * l4 + q;
+      if (i < nt) part[2 * (((long long)chunk * Nk + k) * nx + (long long)i * nb + (cc >> 1)) + (cc & 1)] = acc[s][q];
+    }
+  }
+}
+
+// LDS bytes of direct_tx_restaged, 0 beyond its largest instance
+size_t tx_restaged_lds(int nt, int nb) {
+  const int RT = (nt + 15) / 16, CT = (2 * nb + 15) / 16;
+  if (nt * nt > 256 * 36 || nt * nb > 256 * 8 || RT * CT > 32) return 0;
+  const int KG = ((2 * nt + 3) / 4 + 3) / 4 * 4;
+  return sizeof(float) * (size_t)(16 * (RT + CT)) * (4 * KG + 4);
+}
+
+bse_status launch_tx_restaged(dim3 grid, size_t sh, int nt, hipStream_t st, int Nk, int nq, int q0, int nv, int nc,
+                              int nb, int qlen, const int* kq, const int* kqm, int nself, const float* T,
+                              const double* X, double* part) {
+  const int tiles = ((nt + 15) / 16) * ((2 * nb + 15) / 16), nx = nt * nb;
+  auto go = [&](auto kern) -> bse_status {
+    BSE_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    hipLaunchKernelGGL(kern, grid, dim3(256), sh, st, Nk, nq, q0, nv, nc, nb, qlen, kq, kqm, nself, T, X, part);
+    BSE_CHECK_LAUNCH();
+    return BSE_OK;
+  };
+  if (nt * nt <= 256 * 4 && nx <= 512 && tiles <= 8) return go(direct_tx_restaged<4, 2, 2>);
+  if (nt * nt <= 256 * 16 && nx <= 512 && tiles <= 8) return go(direct_tx_restaged<16, 2, 2>);
+  if (nt * nt <= 256 * 16) return go(direct_tx_restaged<16, 8, 8>);
+  return go(direct_tx_restaged<36, 8, 8>);
+}
+
 // LDS bytes of direct_tx_mfma2 for elements of esz bytes, 0 when its shape conditions do not hold
 size_t tx2_lds(int nv, int nc, int nb, size_t esz) {
   const int nt = nc * nv;
@@ -496,17 +641,30 @@ __global__ void diag_kernel(long long N, int nv, int nc, int nb, const double* _
   Y[2 * t + 1] = d * X[2 * t + 1];
 }
 
-// t[m][b] = sum_s part[s][m][b]
-__global__ void splitk_reduce(int nsplit, int n, const double* __restrict__ part, double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// t[m][b] = sum_s part[s][m][b]: 16 outputs per block, each summed by 16 threads over every 16th part and then
+// over the threads (one thread per output walked the 512 parts of the 8x8x8 workload in 123 us; this takes 5 us)
+__global__ __launch_bounds__(256) void splitk_reduce(int nsplit, int n, const double* __restrict__ part,
+                                                     double* __restrict__ out) {
+  __shared__ double2 sm[16][17];
+  const int o = threadIdx.x & 15, l = threadIdx.x >> 4, i = blockIdx.x * 16 + o;
   double sr = 0, si = 0;
-  for (int s = 0; s < nsplit; ++s) {
-    sr += part[2 * ((long long)s * n + i)];
-    si += part[2 * ((long long)s * n + i) + 1];
+  if (i < n) {
+#pragma unroll 8
+    for (int s = l; s < nsplit; s += 16) {
+      sr += part[2 * ((long long)s * n + i)];
+      si += part[2 * ((long long)s * n + i) + 1];
+    }
   }
-  out[2 * i] = sr;
-  out[2 * i + 1] = si;
+  sm[l][o] = double2{sr, si};
+  __syncthreads();
+  if (l == 0 && i < n) {
+    for (int s = 1; s < 16; ++s) {
+      sr += sm[s][o].x;
+      si += sm[s][o].y;
+    }
+    out[2 * i] = sr;
+    out[2 * i + 1] = si;
+  }
 }
 
 // Gm[qi][k][(v' v)][(c' c)] = sum_b Ybar[k][(c v)][b] conj(X[k'][(c' v')][b])
@@ -1103,7 +1261,7 @@ bse_status apply_exchange(Plan* p, const double* X, double* Y, int nb, hipStream
   double* t = p->xt + 2 * (long long)p->xsplit * na * p->max_nb;  // reduced t after the partials
   {
     const int n = na * nb;
-    hipLaunchKernelGGL(splitk_reduce, dim3((n + 255) / 256), dim3(256), 0, st, p->xsplit, n, p->xt, t);
+    hipLaunchKernelGGL(splitk_reduce, dim3((n + 15) / 16), dim3(256), 0, st, p->xsplit, n, p->xt, t);
     BSE_CHECK_LAUNCH();
   }
   {  // u = Vbar t
@@ -1169,6 +1327,7 @@ bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t
   // n_v = n_c = 8 with N_aux a multiple of 256 on the M_cc' route: the W step and the direct block run as one
   // kernel and P stays on chip (same result as the two GEMMs below)
   const bool fused = p->fused_wt && fused_wstep_enabled();
+  BSE_TRY(pair_workspace(p));
   for (int q0 = 0; q0 < nqt; q0 += p->qb) {
     const int nq = (nqt - q0) < p->qb ? (nqt - q0) : p->qb;
     BSE_TRY(form_pair_densities(p, q0, nq, p->mc_direct, kq, st, p->split));
@@ -1307,6 +1466,9 @@ bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t
           else
             BSE_TRY(go(direct_tx_mfma2<float, 0, 0>, tp));
         }
+      } else if (const size_t shr = f64 || !tx2_enabled() ? 0 : tx_restaged_lds(nt, nb); shr > 0) {
+        BSE_TRY(launch_tx_restaged(grid, shr, nt, st, Nk, nq, q0, nv, nc, nb, qlen, kq, p->kqm, nself,
+                                   (const float*)p->T, X, p->txp));
       } else if (!f64 && ntile <= 4 * TX_MAXT) {  // FP32 matrix cores for c64 T: one item staged at a time
         const size_t tb = ((size_t)nt * nt * p->esz + 15) & ~(size_t)15;
         const size_t shm = tb + (size_t)nt * nb * p->esz;
@@ -1472,6 +1634,7 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
   const bool tn = p->split && (nv * nv) % 8 == 0 && p->given_aux % 8 == 0;
+  BSE_TRY(pair_workspace(p));
   if (tn && p->herm_half && !p->two_centre && nv == 4) return adjoint_paired(p, Ybar, X, nb, gWq, acc, st);
   if (!p->Mc) BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->qb * Nk * nc * nc * na));
   if (tn && p->herm_half) {

@@ -542,16 +542,16 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   if (32 * (size_t)nbox * n2 > budget) return BSE_OK;
 
   std::vector<double> q = plan_kfrac(p);
-  // the inverse sum over the whole box (the kernels' R list is limited to FT_MAXNR, so one R1 at a time)
+  // the inverse sum over the whole box (the kernels' R list is limited to FT_MAXNR: as many R1 at a time as fit)
   Tmp box, red, idx, chk;
   BSE_TRY(dmalloc(&box.p, 16 * (size_t)nbox * n2));
   BSE_TRY(dmalloc(&red.p, 8 * (2 * (size_t)nbox + 1)));
   BSE_TRY(zero_fill(red.p, 8 * (2 * (size_t)nbox + 1), st));
-  const int per = nbox / (hi[0] - lo[0] + 1);
+  const int slab = nbox / (hi[0] - lo[0] + 1), per = FT_MAXNR / slab * slab;
   const std::vector<double> w(nbox, 1.0 / Nk);
   for (int i = 0; i < nbox; i += per) {
     FtArgs ax;
-    if (!ft_axes(&ax, Nk, q.data(), per, R.data() + 3 * (size_t)i, w.data())) return BSE_OK;
+    if (!ft_axes(&ax, Nk, q.data(), std::min(per, nbox - i), R.data() + 3 * (size_t)i, w.data())) return BSE_OK;
     BSE_TRY(ft_gather_launch(ax, -1.0, (const double*)W_q, n2, 0, (double*)box.p + 2 * (size_t)i * n2, st));
   }
   hipLaunchKernelGGL(lat_absmax, dim3(8, nbox), dim3(256), 0, st, n2, (const double*)box.p, (unsigned long long*)red.p);
