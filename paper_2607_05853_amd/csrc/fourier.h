@@ -27,9 +27,13 @@ bool ft_axes(FtArgs* a, int n_q, const double* q, int n_R, const int32_t* R, con
 // out[q][e] = sum_R w_R in[R][e] exp(sign 2 pi i q.R).  mode 0: c128 out, 1: c64 out, 2: max |out - ref|.
 // planar input: [R][E / group][2][group] doubles, summed over nsplit arrays split_stride doubles apart.
 bse_status ft_spread_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
-                            int nsplit, long long split_stride, int mode, void* out, const double* ref, hipStream_t st);
+                            int nsplit, long long split_stride, int mode, void* out, const double* ref, hipStream_t st,
+                            const double* table = nullptr);
 // out[R][e] = w_R sum_q in[q][e] exp(sign 2 pi i q.R); planar: out as [R][2][E]
 bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, double* out,
-                            hipStream_t st);
+                            hipStream_t st, const double* table = nullptr);
+// the phases of the axes for one sign, as the kernels take them from `table`
+size_t ft_table_bytes(const FtArgs& a);
+bse_status ft_table_launch(const FtArgs& a, double sign, double* out, hipStream_t st);
 
 }  // namespace bse

@@ -95,9 +95,17 @@ __device__ __forceinline__ void store_nt(double2* p, const Z v) {
   __builtin_nontemporal_store(dbl2{v.x, v.y}, reinterpret_cast<dbl2*>(p));
 }
 
-// exp(sign 2 pi i q R) of each axis into LDS, [q][NS] per axis (columns beyond the axis' R are zero)
+// exp(sign 2 pi i q R) of each axis, [q][NS] per axis (columns beyond the axis' R are zero), the three axes after each
+// other in LDS; from a table made once where the caller keeps one (the sines take 2 us of a small sum)
 template <int NS>
-__device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, double2* p1, double2* p2, double2* p3) {
+__device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, const double2* __restrict__ tab, double2* p1,
+                                          double2* p2, double2* p3) {
+  if (tab) {
+    const int n = a.n[0] * FT_MAXR + (a.n[1] + a.n[2]) * NS;
+    for (int t = threadIdx.x; t < n; t += blockDim.x) p1[t] = tab[t];
+    __syncthreads();
+    return;
+  }
   for (int x = 0; x < 3; ++x) {
     double2* p = x == 0 ? p1 : (x == 1 ? p2 : p3);
     const int ns = x == 0 ? FT_MAXR : NS;
@@ -126,7 +134,7 @@ template <int NS, int MODE>
 __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, const double* __restrict__ in,
                                                  long long E, int planar, long long group, int nsplit,
                                                  long long split_stride, void* __restrict__ out,
-                                                 const double* __restrict__ ref) {
+                                                 const double* __restrict__ ref, const double2* tab) {
   extern __shared__ double2 ft_lds[];
   const int n1 = a.n[0], n2 = a.n[1], n3 = a.n[2];
   double2* const W = ft_lds;  // [nR + 1][te], the last row zero (the box slots without an R)
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
     W[t] = double2{a.w[r] * v.x, a.w[r] * v.y};
   }
   for (int t = threadIdx.x; t < te; t += blockDim.x) W[a.nR * te + t] = double2{0.0, 0.0};
-  ft_phases<NS>(a, sign, p1, p2, p3);
+  ft_phases<NS>(a, sign, tab, p1, p2, p3);
   const int el = threadIdx.x % te, qstep = blockDim.x / te;
   const long long e = e0 + el;
   double dmax = 0.0;
@@ -235,7 +243,8 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
 // Output: c128 rows of E, or re and im planes of E each ([R][2][E]) when planar.
 template <int NS>
 __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, const double* __restrict__ in,
-                                                 long long E, int planar, double* __restrict__ out) {
+                                                 long long E, int planar, double* __restrict__ out,
+                                                 const double2* tab) {
   extern __shared__ double2 ft_lds[];
   const int n1 = a.n[0], n2 = a.n[1], n3 = a.n[2];
   const int el = threadIdx.x % te, ql = threadIdx.x / te, nq = blockDim.x / te;
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
   double2* const p1 = X + nq * NS * te;
   double2* const p2 = p1 + n1 * FT_MAXR;
   double2* const p3 = p2 + n2 * NS;
-  ft_phases<NS>(a, sign, p1, p2, p3);
+  ft_phases<NS>(a, sign, tab, p1, p2, p3);
   const long long e = (long long)blockIdx.x * te + el;
   for (int i0 = 0; i0 < n1; i0 += nq) {
     const int i1 = i0 + ql;
@@ -314,9 +323,18 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
   }
 }
 
+template <int NS>
+__global__ __launch_bounds__(256) void ft_table(FtArgs a, double sign, double2* __restrict__ out) {
+  extern __shared__ double2 ft_lds[];
+  double2* const p2 = ft_lds + a.n[0] * FT_MAXR;
+  ft_phases<NS>(a, sign, nullptr, ft_lds, p2, p2 + a.n[1] * NS);
+  const int n = a.n[0] * FT_MAXR + (a.n[1] + a.n[2]) * NS;
+  for (int t = threadIdx.x; t < n; t += blockDim.x) out[t] = ft_lds[t];
+}
+
 template <int NS, int MODE>
 bse_status spread_go(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
-                     int nsplit, long long split_stride, void* out, const double* ref, hipStream_t st) {
+                     int nsplit, long long split_stride, void* out, const double* ref, const double2* tab, hipStream_t st) {
   // 32 e per block (512-byte rows) while the tile leaves room for two blocks on a CU, 16 for the larger R sets
   // and while 32 would leave CUs without a block
   const int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
@@ -326,44 +344,64 @@ bse_status spread_go(const FtArgs& a, double sign, const double* in, long long E
     BSE_HIP(hipFuncSetAttribute((const void*)ft_spread<NS, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 160 * 1024));
   hipLaunchKernelGGL((ft_spread<NS, MODE>), dim3((unsigned)((E + te - 1) / te)), dim3(bs), lds, st, a, sign, te, in, E,
-                     planar, group, nsplit, split_stride, out, ref);
+                     planar, group, nsplit, split_stride, out, ref, tab);
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }
 
 template <int NS>
 bse_status spread_ns(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
-                     int nsplit, long long split_stride, int mode, void* out, const double* ref, hipStream_t st) {
-  if (mode == 0) return spread_go<NS, 0>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, st);
-  if (mode == 1) return spread_go<NS, 1>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, st);
-  return spread_go<NS, 2>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, st);
+                     int nsplit, long long split_stride, int mode, void* out, const double* ref, const double2* tab,
+                     hipStream_t st) {
+  if (mode == 0) return spread_go<NS, 0>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
+  if (mode == 1) return spread_go<NS, 1>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
+  return spread_go<NS, 2>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
 }
 
 }  // namespace
 
 bse_status ft_spread_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
                             int nsplit, long long split_stride, int mode, void* out, const double* ref,
-                            hipStream_t st) {
+                            hipStream_t st, const double* table) {
   const int ns = ft_square(a);
-  if (ns <= 3) return spread_ns<3>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, st);
-  if (ns <= 5) return spread_ns<5>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, st);
-  return spread_ns<7>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, st);
+  const double2* tab = reinterpret_cast<const double2*>(table);
+  if (ns <= 3) return spread_ns<3>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
+  if (ns <= 5) return spread_ns<5>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
+  return spread_ns<7>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
 }
 
 bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, double* out,
-                            hipStream_t st) {
+                            hipStream_t st, const double* table) {
   const int ns = ft_square(a);
+  const double2* tab = reinterpret_cast<const double2*>(table);
   // as the spread: 32 e per block while that leaves every CU two blocks
   const int te = E >= 32 * 512 ? 32 : 16;
   const int bs = 256;
   const size_t lds = 16 * ((size_t)(bs / te) * ns * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ns);
   const dim3 grid((unsigned)((E + te - 1) / te)), block(bs);
   if (ns <= 3)
-    hipLaunchKernelGGL(ft_gather<3>, grid, block, lds, st, a, sign, te, in, E, planar, out);
+    hipLaunchKernelGGL(ft_gather<3>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
   else if (ns <= 5)
-    hipLaunchKernelGGL(ft_gather<5>, grid, block, lds, st, a, sign, te, in, E, planar, out);
+    hipLaunchKernelGGL(ft_gather<5>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
   else
-    hipLaunchKernelGGL(ft_gather<7>, grid, block, lds, st, a, sign, te, in, E, planar, out);
+    hipLaunchKernelGGL(ft_gather<7>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
+  BSE_CHECK_LAUNCH();
+  return BSE_OK;
+}
+
+size_t ft_table_bytes(const FtArgs& a) {
+  return 16 * ((size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ft_square(a));
+}
+
+bse_status ft_table_launch(const FtArgs& a, double sign, double* out, hipStream_t st) {
+  const int ns = ft_square(a);
+  const size_t lds = ft_table_bytes(a);
+  if (ns <= 3)
+    hipLaunchKernelGGL(ft_table<3>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
+  else if (ns <= 5)
+    hipLaunchKernelGGL(ft_table<5>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
+  else
+    hipLaunchKernelGGL(ft_table<7>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }

@@ -3,6 +3,7 @@
 // (classical Gram-Schmidt twice) and the continued fraction run in FP64 on the
 // device.  Breakdown is masked per chain on the device, so the host loop never
 // synchronises until the end.
+#include <algorithm>
 #include <cmath>
 
 #include "bse_internal.h"
@@ -92,106 +93,128 @@ __global__ void lz_gather(long long N, int nb, const double* __restrict__ Wblk, 
   w[2 * (bi * N + I) + 1] = Wblk[2 * t + 1];
 }
 
-// w -= a_j q_j + b_{j-1} q_{j-1}
-__global__ void lz_three_term(long long N, int m, int j, const double* __restrict__ a, const double* __restrict__ b,
-                              const double* __restrict__ basis, double* __restrict__ w) {
-  const int bi = blockIdx.y;
-  const long long I = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= N) return;
-  const double aj = a[(long long)bi * m + (j - 1)];
-  const double* qj = basis + 2 * ((long long)bi * m * N + (long long)(j - 1) * N + I);
-  double* wi = w + 2 * (bi * N + I);
-  double wr = wi[0] - aj * qj[0], wim = wi[1] - aj * qj[1];
-  if (j > 1) {
-    const double bp = b[(long long)bi * (m + 1) + (j - 1)];
-    const double* qp = basis + 2 * ((long long)bi * m * N + (long long)(j - 2) * N + I);
-    wr -= bp * qp[0];
-    wim -= bp * qp[1];
-  }
-  wi[0] = wr;
-  wi[1] = wim;
-}
-
-// h[bi][i] = q_i^H w for i < j   (grid: j x nb blocks)
-__global__ void lz_project(long long N, int m, const double* __restrict__ basis, const double* __restrict__ w,
-                           double* __restrict__ h) {
+// h[bi][i] = q_i^H w for i < j (grid: j x nb blocks); element I of chain bi of w at bi sb + I si.  With a, the last
+// block also gives a_j = Re q_j^H w.
+__global__ __launch_bounds__(RB) void lz_project(long long N, int m, int j, const double* __restrict__ basis,
+                                                 const double* __restrict__ w, long long sb, long long si,
+                                                 double* __restrict__ h, double* __restrict__ a) {
   const int i = blockIdx.x, bi = blockIdx.y;
-  const double* q = basis + 2 * ((long long)bi * m * N + (long long)i * N);
-  const double* wb = w + 2 * (long long)bi * N;
-  double sr = 0, si = 0;
+  const double2* q = reinterpret_cast<const double2*>(basis) + ((long long)bi * m * N + (long long)i * N);
+  const double2* wb = reinterpret_cast<const double2*>(w) + bi * sb;
+  double sr = 0, sim = 0;
+#pragma unroll 4
   for (long long I = threadIdx.x; I < N; I += RB) {
-    const double ar = q[2 * I], ai = -q[2 * I + 1], br = wb[2 * I], bi_ = wb[2 * I + 1];
-    sr += ar * br - ai * bi_;
-    si += ar * bi_ + ai * br;
+    const double2 x = q[I], y = wb[I * si];
+    sr += x.x * y.x + x.y * y.y;
+    sim += x.x * y.y - x.y * y.x;
   }
-  block_sum2(sr, si);
+  block_sum2(sr, sim);
   if (threadIdx.x == 0) {
     h[2 * ((long long)bi * m + i)] = sr;
-    h[2 * ((long long)bi * m + i) + 1] = si;
+    h[2 * ((long long)bi * m + i) + 1] = sim;
+    if (a && i == j - 1) a[(long long)bi * m + i] = sr;
   }
 }
 
-// w -= sum_{i<j} q_i h_i
-__global__ void lz_subtract(long long N, int m, int j, const double* __restrict__ basis, const double* __restrict__ h,
-                            double* __restrict__ w) {
+// out = w - sum_{i<j} q_i h_i (grid: blocks of RB / G elements x nb), w as in lz_project, out [nb][N]; the G groups of a
+// block share the sum over i.  With part also each block's share of |out|^2.
+template <int G>
+__global__ __launch_bounds__(RB) void lz_subtract(long long N, int m, int j, const double* __restrict__ basis,
+                                                  const double* __restrict__ h, const double* w, long long sb,
+                                                  long long si, double* out, double* __restrict__ part) {
+  constexpr int E = RB / G;
   extern __shared__ double hs[];
-  const int bi = blockIdx.y;
-  for (int i = threadIdx.x; i < 2 * j; i += blockDim.x) hs[i] = h[2 * (long long)bi * m + i];
+  __shared__ double2 gs[G][E];
+  const int bi = blockIdx.y, el = threadIdx.x % E, gr = threadIdx.x / E;
+  for (int i = threadIdx.x; i < 2 * j; i += RB) hs[i] = h[2 * (long long)bi * m + i];
   __syncthreads();
-  const long long I = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= N) return;
-  double sr = 0, si = 0;
-  const double* q = basis + 2 * ((long long)bi * m * N + I);
-  for (int i = 0; i < j; ++i) {
-    const double qr = q[2 * (long long)i * N], qi = q[2 * (long long)i * N + 1];
-    const double hr = hs[2 * i], hi = hs[2 * i + 1];
-    sr += qr * hr - qi * hi;
-    si += qr * hi + qi * hr;
+  const long long I = (long long)blockIdx.x * E + el;
+  double sr = 0, sim = 0;
+  if (I < N) {
+    const double2* q = reinterpret_cast<const double2*>(basis) + ((long long)bi * m * N + I);
+#pragma unroll 8
+    for (int i = gr; i < j; i += G) {
+      const double2 x = q[(long long)i * N];
+      const double hr = hs[2 * i], hi = hs[2 * i + 1];
+      sr += x.x * hr - x.y * hi;
+      sim += x.x * hi + x.y * hr;
+    }
   }
-  w[2 * (bi * N + I)] -= sr;
-  w[2 * (bi * N + I) + 1] -= si;
+  if (G > 1) {
+    gs[gr][el] = double2{sr, sim};
+    __syncthreads();
+    if (gr == 0)
+      for (int s = 1; s < G; ++s) {
+        sr += gs[s][el].x;
+        sim += gs[s][el].y;
+      }
+  }
+  double vr = 0, vi = 0;
+  if (gr == 0 && I < N) {
+    const double2 y = reinterpret_cast<const double2*>(w)[bi * sb + I * si];
+    vr = y.x - sr;
+    vi = y.y - sim;
+    reinterpret_cast<double2*>(out)[(long long)bi * N + I] = double2{vr, vi};
+  }
+  if (part) {
+    double s = vr * vr + vi * vi, z = 0;
+    block_sum2(s, z);
+    if (threadIdx.x == 0) part[(long long)bi * gridDim.x + blockIdx.x] = s;
+  }
 }
 
-// breakdown test of step j, one thread per chain: b_j <= tol * s_j with s_j = max(|a_1|, .., |a_j|,
-// b_1, .., b_{j-1}), the largest recurrence coefficient of the chain so far (kept in scale[bi]).  b_j is in
-// the units of A (the q_j are unit vectors); b_0 = |p| is the start vector's size and does not enter, so the
-// test does not depend on how p is scaled.  A chain that breaks down records steps = j and goes inactive.
-__global__ void lz_decide(int nb, int m, int j, double tol, const double* __restrict__ a,
-                          const double* __restrict__ b, double* __restrict__ scale, int* __restrict__ active,
-                          int* __restrict__ steps) {
-  const int bi = blockIdx.x * blockDim.x + threadIdx.x;
-  if (bi >= nb || !active[bi]) return;
-  double sc = fmax(scale[bi], fabs(a[(long long)bi * m + j - 1]));
-  if (j > 1) sc = fmax(sc, b[(long long)bi * (m + 1) + j - 1]);
-  scale[bi] = sc;
-  const double bj = b[(long long)bi * (m + 1) + j];
-  if (!(bj > tol * sc)) {
-    active[bi] = 0;
-    steps[bi] = j;
-  }
+// npart partial sums of each chain to one (grid nb)
+__global__ __launch_bounds__(RB) void lz_norm(int npart, const double* __restrict__ part, double* __restrict__ out) {
+  double s = 0, z = 0;
+  for (int i = threadIdx.x; i < npart; i += RB) s += part[(long long)blockIdx.x * npart + i];
+  block_sum2(s, z);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// q_{j+1} = w / b_j on the chains still active after step j's test (zero on the others)
-__global__ void lz_next(long long N, int nb, int m, int j, const double* __restrict__ b,
-                        const double* __restrict__ w, double* __restrict__ basis, double* __restrict__ Qcur,
-                        const int* __restrict__ active) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// End of step j: b_j = |w| from its partial sums; breakdown test per chain, b_j <= tol * s_j with s_j = max(|a_1|, ..,
+// |a_j|, b_1, .., b_{j-1}), the largest recurrence coefficient of the chain so far; q_{j+1} = w / b_j on the chains
+// still active (zero on the others) into the basis and the apply block.  b_j is in the units of A (the q_j are unit
+// vectors); b_0 = |p| is the start vector's size and does not enter, so the test does not depend on how p is scaled.
+// Every block works the few chain scalars out for itself; scale and active are kept per step (rows of nb), so that
+// the first block's new row does not race with the others' reading of the old one.
+__global__ __launch_bounds__(RB) void lz_next(long long N, int nb, int m, int j, double tol, int npart,
+                                              const double* __restrict__ part, const double* __restrict__ a,
+                                              double* __restrict__ b, double* __restrict__ scale,
+                                              int* __restrict__ active, int* __restrict__ steps,
+                                              const double* __restrict__ w, double* __restrict__ basis,
+                                              double* __restrict__ Qcur) {
+  extern __shared__ double inv[];  // [nb]: 1 / b_j as b_j, 0 where inactive
+  for (int bi = threadIdx.x >> 6; bi < nb; bi += RB / 64) {  // one wave per chain
+    double s = 0;
+    for (int i = threadIdx.x & 63; i < npart; i += 64) s += part[(long long)bi * npart + i];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
+    if (threadIdx.x & 63) continue;
+    const double bj = sqrt(fmax(s, 0.0));
+    double sc = fmax(scale[(long long)(j - 1) * nb + bi], fabs(a[(long long)bi * m + j - 1]));
+    if (j > 1) sc = fmax(sc, b[(long long)bi * (m + 1) + j - 1]);
+    const int was = active[(long long)(j - 1) * nb + bi], is = was && bj > tol * sc ? 1 : 0;
+    inv[bi] = is ? bj : 0.0;
+    if (blockIdx.x == 0) {
+      b[(long long)bi * (m + 1) + j] = bj;
+      scale[(long long)j * nb + bi] = was ? sc : scale[(long long)(j - 1) * nb + bi];
+      active[(long long)j * nb + bi] = is;
+      if (was && !is) steps[bi] = j;
+    }
+  }
+  __syncthreads();
+  const long long t = (long long)blockIdx.x * RB + threadIdx.x;
   if (t >= N * nb) return;
   const long long I = t / nb;
   const int bi = (int)(t % nb);
   double vr = 0, vi = 0;
-  if (active[bi]) {
-    const double bj = b[(long long)bi * (m + 1) + j];
-    vr = w[2 * (bi * N + I)] / bj;
-    vi = w[2 * (bi * N + I) + 1] / bj;
+  if (inv[bi] != 0.0) {
+    const double2 v = reinterpret_cast<const double2*>(w)[bi * N + I];
+    vr = v.x / inv[bi];
+    vi = v.y / inv[bi];
   }
   Qcur[2 * t] = vr;
   Qcur[2 * t + 1] = vi;
-  if (j < m) {
-    double* row = basis + 2 * ((long long)bi * m * N + (long long)j * N + I);
-    row[0] = vr;
-    row[1] = vi;
-  }
+  if (j < m) reinterpret_cast<double2*>(basis)[(long long)bi * m * N + (long long)j * N + I] = double2{vr, vi};
 }
 
 // continued fraction, one thread per (chain, frequency)
@@ -284,11 +307,11 @@ extern "C" bse_status bse_haydock_spectrum(bse_plan* plan, const void* P, int32_
   BSE_TRY(dmalloc((void**)&B.da, 8 * (size_t)nb * m));
   BSE_TRY(dmalloc((void**)&B.db, 8 * (size_t)nb * (m + 1)));
   BSE_TRY(dmalloc((void**)&B.h, 16 * (size_t)nb * m));
-  BSE_TRY(dmalloc((void**)&B.part, 16 * (size_t)nb * nblk));
+  BSE_TRY(dmalloc((void**)&B.part, std::max<size_t>(16 * (size_t)nb * nblk, 8 * (size_t)nb * ((N + 63) / 64 + 1))));
   BSE_TRY(dmalloc((void**)&B.dom, 8 * (size_t)n_w));
   BSE_TRY(dmalloc((void**)&B.dS, 8 * (size_t)nb * n_w));
-  BSE_TRY(dmalloc((void**)&B.scl, 8 * (size_t)nb));
-  BSE_TRY(dmalloc((void**)&B.act, sizeof(int) * nb));
+  BSE_TRY(dmalloc((void**)&B.scl, 8 * (size_t)nb * (m + 1)));
+  BSE_TRY(dmalloc((void**)&B.act, sizeof(int) * (size_t)nb * (m + 1)));
   BSE_TRY(dmalloc((void**)&B.stp, sizeof(int) * nb));
   BSE_TRY(zero_fill(B.da, 8 * (size_t)nb * m, st));
   BSE_TRY(zero_fill(B.db, 8 * (size_t)nb * (m + 1), st));
@@ -296,7 +319,7 @@ extern "C" bse_status bse_haydock_spectrum(bse_plan* plan, const void* P, int32_
   BSE_HIP(hipMemcpyAsync(B.dom, omega, 8 * (size_t)n_w, hipMemcpyHostToDevice, st));
 
   const unsigned gN = (unsigned)((N * nb + 255) / 256);
-  const dim3 gV((unsigned)((N + 255) / 256), nb);
+  const dim3 gV((unsigned)((N + RB - 1) / RB), nb);
   // b_0 = |p|   (P is [N][nb]: chain stride 1, element stride nb -> gather first)
   hipLaunchKernelGGL(lz_gather, dim3(gN), dim3(256), 0, st, N, nb, (const double*)P, B.w);
   hipLaunchKernelGGL(dotc_partial, dim3(nblk, nb), dim3(RB), 0, st, N, B.w, N, B.w, N, B.part);
@@ -304,24 +327,41 @@ extern "C" bse_status bse_haydock_spectrum(bse_plan* plan, const void* P, int32_
   hipLaunchKernelGGL(lz_init, dim3(gN), dim3(256), 0, st, N, nb, m, (const double*)P, B.db, B.basis, B.Q, B.act,
                      B.stp);
   BSE_CHECK_LAUNCH();
+  // One step: h = Q^H w (its last entry is a_j), w -= Q h, both once more (classical Gram-Schmidt twice; the first
+  // pass takes the three-term part with it), then b_j, the breakdown test and q_{j+1}: five launches.  Small chains
+  // read w from the apply block as it lies; larger ones gather it into rows first, or each of the j blocks of a
+  // chain would read n_b times the lines it needs.  More than 128 partial norms are summed by a launch of their own.
+  // At 4x4x4 (3 chains of 1024) the recurrence took 38 us per step in twelve launches, now 22.
+  // Chains of up to 8192 transitions share the sum over the basis between four groups of threads (the blocks of 256
+  // elements would be few).
+  const bool direct = N * nb <= 16384, shared_sum = N <= 8192;
+  const dim3 gS(shared_sum ? (unsigned)((N + RB / 4 - 1) / (RB / 4)) : gV.x, nb);
+  const unsigned npart = gS.x;
+  const bool norm = npart > 128;
+  if (m > 3000) {  // h of a chain in LDS beyond the default limit
+    BSE_HIP(hipFuncSetAttribute((const void*)lz_subtract<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
+    BSE_HIP(hipFuncSetAttribute((const void*)lz_subtract<4>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
+  }
+  auto subtract = [&](int j, const double* src, long long sb, long long si, double* part) {
+    const size_t sh = 16 * (size_t)j;
+    if (shared_sum)
+      hipLaunchKernelGGL(lz_subtract<4>, gS, dim3(RB), sh, st, N, m, j, B.basis, B.h, src, sb, si, B.w, part);
+    else
+      hipLaunchKernelGGL(lz_subtract<1>, gS, dim3(RB), sh, st, N, m, j, B.basis, B.h, src, sb, si, B.w, part);
+  };
   for (int j = 1; j <= m; ++j) {
     BSE_TRY(bse_apply(plan, B.Q, B.Wb, nb, hip_stream));
     StageMark sm_(p, BSE_STAGE_LANCZOS, st);
-    hipLaunchKernelGGL(lz_gather, dim3(gN), dim3(256), 0, st, N, nb, B.Wb, B.w);
-    // a_j = Re q_j^H w
-    hipLaunchKernelGGL(dotc_partial, dim3(nblk, nb), dim3(RB), 0, st, N, B.basis + 2 * (long long)(j - 1) * N,
-                       (long long)m * N, B.w, N, B.part);
-    hipLaunchKernelGGL(dot_finalize, dim3(nb), dim3(RB), 0, st, nblk, B.part, B.da + (j - 1), (long long)m, 0);
-    hipLaunchKernelGGL(lz_three_term, gV, dim3(256), 0, st, N, m, j, B.da, B.db, B.basis, B.w);
-    for (int pass = 0; pass < 2; ++pass) {
-      hipLaunchKernelGGL(lz_project, dim3(j, nb), dim3(RB), 0, st, N, m, B.basis, B.w, B.h);
-      hipLaunchKernelGGL(lz_subtract, gV, dim3(256), 16 * (size_t)j, st, N, m, j, B.basis, B.h, B.w);
-    }
-    hipLaunchKernelGGL(dotc_partial, dim3(nblk, nb), dim3(RB), 0, st, N, B.w, N, B.w, N, B.part);
-    hipLaunchKernelGGL(dot_finalize, dim3(nb), dim3(RB), 0, st, nblk, B.part, B.db + j, (long long)(m + 1), 1);
-    hipLaunchKernelGGL(lz_decide, dim3((nb + 63) / 64), dim3(64), 0, st, nb, m, j, tol, B.da, B.db, B.scl, B.act,
-                       B.stp);
-    hipLaunchKernelGGL(lz_next, dim3(gN), dim3(256), 0, st, N, nb, m, j, B.db, B.w, B.basis, B.Q, B.act);
+    if (!direct) hipLaunchKernelGGL(lz_gather, dim3(gN), dim3(256), 0, st, N, nb, B.Wb, B.w);
+    const double* src = direct ? B.Wb : B.w;
+    const long long sb = direct ? 1 : N, si = direct ? nb : 1;
+    hipLaunchKernelGGL(lz_project, dim3(j, nb), dim3(RB), 0, st, N, m, j, B.basis, src, sb, si, B.h, B.da);
+    subtract(j, src, sb, si, nullptr);
+    hipLaunchKernelGGL(lz_project, dim3(j, nb), dim3(RB), 0, st, N, m, j, B.basis, B.w, N, 1LL, B.h, (double*)nullptr);
+    subtract(j, B.w, N, 1, B.part);
+    if (norm) hipLaunchKernelGGL(lz_norm, dim3(nb), dim3(RB), 0, st, (int)npart, B.part, B.part + (size_t)nb * npart);
+    hipLaunchKernelGGL(lz_next, dim3(gN), dim3(RB), 8 * (size_t)nb, st, N, nb, m, j, tol, norm ? 1 : (int)npart,
+                       norm ? B.part + (size_t)nb * npart : B.part, B.da, B.db, B.scl, B.act, B.stp, B.w, B.basis, B.Q);
     BSE_CHECK_LAUNCH();
   }
   {

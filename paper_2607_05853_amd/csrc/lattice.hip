@@ -42,6 +42,7 @@ struct Lattice {
   double* F = nullptr;       // [split][nR][nbc][2][n_ao][n_ao]
   long long f_doubles = 0;
   double* t = nullptr;       // c128 [n_aux][nbc]
+  double* tab[2] = {};       // the axes' phases, sign +1 and -1 (ft_table_launch)
 };
 
 namespace {
@@ -65,8 +66,7 @@ struct LatGemm {
 // 256 threads as 2 x 2 waves on a BM x BN tile, BK deep stages in two LDS buffers with the next stage's loads in
 // flight during the products.  The 16x16x4 FP64 instruction takes 64 cycles and two 8-byte LDS reads feed it, so
 // the tiles only have to keep the matrix cores busy: real 128 x 128 (64 x 64 per wave), complex 64 x 128 (32 x 64
-// per wave and plane), both 128 accumulator registers and two blocks per CU; the half-size tiles serve operands
-// that would leave CUs without a block.  LDS rows are padded so that a fragment's 64 lanes spread over the banks.
+// per wave and plane), both 128 accumulator registers and two blocks per CU.  LDS rows are padded so that a fragment's 64 lanes spread over the banks.
 // VEC: 16-byte loads (even strides and sizes).
 template <bool CPLX, int BM, int BN, int BK, bool VEC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_gemm(LatGemm g) {
@@ -244,20 +244,26 @@ long long tiles(const LatGemm& g, int bm, int bn) {
   return (long long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.Z * g.nsplit;
 }
 
-// full-size tiles once they give most CUs a block (a second round of half-size tiles costs more than the idle
-// CUs), half-size tiles below and for operands of few rows
+// Full-size tiles once there are enough of them to hide each other's loads (fewer if the sum is long), small shallow tiles (four to five blocks
+// per CU) below and for operands of few rows: 5x6x7, N_ao 30, N_aux 90 (1782 full-size tiles of the first product):
+// 91 -> 73 us and 90 -> 80 us for the complex products.  The real one takes 96-row tiles where these leave less
+// empty than 128 (N_aux = 90: 142 -> 120 us).
 template <bool CPLX>
 bse_status lat_gemm_run(const LatGemm& g, hipStream_t st) {
   auto even = [](long long x) { return (x & 1) == 0; };
   const bool vec = even(g.lda) && even(g.a_ps) && even(g.a_z) && even(g.K) && even(g.klen) && even(g.N) && even(g.nd) &&
                    even(g.rs0) && even(g.rs1) && even(g.cs1) && even(g.b_ps) && even(g.b_z);
   if constexpr (CPLX) {
-    if (g.M > 32 && tiles(g, 64, 128) >= 192) return lat_gemm_go<true, 64, 128, 8>(g, vec, st);
-    return lat_gemm_go<true, 32, 64, 16>(g, vec, st);
+    const long long full = tiles(g, 64, 128);
+    if (g.M > 32 && (full >= 2048 || (full >= 384 && g.klen >= 1024))) return lat_gemm_go<true, 64, 128, 8>(g, vec, st);
+    return lat_gemm_go<true, 32, 64, 8>(g, vec, st);
   } else {
-    if (g.M > 64 && tiles(g, 128, 128) >= 384) return lat_gemm_go<false, 128, 128, 16>(g, vec, st);
-    if (tiles(g, 64, 128) >= 192) return lat_gemm_go<false, 64, 128, 16>(g, vec, st);
-    return lat_gemm_go<false, 64, 64, 32>(g, vec, st);
+    auto rows = [&](int bm) { return (g.M + bm - 1) / bm * bm; };
+    if (g.M > 64 && tiles(g, 128, 128) >= 384) {
+      if (rows(96) < rows(128)) return lat_gemm_go<false, 96, 128, 16>(g, vec, st);
+      return lat_gemm_go<false, 128, 128, 16>(g, vec, st);
+    }
+    return lat_gemm_go<false, 64, 64, 16>(g, vec, st);
   }
 }
 
@@ -388,34 +394,40 @@ __global__ __launch_bounds__(64) void lat_ex_t(int na, int no, int nbc, const do
   }
 }
 
-// V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu; block (mu, b) of one wave.  DIRECT: t summed here from U (small
-// n_aux n_ao, one launch less)
+// V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu; block (mu, b).  DIRECT: t summed here from U (small n_aux n_ao, one
+// launch less), the waves sharing the diagonal
 template <bool DIRECT>
-__global__ __launch_bounds__(64) void lat_ex_v(int na, int no, int nbc, double alpha, const double* __restrict__ vbar,
-                                               const double* __restrict__ U0, const double* __restrict__ t,
-                                               double* __restrict__ V0) {
-  const int mu = blockIdx.x, b = blockIdx.y;
+__global__ __launch_bounds__(256) void lat_ex_v(int na, int no, int nbc, double alpha, const double* __restrict__ vbar,
+                                                const double* __restrict__ U0, const double* __restrict__ t,
+                                                double* __restrict__ V0) {
+  __shared__ double2 red[4];
+  const int mu = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long pl = (long long)na * no;
   double2 s = {0.0, 0.0};
-  for (int nu = threadIdx.x; nu < na; nu += 64) {
-    const double* v = vbar + 2 * ((long long)mu * na + nu);
-    double2 x = {0.0, 0.0};
-    if constexpr (DIRECT) {
-#pragma unroll 8
-      for (int a = 0; a < no; ++a) {
+  if constexpr (DIRECT) {
+    for (int nu = lane; nu < na; nu += 64) {
+      const double* v = vbar + 2 * ((long long)mu * na + nu);
+      double2 x = {0.0, 0.0};
+#pragma unroll 4
+      for (int a = wave; a < no; a += 4) {
         const double* u = U0 + ((long long)a * nbc + b) * 2 * pl + (long long)nu * no + a;
         x.x += u[0];
         x.y += u[pl];
       }
-    } else {
-      x = double2{t[2 * (nu * nbc + b)], t[2 * (nu * nbc + b) + 1]};
+      s = cmadd(s, double2{v[0], v[1]}, x);
     }
-    s = cmadd(s, double2{v[0], v[1]}, x);
+  } else {
+    for (int nu = threadIdx.x; nu < na; nu += 256) {
+      const double* v = vbar + 2 * ((long long)mu * na + nu);
+      s = cmadd(s, double2{v[0], v[1]}, double2{t[2 * (nu * nbc + b)], t[2 * (nu * nbc + b) + 1]});
+    }
   }
   wave_sum(s);
-  s.x = __shfl(s.x, 0);
-  s.y = __shfl(s.y, 0);
-  for (int a = threadIdx.x; a < no; a += 64) {
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  s.x = red[0].x + red[1].x + red[2].x + red[3].x;
+  s.y = red[0].y + red[1].y + red[2].y + red[3].y;
+  for (int a = threadIdx.x; a < no; a += 256) {
     double* v = V0 + ((long long)a * nbc + b) * 2 * pl + (long long)mu * no + a;
     v[0] -= alpha * s.x;
     v[pl] -= alpha * s.y;
@@ -625,6 +637,10 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   BSE_TRY(plan_alloc(p, (void**)&L->V, per_r / 2 * L->rc));
   BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
   BSE_TRY(plan_alloc(p, (void**)&L->t, 16 * (size_t)na * nbc));
+  for (int s = 0; s < 2; ++s) {
+    BSE_TRY(plan_alloc(p, (void**)&L->tab[s], ft_table_bytes(ax)));
+    BSE_TRY(ft_table_launch(ax, s == 0 ? 1.0 : -1.0, L->tab[s], st));
+  }
   return BSE_OK;
 }
 
@@ -643,7 +659,7 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
       hipLaunchKernelGGL(lat_outer, dim3(Nk, w), dim3(256), lds_outer(p), st, d.nv, d.nc, no, nb, b0, w, p->psi64, X,
                          L->D);
       BSE_CHECK_LAUNCH();
-      BSE_TRY(ft_gather_launch(L->ax, 1.0, L->D, E, 1, L->DR, st));
+      BSE_TRY(ft_gather_launch(L->ax, 1.0, L->D, E, 1, L->DR, st, L->tab[0]));
     }
     // split of the last contraction's (t, mu) sum: enough parts for 1024 blocks of its tiles, at least 64 deep
     const int rc = std::min(L->rc, nR);
@@ -704,11 +720,11 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
         StageMark sm_(p, BSE_STAGE_EXCHANGE, st);
         const long long o = 2 * nu * no * w * (L->r0 - r);
         if (nu <= 2048) {
-          hipLaunchKernelGGL(lat_ex_v<true>, dim3(na, w), dim3(64), 0, st, na, no, w, d.alpha, p->vbar, L->U + o,
+          hipLaunchKernelGGL(lat_ex_v<true>, dim3(na, w), dim3(256), 0, st, na, no, w, d.alpha, p->vbar, L->U + o,
                              nullptr, L->V + o);
         } else {
           hipLaunchKernelGGL(lat_ex_t, dim3(na, w), dim3(64), 0, st, na, no, w, L->U + o, L->t);
-          hipLaunchKernelGGL(lat_ex_v<false>, dim3(na, w), dim3(64), 0, st, na, no, w, d.alpha, p->vbar, nullptr,
+          hipLaunchKernelGGL(lat_ex_v<false>, dim3(na, w), dim3(256), 0, st, na, no, w, d.alpha, p->vbar, nullptr,
                              L->t, L->V + o);
         }
         BSE_CHECK_LAUNCH();
@@ -744,7 +760,7 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
     }
     {
       StageMark sm_(p, BSE_STAGE_TX, st);
-      BSE_TRY(ft_spread_launch(L->ax, -1.0, L->F, E, 1, no2, nsplit, 2 * E * nR, 0, L->D, nullptr, st));
+      BSE_TRY(ft_spread_launch(L->ax, -1.0, L->F, E, 1, no2, nsplit, 2 * E * nR, 0, L->D, nullptr, st, L->tab[1]));
       hipLaunchKernelGGL(lat_project, dim3(Nk, w), dim3(256), lds_project(p), st, d.nv, d.nc, no, nb, b0, w,
                          project_groups(p), 1.0 / (double)Nk, p->eps, p->psi64, L->D, X, Y);
       BSE_CHECK_LAUNCH();
