@@ -43,6 +43,12 @@ struct Lattice {
   long long f_doubles = 0;
   double* t = nullptr;       // c128 [n_aux][nbc]
   double* tab[2] = {};       // the axes' phases, sign +1 and -1 (ft_table_launch)
+  // the Hermitian K(R) of one R of each pair (R, -R), R = 0 first: tiles (I, J), I <= J < S, at J (J + 1) / 2 + I, each
+  // [re, im][16 columns][16 rows]
+  double* K = nullptr;
+  int nh = 0, S = 0;
+  int2* pair = nullptr;      // [nh] places of R and -R in the list, the second -1 for R = 0
+  double* part = nullptr;    // partial sums of lat_kx
 };
 
 namespace {
@@ -61,14 +67,23 @@ struct LatGemm {
   long long ldc, cc1, c_ps, c_z;
   int nsplit, klen;                     // split of K: part s covers [s klen, ..) and writes C + s c_split
   long long c_split;
+  // TILED: C is one K(R) with S tiles per side.  Row m is (s, a) = rows[m], at s a_z + a lda of A; with column (b, s') it
+  // is row (s, s') and column (a, b) of K(R) (swap: row (s, a), column (s', b)), times scale, on top if add
+  // (rows with a >= s suffice then: the lower half of the diagonal tiles is filled in)
+  const int2* rows;
+  int S, swap, add;
+  double scale;
 };
+
+// tiles in front of tile (I, J) of a Hermitian matrix
+__device__ __forceinline__ long long lat_tile(int I, int J) { return (long long)J * (J + 1) / 2 + I; }
 
 // 256 threads as 2 x 2 waves on a BM x BN tile, BK deep stages in two LDS buffers with the next stage's loads in
 // flight during the products.  The 16x16x4 FP64 instruction takes 64 cycles and two 8-byte LDS reads feed it, so
 // the tiles only have to keep the matrix cores busy: real 128 x 128 (64 x 64 per wave), complex 64 x 128 (32 x 64
 // per wave and plane), both 128 accumulator registers and two blocks per CU.  LDS rows are padded so that a fragment's 64 lanes spread over the banks.
 // VEC: 16-byte loads (even strides and sizes).
-template <bool CPLX, int BM, int BN, int BK, bool VEC>
+template <bool CPLX, int BM, int BN, int BK, bool VEC, bool TILED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_gemm(LatGemm g) {
   constexpr int NP = CPLX ? 2 : 1;
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
@@ -103,7 +118,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
     const int row = m0 + u / (BK / 2);
     ak[i] = 2 * (u % (BK / 2));
     aok[i] = row < g.M;
-    ao[i] = pl * g.a_ps + (aok[i] ? row : 0) * g.lda;
+    const int r = aok[i] ? row : 0;
+    if constexpr (TILED)
+      ao[i] = pl * g.a_ps + g.rows[r].x * g.a_z + g.rows[r].y * g.lda;
+    else
+      ao[i] = pl * g.a_ps + r * g.lda;
   }
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
@@ -214,6 +233,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
   for (int j = 0; j < TN; ++j) {
     const int n = n0 + wn * WN + j * 16 + l16;
     if (n >= g.N) continue;
+    if constexpr (TILED) {
+      const int a = n % g.nd, b = n / g.nd;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int m = m0 + wm * WM + i * 16 + 4 * q + l4;
+          if (m >= g.M) continue;
+          const int2 r = g.rows[m];
+          const int row = r.x * g.nd + (g.swap ? r.y : a), col = (g.swap ? a : r.y) * g.nd + b;
+          if ((row >> 4) > (col >> 4)) continue;
+          double* c = g.C + lat_tile(row >> 4, col >> 4) * 512 + (col & 15) * 16 + (row & 15);
+#pragma unroll
+          for (int p = 0; p < NP; ++p) c[256 * p] = g.scale * acc[p][i][j][q] + (g.add ? c[256 * p] : 0.0);
+          if (!g.swap && r.x < r.y && (row >> 4) == (col >> 4)) {  // a diagonal tile's lower half
+            c += (row & 15) * 16 + (col & 15) - ((col & 15) * 16 + (row & 15));
+            c[0] = g.scale * acc[0][i][j][q];
+            c[256] = -g.scale * acc[NP - 1][i][j][q];
+          }
+        }
+      continue;
+    }
     double* c = C + (long long)(n / g.nd) * g.cc1 + n % g.nd;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -227,15 +268,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
   }
 }
 
-template <bool CPLX, int BM, int BN, int BK>
+template <bool CPLX, int BM, int BN, int BK, bool TILED = false>
 bse_status lat_gemm_go(const LatGemm& g, bool vec, hipStream_t st) {
   const int mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
   const long long groups = (long long)nt * g.Z * g.nsplit;
   const dim3 grid((unsigned)((groups + 7) / 8 * 8 * mt));
   if (vec)
-    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, true>), grid, dim3(256), 0, st, g);
+    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, true, TILED>), grid, dim3(256), 0, st, g);
   else
-    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, false>), grid, dim3(256), 0, st, g);
+    hipLaunchKernelGGL((lat_gemm<CPLX, BM, BN, BK, false, TILED>), grid, dim3(256), 0, st, g);
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }
@@ -248,12 +289,15 @@ long long tiles(const LatGemm& g, int bm, int bn) {
 // per CU) below and for operands of few rows: 5x6x7, N_ao 30, N_aux 90 (1782 full-size tiles of the first product):
 // 91 -> 73 us and 90 -> 80 us for the complex products.  The real one takes 96-row tiles where these leave less
 // empty than 128 (N_aux = 90: 142 -> 120 us).
-template <bool CPLX>
+template <bool CPLX, bool TILED = false>
 bse_status lat_gemm_run(const LatGemm& g, hipStream_t st) {
   auto even = [](long long x) { return (x & 1) == 0; };
   const bool vec = even(g.lda) && even(g.a_ps) && even(g.a_z) && even(g.K) && even(g.klen) && even(g.N) && even(g.nd) &&
                    even(g.rs0) && even(g.rs1) && even(g.cs1) && even(g.b_ps) && even(g.b_z);
-  if constexpr (CPLX) {
+  if constexpr (TILED) {
+    if (tiles(g, 64, 128) >= 512) return lat_gemm_go<true, 64, 128, 8, true>(g, vec, st);
+    return lat_gemm_go<true, 32, 64, 8, true>(g, vec, st);
+  } else if constexpr (CPLX) {
     const long long full = tiles(g, 64, 128);
     if (g.M > 32 && (full >= 2048 || (full >= 384 && g.klen >= 1024))) return lat_gemm_go<true, 64, 128, 8>(g, vec, st);
     return lat_gemm_go<true, 32, 64, 8>(g, vec, st);
@@ -367,6 +411,200 @@ __global__ __launch_bounds__(256) void lat_project(int nv, int nc, int no, int n
 }
 
 // ----------------------------------------------------------------------------
+// F(R) = K(R) D(R) and F(-R) = K(-R) D(-R) from one reading of half of K(R)
+// ----------------------------------------------------------------------------
+// With Hermitian C^mu and Vbar, K(R) is Hermitian, and W(-R) = W(R)^T makes K(-R)_ab,cd = K(R)_dc,ba: with
+// E_dc = conj(D(-R)_cd), G = K(R) E is G_ba = conj(F(-R)_ab).  So a pair (R, -R) and nb vectors are one Hermitian
+// matrix times 2 nb vectors.
+struct LatKx {
+  int no, w, b0, nb;       // D(R) is [2][no][w][no]; vectors b0 .. b0 + nb - 1 of w
+  int S, nh, RS, panels, cl;  // tiles per side, pairs of R, row tiles per panel, panels, column tiles per block
+  int blocks;              // per pair
+  long long E;             // no no w
+  const double* K;
+  const double* DR;
+  const int2* pair;
+  double* PF;              // [block of the panel][nh][16 S][16 NT]: upper tiles, columns 8 re then 8 im of eight vectors
+  double* PT;              // [panel][nh][16 S][16 NT]: their conjugate transposes
+};
+
+// One block per RS row tiles of a K(R) and cl of its column tiles, one column tile per wave at a time.  A wave reads
+// each 16 x 16 complex tile once, a tile ahead, multiplies it with the columns' vectors, turns it in LDS and multiplies
+// its conjugate transpose with the rows' vectors (in LDS); the sums of its rows stay in registers over all its column
+// tiles, those of its columns over its row tiles.  Eight vectors fill the 16 columns of the FP64 instruction with real
+// and imaginary parts, so a tile of 4 KiB is 16 NT instructions of 64 cycles: a CU that runs them back to back takes
+// 16 / NT bytes per cycle, where its share of the memory's rate is 8 to 9.
+template <int RS, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_kx(LatKx g) {
+  constexpr int N = 16 * NT, TS = 18;
+  __shared__ double dt[RS * 16 * N];
+  __shared__ double turn[4][2][16 * TS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l4 = lane >> 4, l16 = lane & 15;
+  const int h = (int)(blockIdx.x / g.blocks), no2 = g.no * g.no;
+  int panel = 0, c = (int)(blockIdx.x % g.blocks);  // block c of the panel
+  for (int n; c >= (n = (g.S - panel * RS + g.cl - 1) / g.cl); ++panel) c -= n;
+  const int i0 = panel * RS, ns = min(RS, g.S - i0);
+  const int c1 = min(g.S, i0 + (c + 1) * g.cl);
+  const int2 pr = g.pair[h];
+  const double* K = g.K + (long long)h * (g.S * (long long)(g.S + 1) / 2) * 512 + lane;
+  double tr[2][4], ti[2][4];
+  auto load = [&](int slot, int ct, int s) {
+    const double* p = K + lat_tile(min(i0 + min(s, ns - 1), ct), ct) * 512;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      tr[slot][q] = p[q * 64];
+      ti[slot][q] = p[256 + q * 64];
+    }
+  };
+  int ct = i0 + c * g.cl + wave;
+  if (ct < c1) load(0, ct, 0);
+  // element e = (a, b) of vector v (D(R), then E) is D[e / no * s1 + e % no * s2], im g.E behind
+  auto vec = [&](int v, int* s1, int* s2) {
+    const bool plus = v < g.nb;
+    *s1 = plus ? g.w * g.no : 1;
+    *s2 = plus ? 1 : g.w * g.no;
+    return g.DR + 2 * g.E * (plus ? pr.x : max(pr.y, 0)) + (g.b0 + (plus ? v : v - g.nb)) * g.no;
+  };
+  const int nvec = pr.y >= 0 ? 2 * g.nb : g.nb;
+  for (int i = tid; i < RS * 16 * N; i += 256) {
+    const int n = i % N, e = i0 * 16 + i / N, v = (n >> 4) * 8 + (n & 7);
+    double x = 0.0;
+    if (e < no2 && v < nvec) {
+      int s1, s2;
+      const double* d = vec(v, &s1, &s2) + (n & 8 ? g.E : 0);
+      x = d[e / g.no * s1 + e % g.no * s2];
+      if ((n & 8) && v >= g.nb) x = -x;
+    }
+    dt[i] = x;
+  }
+  __syncthreads();
+  d4v acc[RS][NT];
+#pragma unroll
+  for (int s = 0; s < RS; ++s)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[s][t] = d4v{0, 0, 0, 0};
+  double* const tu = turn[wave][0];
+  const double sign = l16 < 8 ? -1.0 : 1.0;
+  for (; ct < c1; ct += 4) {
+    const int next = ct + 4 < c1 ? ct + 4 : ct;
+    double b1[NT][4], b2[NT][4];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int v = 8 * j + (l16 & 7);
+      int s1, s2;
+      const double* d = vec(min(v, nvec - 1), &s1, &s2);
+      const double im = v < g.nb ? 1.0 : -1.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = ct * 16 + 4 * q + l4;
+        const bool ok = e < no2 && v < nvec;
+        const int o = ok ? e / g.no * s1 + e % g.no * s2 : 0;
+        const double x = d[o], y = im * d[g.E + o];
+        b1[j][q] = ok ? (l16 < 8 ? x : y) : 0.0;
+        b2[j][q] = ok ? (l16 < 8 ? -y : x) : 0.0;
+      }
+    }
+    d4v at[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) at[j] = d4v{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < RS; ++s) {
+      const int sl = s & 1;
+      if (s + 1 < RS)
+        load(sl ^ 1, ct, s + 1);
+      else
+        load(sl ^ 1, next, 0);
+      if (s < ns && i0 + s <= ct) {
+        const bool off = i0 + s < ct;
+        if (off) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            tu[(4 * q + l4) * TS + l16] = tr[sl][q];
+            tu[16 * TS + (4 * q + l4) * TS + l16] = ti[sl][q];
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) {
+            acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(tr[sl][q], b1[j][q], acc[s][j], 0, 0, 0);
+            acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ti[sl][q], b2[j][q], acc[s][j], 0, 0, 0);
+          }
+        if (off) {
+          // the wave's own buffer: its LDS accesses run in order, the fences only hold the compiler
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double ar = tu[l16 * TS + 4 * q + l4], ai = -tu[16 * TS + l16 * TS + 4 * q + l4];
+            const double* d = dt + (s * 16 + 4 * q + l4) * N;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+              at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, d[16 * j + l16], at[j], 0, 0, 0);
+              at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, sign * d[16 * j + (l16 ^ 8)], at[j], 0, 0, 0);
+            }
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+      }
+    }
+    double* o = g.PT + (((long long)panel * g.nh + h) * g.S + ct) * 16 * N;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) o[(4 * q + l4) * N + 16 * j + l16] = at[j][q];
+  }
+  // the four waves' rows added in order
+  for (int v = 0; v < 4; ++v) {
+    __syncthreads();
+    if (wave == v) {
+#pragma unroll
+      for (int s = 0; s < RS; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) {
+            const int i = (s * 16 + 4 * q + l4) * N + 16 * j + l16;
+            dt[i] = v ? dt[i] + acc[s][j][q] : acc[s][j][q];
+          }
+    }
+  }
+  __syncthreads();
+  double* o = g.PF + (((long long)c * g.nh + h) * g.S + i0) * 16 * N;
+  for (int i = tid; i < ns * 16 * N; i += 256) o[i] = dt[i];
+}
+
+// F from the partial sums, F(R)_ab at row (a, b) and conj F(-R)_ab at row (b, a): block (16 b of an a; pair and sign;
+// eight vectors) of 16 rows x 16 columns, turned in LDS so that F [R][vector][2][a][b] is written in runs of b
+__global__ __launch_bounds__(256) void lat_kx_sum(LatKx g, int N, double* __restrict__ F) {
+  __shared__ double x[16][17];
+  const int bl = (g.no + 15) / 16;
+  const int a = blockIdx.x / bl, b = blockIdx.x % bl * 16 + (threadIdx.x >> 4);
+  const int h = blockIdx.y >> 1, minus = blockIdx.y & 1, n = threadIdx.x & 15;
+  const int2 pr = g.pair[h];
+  const int R = minus ? pr.y : pr.x, v0 = blockIdx.z * 8 - (minus ? g.nb : 0);  // vector of column 0
+  if (R < 0 || v0 + 7 < 0 || v0 >= g.nb) return;
+  const long long rows = 16ll * g.S, step = (long long)g.nh * rows * N;
+  double s = 0.0;
+  if (b < g.no && (unsigned)(v0 + (n & 7)) < (unsigned)g.nb) {
+    const int e = minus ? b * g.no + a : a * g.no + b, panel = (e >> 4) / g.RS;
+    const long long o = (h * rows + e) * N + blockIdx.z * 16 + n;
+    const int nf = (g.S - panel * g.RS + g.cl - 1) / g.cl;
+    for (int i = 0; i < nf; ++i) s += g.PF[o + i * step];
+#pragma unroll 4
+    for (int i = 0; i <= panel; ++i) s += g.PT[o + i * step];
+  }
+  x[n][threadIdx.x >> 4] = minus && (n & 8) ? -s : s;
+  __syncthreads();
+  const int m = threadIdx.x >> 4, v = v0 + (m & 7), bo = blockIdx.x % bl * 16 + (threadIdx.x & 15);
+  if ((unsigned)v < (unsigned)g.nb && bo < g.no)
+    F[2 * g.E * R + ((long long)(g.b0 + v) * 2 + (m >> 3)) * g.no * g.no + a * g.no + bo] = x[m][threadIdx.x & 15];
+}
+
+// ----------------------------------------------------------------------------
 // exchange term
 // ----------------------------------------------------------------------------
 __device__ __forceinline__ void wave_sum(double2& s) {
@@ -469,6 +707,32 @@ __global__ void lat_take_real(long long n, const int* __restrict__ idx, const do
   }
 }
 
+// largest |W(R)_ij - W(-R)_ji| of the pairs (R = 0 with itself), as bits; 16 x 16 elements per block
+__global__ __launch_bounds__(256) void lat_asym(int na, const int2* __restrict__ pair, int r0,
+                                                const double* __restrict__ Wr, unsigned long long* __restrict__ out) {
+  __shared__ double x[16][17];
+  const int2 pr = pair[blockIdx.z];
+  const double* w = Wr + (long long)pr.x * na * na;
+  const double* v = Wr + (long long)(pr.y < 0 ? r0 : pr.y) * na * na;
+  const int a = threadIdx.x >> 4, b = threadIdx.x & 15, i0 = blockIdx.x * 16, j0 = blockIdx.y * 16;
+  x[a][b] = j0 + a < na && i0 + b < na ? v[(long long)(j0 + a) * na + i0 + b] : 0.0;
+  __syncthreads();
+  double m = i0 + a < na && j0 + b < na ? fabs(w[(long long)(i0 + a) * na + j0 + b] - x[b][a]) : 0.0;
+  for (int o = 32; o > 0; o >>= 1) {
+    const double s = __shfl_down(m, o);
+    if (!(s <= m)) m = s;
+  }
+  if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(m));
+}
+
+// planes of re and im
+__global__ void lat_planes(long long n, const double* __restrict__ A, double* __restrict__ P) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    P[i] = A[2 * i];
+    P[n + i] = A[2 * i + 1];
+  }
+}
+
 __global__ void lat_pack_C(int na, int no, long long ldc, const double* __restrict__ C, double* __restrict__ C1,
                            double* __restrict__ C3) {
   const long long n = (long long)na * no * no;
@@ -493,14 +757,60 @@ struct Tmp {
   ~Tmp() { dfree(p); }
 };
 
-// operations of one application over R and over pairs of k
-double flops_lattice(const Plan* p, int nb) {
-  const double na = p->d.n_aux, no = p->d.n_ao;
-  return (double)nb * p->lat->nR * (16.0 * na * no * no * no + 4.0 * na * na * no * no);
-}
-double flops_pairs(const Plan* p) {
+// seconds of the matrix work of one application over pairs of k, over nR lattice vectors in three contractions, and over
+// kernels K(R); the rates are those of the 8x8x8 workload (N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors), whose
+// pair route has GEMMs of a few rows per pair
+double secs_pairs(const Plan* p) {
   const double na = p->d.n_aux, no = p->d.n_ao, nv = p->d.nv, nc = p->d.nc;
-  return 8.0 * p->Nk * p->nhalf * (na * no * (nv * nv + nc * nc) + na * na * nv * nv + na * nv * nv * nc * nc);
+  return 8.0 * p->Nk * p->nhalf * (na * no * (nv * nv + nc * nc) + na * na * nv * nv + na * nv * nv * nc * nc) / 37e12;
+}
+double secs_gemm(const Plan* p, int nR, int nb) {
+  const double na = p->d.n_aux, no = p->d.n_ao;
+  return (double)nb * nR * (16.0 * na * no * no * no + 4.0 * na * na * no * no) / 56e12;
+}
+int kx_tiles(const Plan* p) { return (p->d.n_ao * p->d.n_ao + 15) / 16; }
+size_t kx_bytes(const Plan* p, int nh) { return (size_t)kx_tiles(p) * (kx_tiles(p) + 1) / 2 * 4096 * nh; }
+double secs_kernel(const Plan* p, int nR, int nb) {
+  const double b = (double)kx_bytes(p, (nR + 1) / 2);
+  return (nb / 8 + (nb % 8 > 4)) * b / 3.2e12 + (nb % 8 && nb % 8 <= 4 ? b / 4e12 : 0.0);
+}
+
+struct KxShape {
+  int RS, NT, panels, cl, blocks, most;
+  size_t doubles(int nh, int S) const { return (size_t)(most + panels) * nh * S * 256 * NT; }
+};
+// NT: 2 nb vectors in groups of eight.  Rows per block: 16 NT = 1 or 8 NT = 2 tiles (the same registers; the sums of the
+// columns go through memory once per panel), 4 where that leaves CUs idle.  Columns per block: about 2 MiB of tiles,
+// less until there are 1024 blocks.
+KxShape kx_shape(int nh, int S, int nb) {
+  KxShape x;
+  x.NT = nb > 4 ? 2 : 1;
+  x.RS = 16 / x.NT;
+  auto count = [&] {
+    x.panels = (S + x.RS - 1) / x.RS;
+    x.blocks = 0;
+    for (int i = 0; i < x.panels; ++i) x.blocks += (S - i * x.RS + x.cl - 1) / x.cl;
+    x.most = (S + x.cl - 1) / x.cl;
+  };
+  x.cl = 4;
+  count();
+  if ((long long)nh * x.blocks < 512) x.RS = 4;
+  for (x.cl = 512 / x.RS, count(); x.cl > 4 && (long long)nh * x.blocks < 1024; count()) x.cl /= 2;
+  return x;
+}
+
+bse_status kx_go(const LatKx& g, const KxShape& x, hipStream_t st) {
+  const dim3 grid((unsigned)(g.nh * x.blocks));
+  if (x.NT == 1 && x.RS == 16)
+    hipLaunchKernelGGL((lat_kx<16, 1>), grid, dim3(256), 0, st, g);
+  else if (x.NT == 1)
+    hipLaunchKernelGGL((lat_kx<4, 1>), grid, dim3(256), 0, st, g);
+  else if (x.RS == 8)
+    hipLaunchKernelGGL((lat_kx<8, 2>), grid, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL((lat_kx<4, 2>), grid, dim3(256), 0, st, g);
+  BSE_CHECK_LAUNCH();
+  return BSE_OK;
 }
 
 }  // namespace
@@ -513,8 +823,104 @@ void lattice_free(Plan* p) {
 // Whether an application to nb vectors goes over R: by the matrix work of the two routes, the pair route counted
 // 1.5 times because its GEMMs of a few rows per pair run at 33 TFLOP/s (8x8x8 workload) against 56 here
 bool lattice_applies(const Plan* p, int nb) {
-  return p->lat && flops_lattice(p, nb) < 1.5 * flops_pairs(p);
+  if (!p->lat) return false;
+  const int nR = p->lat->nR;
+  return (p->lat->K ? secs_kernel(p, nR, nb) : secs_gemm(p, nR, nb)) < secs_pairs(p);
 }
+
+namespace {
+
+// K(R)_ss',tt' = sum_munu C^mu_ts W(R)_munu C^nu_s't' of one R of each pair; the exchange term, the same at all R = 0,
+// is K(0)_ss',tt' -= alpha sum_munu C^mu_s's Vbar_munu C^nu_tt'
+bse_status kernels_build(Plan* p, const std::vector<int2>& pair, hipStream_t st) {
+  Lattice* L = p->lat;
+  const int na = p->d.n_aux, no = p->d.n_ao;
+  const long long no2 = (long long)no * no, n2 = (long long)na * na, hp = no2 * na;
+  L->nh = (int)pair.size();
+  L->S = kx_tiles(p);
+  BSE_TRY(plan_alloc(p, (void**)&L->pair, sizeof(int2) * pair.size()));
+  BSE_HIP(hipMemcpyAsync(L->pair, pair.data(), sizeof(int2) * pair.size(), hipMemcpyHostToDevice, st));
+  BSE_TRY(plan_alloc(p, (void**)&L->K, kx_bytes(p, L->nh)));
+  if (no2 % 16) BSE_TRY(zero_fill(L->K, kx_bytes(p, L->nh), st));
+  Tmp H, vp, rows;
+  BSE_TRY(dmalloc(&H.p, 16 * (size_t)hp));
+  std::vector<int2> list;  // (s, t) with t >= s, then all
+  for (int s = 0; s < no; ++s)
+    for (int t = s; t < no; ++t) list.push_back(int2{s, t});
+  const int tri = (int)list.size();
+  for (int i = 0; i < (int)no2; ++i) list.push_back(int2{i / no, i % no});
+  BSE_TRY(dmalloc(&rows.p, sizeof(int2) * list.size()));
+  BSE_HIP(hipMemcpyAsync(rows.p, list.data(), sizeof(int2) * list.size(), hipMemcpyHostToDevice, st));
+  LatGemm k{};  // rows (s, t), columns (t', s')
+  k.M = tri;
+  k.N = (int)no2;
+  k.K = na;
+  k.Z = 1;
+  k.rows = (const int2*)rows.p;
+  k.A = L->C3;
+  k.lda = na;
+  k.a_ps = no * L->ldc;
+  k.a_z = L->ldc;
+  k.B = (const double*)H.p;
+  k.kd = na;
+  k.rs0 = no;
+  k.nd = no;
+  k.cs1 = (long long)na * no;
+  k.b_ps = hp;
+  k.nsplit = 1;
+  k.klen = na;
+  k.S = L->S;
+  LatGemm h{};  // H^mu_s't' = sum_nu W(R)_munu C^nu_s't', [2][t'][mu][s']
+  h.M = na;
+  h.K = na;
+  h.Z = 1;
+  h.lda = na;
+  h.B = L->C1;
+  h.kd = na;
+  h.rs0 = no;
+  h.nd = no;
+  h.cs1 = L->ldc;
+  h.C = (double*)H.p;
+  h.ldc = no;
+  h.cc1 = (long long)na * no;
+  h.nsplit = 1;
+  h.klen = na;
+  for (int i = 0; i < L->nh; ++i) {
+    h.N = 2 * (int)no2;
+    h.A = L->Wr + pair[i].x * n2;
+    BSE_TRY(lat_gemm_run<false>(h, st));
+    k.C = L->K + (long long)i * (L->S * (long long)(L->S + 1) / 2) * 512;
+    k.scale = 1.0;
+    BSE_TRY((lat_gemm_run<true, true>(k, st)));
+    if (i == 0 && p->d.alpha != 0.0) {
+      BSE_TRY(dmalloc(&vp.p, 16 * (size_t)n2));
+      hipLaunchKernelGGL(lat_planes, dim3(256), dim3(256), 0, st, n2, p->vbar, (double*)vp.p);
+      BSE_CHECK_LAUNCH();
+      h.N = (int)no2;
+      h.A = (const double*)vp.p;
+      h.a_ps = n2;
+      h.b_ps = no * L->ldc;
+      h.c_ps = hp;
+      BSE_TRY(lat_gemm_run<true>(h, st));
+      k.swap = k.add = 1;
+      k.scale = -p->d.alpha;
+      k.M = (int)no2;
+      k.rows += tri;
+      BSE_TRY((lat_gemm_run<true, true>(k, st)));
+      k.swap = k.add = 0;
+      k.M = tri;
+      k.rows -= tri;
+    }
+  }
+  size_t part = 0;
+  for (int b : {1, 8})
+    if (b == 1 || L->nbc > 4) part = std::max(part, kx_shape(L->nh, L->S, b).doubles(L->nh, L->S));
+  BSE_TRY(plan_alloc(p, (void**)&L->part, 8 * part));
+  BSE_HIP(hipStreamSynchronize(st));
+  return BSE_OK;
+}
+
+}  // namespace
 
 // Finds the R set of W_q: W(R) on a box of at most 7 x 7 x 7 around R = 0 by the inverse sum, the R whose matrix is
 // not rounding noise, and a check that they give W_q back to 1e-14 of its largest element (a W_q that is no such sum
@@ -542,8 +948,8 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   const int nbox = (int)R.size() / 3;
   // worth looking at only if a small set would win for one vector
   {
-    const double one = std::min(nbox, 7) * (16.0 * na * (double)no * no * no + 4.0 * na * (double)na * no * no);
-    if (one > 1.5 * flops_pairs(p)) return BSE_OK;
+    const int few = std::min(nbox, 7);
+    if (std::min(secs_gemm(p, few, 1), secs_kernel(p, few, 1)) > secs_pairs(p)) return BSE_OK;
   }
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
@@ -591,7 +997,17 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   L->nR = nR;
   for (int r = 0; r < nR; ++r)
     if (act[3 * r] == 0 && act[3 * r + 1] == 0 && act[3 * r + 2] == 0) L->r0 = r;
-  if (!lattice_applies(p, 1)) {
+  // the R in pairs, R = 0 first
+  std::vector<int2> pair{int2{L->r0, -1}};
+  for (int r = 0; r < nR; ++r)
+    for (int s = r + 1; s < nR; ++s)
+      if (act[3 * r] == -act[3 * s] && act[3 * r + 1] == -act[3 * s + 1] && act[3 * r + 2] == -act[3 * s + 2])
+        pair.push_back(int2{r, s});
+  size_t room = budget;
+  if (const char* e = std::getenv("BSE_WORKSPACE_GB")) room = (size_t)(std::atof(e) * (double)(1ull << 30));
+  bool kernels = 2 * (int)pair.size() - 1 == nR && kx_bytes(p, (nR + 1) / 2) <= std::min(room, budget) &&
+                 secs_kernel(p, nR, p->max_nb) < secs_gemm(p, nR, p->max_nb);
+  if (!((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) {
     lattice_free(p);
     return BSE_OK;
   }
@@ -613,6 +1029,19 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
     lattice_free(p);
     return BSE_OK;
   }
+  if (kernels) {  // W(-R) = W(R)^T as of a Hermitian W_q
+    double asym = 0.0;
+    Tmp pr;
+    BSE_TRY(dmalloc(&pr.p, sizeof(int2) * pair.size()));
+    BSE_HIP(hipMemcpyAsync(pr.p, pair.data(), sizeof(int2) * pair.size(), hipMemcpyHostToDevice, st));
+    BSE_TRY(zero_fill(dmax, 8, st));
+    hipLaunchKernelGGL(lat_asym, dim3((na + 15) / 16, (na + 15) / 16, (unsigned)pair.size()), dim3(256), 0, st, na,
+                       (const int2*)pr.p, L->r0, L->Wr, (unsigned long long*)dmax);
+    BSE_CHECK_LAUNCH();
+    BSE_HIP(hipMemcpyAsync(&asym, dmax, 8, hipMemcpyDeviceToHost, st));
+    BSE_HIP(hipStreamSynchronize(st));
+    kernels = asym <= 1e-14 * top;
+  }
   L->ldc = ((long long)na * no + 15) / 16 * 16 + 16;
   BSE_TRY(plan_alloc(p, (void**)&L->C1, 16 * (size_t)(no * L->ldc)));
   BSE_TRY(plan_alloc(p, (void**)&L->C3, 16 * (size_t)(no * L->ldc)));
@@ -620,27 +1049,29 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   BSE_CHECK_LAUNCH();
   // workspaces: all max_nb vectors at once and R in passes of about 4 GiB of U and V, fewer vectors when D(k) and
   // the R arrays would not fit; 8 partial F(R) for the split of the last contraction, 32 of small ones
-  size_t room = budget;
-  if (const char* e = std::getenv("BSE_WORKSPACE_GB")) room = (size_t)(std::atof(e) * (double)(1ull << 30));
   const size_t no2 = (size_t)no * no;
   int nbc = p->max_nb;
   auto fixed = [&](int b) { return 16 * no2 * b * ((size_t)Nk + 10 * (size_t)nR); };
   while (nbc > 1 && fixed(nbc) > room / 2) nbc = (nbc + 1) / 2;
   L->nbc = nbc;
-  const size_t per_r = 32 * (size_t)nc1 * nbc;
-  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / per_r));
-  const size_t f1 = 2 * no2 * nbc * (size_t)nR;
-  L->f_doubles = (long long)(f1 * (f1 > ((size_t)1 << 22) ? 8 : 32));
   BSE_TRY(plan_alloc(p, (void**)&L->D, 16 * no2 * nbc * (size_t)Nk));
   BSE_TRY(plan_alloc(p, (void**)&L->DR, 16 * no2 * nbc * (size_t)nR));
-  BSE_TRY(plan_alloc(p, (void**)&L->U, per_r / 2 * L->rc));
-  BSE_TRY(plan_alloc(p, (void**)&L->V, per_r / 2 * L->rc));
-  BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
-  BSE_TRY(plan_alloc(p, (void**)&L->t, 16 * (size_t)na * nbc));
   for (int s = 0; s < 2; ++s) {
     BSE_TRY(plan_alloc(p, (void**)&L->tab[s], ft_table_bytes(ax)));
     BSE_TRY(ft_table_launch(ax, s == 0 ? 1.0 : -1.0, L->tab[s], st));
   }
+  if (kernels) {
+    BSE_TRY(plan_alloc(p, (void**)&L->F, 16 * no2 * nbc * (size_t)nR));
+    return kernels_build(p, pair, st);
+  }
+  const size_t per_r = 32 * (size_t)nc1 * nbc;
+  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / per_r));
+  const size_t f1 = 2 * no2 * nbc * (size_t)nR;
+  L->f_doubles = (long long)(f1 * (f1 > ((size_t)1 << 22) ? 8 : 32));
+  BSE_TRY(plan_alloc(p, (void**)&L->U, per_r / 2 * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->V, per_r / 2 * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
+  BSE_TRY(plan_alloc(p, (void**)&L->t, 16 * (size_t)na * nbc));
   return BSE_OK;
 }
 
@@ -654,12 +1085,35 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
   for (int b0 = 0; b0 < nb; b0 += L->nbc) {
     const int w = std::min(L->nbc, nb - b0);
     const long long E = no2 * w;
+    auto project = [&](int nsplit) -> bse_status {
+      BSE_TRY(ft_spread_launch(L->ax, -1.0, L->F, E, 1, no2, nsplit, 2 * E * nR, 0, L->D, nullptr, st, L->tab[1]));
+      hipLaunchKernelGGL(lat_project, dim3(Nk, w), dim3(256), lds_project(p), st, d.nv, d.nc, no, nb, b0, w,
+                         project_groups(p), 1.0 / (double)Nk, p->eps, p->psi64, L->D, X, Y);
+      BSE_CHECK_LAUNCH();
+      return BSE_OK;
+    };
     {
       StageMark sm_(p, BSE_STAGE_PAIRDENS_V, st);
       hipLaunchKernelGGL(lat_outer, dim3(Nk, w), dim3(256), lds_outer(p), st, d.nv, d.nc, no, nb, b0, w, p->psi64, X,
                          L->D);
       BSE_CHECK_LAUNCH();
       BSE_TRY(ft_gather_launch(L->ax, 1.0, L->D, E, 1, L->DR, st, L->tab[0]));
+    }
+    if (L->K) {
+      for (int g0 = 0; g0 < w; g0 += 8) {
+        const int n = std::min(8, w - g0);
+        const KxShape x = kx_shape(L->nh, L->S, n);
+        LatKx g{no, w, g0, n, L->S, L->nh, x.RS, x.panels, x.cl, x.blocks, E, L->K, L->DR, L->pair, L->part, nullptr};
+        g.PT = L->part + (size_t)x.most * L->nh * L->S * 256 * x.NT;
+        StageMark sm_(p, BSE_STAGE_DBLOCK, st);
+        BSE_TRY(kx_go(g, x, st));
+        hipLaunchKernelGGL(lat_kx_sum, dim3(no * ((no + 15) / 16), 2 * L->nh, x.NT), dim3(256), 0, st, g, 16 * x.NT,
+                           L->F);
+        BSE_CHECK_LAUNCH();
+      }
+      StageMark sm_(p, BSE_STAGE_TX, st);
+      BSE_TRY(project(1));
+      continue;
     }
     // split of the last contraction's (t, mu) sum: enough parts for 1024 blocks of its tiles, at least 64 deep
     const int rc = std::min(L->rc, nR);
@@ -758,13 +1212,8 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
         BSE_TRY(lat_gemm_run<true>(g, st));
       }
     }
-    {
-      StageMark sm_(p, BSE_STAGE_TX, st);
-      BSE_TRY(ft_spread_launch(L->ax, -1.0, L->F, E, 1, no2, nsplit, 2 * E * nR, 0, L->D, nullptr, st, L->tab[1]));
-      hipLaunchKernelGGL(lat_project, dim3(Nk, w), dim3(256), lds_project(p), st, d.nv, d.nc, no, nb, b0, w,
-                         project_groups(p), 1.0 / (double)Nk, p->eps, p->psi64, L->D, X, Y);
-      BSE_CHECK_LAUNCH();
-    }
+    StageMark sm_(p, BSE_STAGE_TX, st);
+    BSE_TRY(project(nsplit));
   }
   return BSE_OK;
 }
