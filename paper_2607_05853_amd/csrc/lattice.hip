@@ -44,7 +44,8 @@ struct Lattice {
   double* t = nullptr;       // c128 [n_aux][nbc]
   double* tab[2] = {};       // the axes' phases, sign +1 and -1 (ft_table_launch)
   // the Hermitian K(R) of one R of each pair (R, -R), R = 0 first: tiles (I, J), I <= J < S, at J (J + 1) / 2 + I, each
-  // [re, im][16 columns][16 rows]
+  // [re, im][16 columns][16 rows], the diagonal ones halved (half of a tile and its conjugate transpose are the tile); then
+  // a tile of zeros
   double* K = nullptr;
   int nh = 0, S = 0;
   int2* pair = nullptr;      // [nh] places of R and -R in the list, the second -1 for R = 0
@@ -245,12 +246,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
           const int row = r.x * g.nd + (g.swap ? r.y : a), col = (g.swap ? a : r.y) * g.nd + b;
           if ((row >> 4) > (col >> 4)) continue;
           double* c = g.C + lat_tile(row >> 4, col >> 4) * 512 + (col & 15) * 16 + (row & 15);
+          const bool diag = (row >> 4) == (col >> 4);
+          const double f = diag ? 0.5 * g.scale : g.scale;
 #pragma unroll
-          for (int p = 0; p < NP; ++p) c[256 * p] = g.scale * acc[p][i][j][q] + (g.add ? c[256 * p] : 0.0);
-          if (!g.swap && r.x < r.y && (row >> 4) == (col >> 4)) {  // a diagonal tile's lower half
+          for (int p = 0; p < NP; ++p) c[256 * p] = f * acc[p][i][j][q] + (g.add ? c[256 * p] : 0.0);
+          if (!g.swap && r.x < r.y && diag) {  // its lower half
             c += (row & 15) * 16 + (col & 15) - ((col & 15) * 16 + (row & 15));
-            c[0] = g.scale * acc[0][i][j][q];
-            c[256] = -g.scale * acc[NP - 1][i][j][q];
+            c[0] = f * acc[0][i][j][q];
+            c[256] = -f * acc[NP - 1][i][j][q];
           }
         }
       continue;
@@ -422,6 +425,7 @@ struct LatKx {
   int blocks;              // per pair
   long long E;             // no no w
   const double* K;
+  const double* zero;      // a tile of zeros, for the places of a panel below the diagonal or past the last row
   const double* DR;
   const int2* pair;
   double* PF;              // [block of the panel][nh][16 S][16 NT]: upper tiles, columns 8 re then 8 im of eight vectors
@@ -429,31 +433,35 @@ struct LatKx {
 };
 
 // One block per RS row tiles of a K(R) and cl of its column tiles, one column tile per wave at a time.  A wave reads
-// each 16 x 16 complex tile once, a tile ahead, multiplies it with the columns' vectors, turns it in LDS and multiplies
-// its conjugate transpose with the rows' vectors (in LDS); the sums of its rows stay in registers over all its column
-// tiles, those of its columns over its row tiles.  Eight vectors fill the 16 columns of the FP64 instruction with real
-// and imaginary parts, so a tile of 4 KiB is 16 NT instructions of 64 cycles: a CU that runs them back to back takes
+// each 16 x 16 complex tile once, a tile ahead, multiplies it with the columns' vectors and its conjugate transpose,
+// turned in LDS, with the rows' vectors (in LDS); the sums of its rows stay in registers over all its column tiles,
+// those of its columns over its row tiles.  Eight vectors fill the 16 columns of the FP64 instruction with real and
+// imaginary parts, so a tile of 4 KiB is 16 NT instructions of 64 cycles: a CU that runs them back to back takes
 // 16 / NT bytes per cycle, where its share of the memory's rate is 8 to 9.
 template <int RS, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_kx(LatKx g) {
   constexpr int N = 16 * NT, TS = 18;
   __shared__ double dt[RS * 16 * N];
   __shared__ double turn[4][2][16 * TS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l4 = lane >> 4, l16 = lane & 15;
-  const int h = (int)(blockIdx.x / g.blocks), no2 = g.no * g.no;
-  int panel = 0, c = (int)(blockIdx.x % g.blocks);  // block c of the panel
+  const int tid = threadIdx.x, lane = tid & 63, l4 = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // each XCD takes an eighth of the blocks, in order: D(R) then stays in its L2 while it works on that R
+  const unsigned all = (unsigned)g.nh * g.blocks, per = (all + 7) / 8, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (id >= all) return;
+  const int h = (int)(id / g.blocks), no2 = g.no * g.no;
+  int panel = 0, c = (int)(id % g.blocks);  // block c of the panel
   for (int n; c >= (n = (g.S - panel * RS + g.cl - 1) / g.cl); ++panel) c -= n;
   const int i0 = panel * RS, ns = min(RS, g.S - i0);
   const int c1 = min(g.S, i0 + (c + 1) * g.cl);
   const int2 pr = g.pair[h];
-  const double* K = g.K + (long long)h * (g.S * (long long)(g.S + 1) / 2) * 512 + lane;
+  const double* K = g.K + (long long)h * (g.S * (long long)(g.S + 1) / 2) * 512;
   double tr[2][4], ti[2][4];
   auto load = [&](int slot, int ct, int s) {
-    const double* p = K + lat_tile(min(i0 + min(s, ns - 1), ct), ct) * 512;
+    const double* p = s < ns && i0 + s <= ct ? K + lat_tile(i0 + s, ct) * 512 : g.zero;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      tr[slot][q] = p[q * 64];
-      ti[slot][q] = p[256 + q * 64];
+      tr[slot][q] = p[q * 64 + lane];
+      ti[slot][q] = p[256 + q * 64 + lane];
     }
   };
   int ct = i0 + c * g.cl + wave;
@@ -484,7 +492,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[s][t] = d4v{0, 0, 0, 0};
   double* const tu = turn[wave][0];
-  const double sign = l16 < 8 ? -1.0 : 1.0;
+  const double sign = l16 < 8 ? 1.0 : -1.0;
   for (; ct < c1; ct += 4) {
     const int next = ct + 4 < c1 ? ct + 4 : ct;
     double b1[NT][4], b2[NT][4];
@@ -514,40 +522,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
         load(sl ^ 1, ct, s + 1);
       else
         load(sl ^ 1, next, 0);
-      if (s < ns && i0 + s <= ct) {
-        const bool off = i0 + s < ct;
-        if (off) {
+      // turned: the buffer is the wave's own, whose LDS accesses run in order; the fences only hold the compiler
+      double ar[4], ai[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            tu[(4 * q + l4) * TS + l16] = tr[sl][q];
-            tu[16 * TS + (4 * q + l4) * TS + l16] = ti[sl][q];
-          }
+      for (int q = 0; q < 4; ++q) {
+        tu[(4 * q + l4) * TS + l16] = tr[sl][q];
+        tu[16 * TS + (4 * q + l4) * TS + l16] = ti[sl][q];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        ar[q] = tu[l16 * TS + 4 * q + l4];
+        ai[q] = tu[16 * TS + l16 * TS + 4 * q + l4];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(tr[sl][q], b1[j][q], acc[s][j], 0, 0, 0);
+          acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ti[sl][q], b2[j][q], acc[s][j], 0, 0, 0);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q) {
+        const double* d = dt + (s * 16 + 4 * q + l4) * N;
 #pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(tr[sl][q], b1[j][q], acc[s][j], 0, 0, 0);
-            acc[s][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ti[sl][q], b2[j][q], acc[s][j], 0, 0, 0);
-          }
-        if (off) {
-          // the wave's own buffer: its LDS accesses run in order, the fences only hold the compiler
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double ar = tu[l16 * TS + 4 * q + l4], ai = -tu[16 * TS + l16 * TS + 4 * q + l4];
-            const double* d = dt + (s * 16 + 4 * q + l4) * N;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-              at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, d[16 * j + l16], at[j], 0, 0, 0);
-              at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, sign * d[16 * j + (l16 ^ 8)], at[j], 0, 0, 0);
-            }
-          }
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int j = 0; j < NT; ++j) {
+          at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[q], d[16 * j + l16], at[j], 0, 0, 0);
+          at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[q], sign * d[16 * j + (l16 ^ 8)], at[j], 0, 0, 0);
         }
       }
     }
@@ -800,7 +806,7 @@ KxShape kx_shape(int nh, int S, int nb) {
 }
 
 bse_status kx_go(const LatKx& g, const KxShape& x, hipStream_t st) {
-  const dim3 grid((unsigned)(g.nh * x.blocks));
+  const dim3 grid((unsigned)(g.nh * x.blocks + 7) / 8 * 8);
   if (x.NT == 1 && x.RS == 16)
     hipLaunchKernelGGL((lat_kx<16, 1>), grid, dim3(256), 0, st, g);
   else if (x.NT == 1)
@@ -840,8 +846,12 @@ bse_status kernels_build(Plan* p, const std::vector<int2>& pair, hipStream_t st)
   L->S = kx_tiles(p);
   BSE_TRY(plan_alloc(p, (void**)&L->pair, sizeof(int2) * pair.size()));
   BSE_HIP(hipMemcpyAsync(L->pair, pair.data(), sizeof(int2) * pair.size(), hipMemcpyHostToDevice, st));
-  BSE_TRY(plan_alloc(p, (void**)&L->K, kx_bytes(p, L->nh)));
-  if (no2 % 16) BSE_TRY(zero_fill(L->K, kx_bytes(p, L->nh), st));
+  const size_t kb = kx_bytes(p, L->nh);
+  BSE_TRY(plan_alloc(p, (void**)&L->K, kb + 4096));
+  if (no2 % 16)
+    BSE_TRY(zero_fill(L->K, kb + 4096, st));
+  else
+    BSE_TRY(zero_fill((char*)L->K + kb, 4096, st));
   Tmp H, vp, rows;
   BSE_TRY(dmalloc(&H.p, 16 * (size_t)hp));
   std::vector<int2> list;  // (s, t) with t >= s, then all
@@ -1103,7 +1113,7 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
       for (int g0 = 0; g0 < w; g0 += 8) {
         const int n = std::min(8, w - g0);
         const KxShape x = kx_shape(L->nh, L->S, n);
-        LatKx g{no, w, g0, n, L->S, L->nh, x.RS, x.panels, x.cl, x.blocks, E, L->K, L->DR, L->pair, L->part, nullptr};
+        LatKx g{no, w, g0, n, L->S, L->nh, x.RS, x.panels, x.cl, x.blocks, E, L->K, L->K + kx_bytes(p, L->nh) / 8, L->DR, L->pair, L->part, nullptr};
         g.PT = L->part + (size_t)x.most * L->nh * L->S * 256 * x.NT;
         StageMark sm_(p, BSE_STAGE_DBLOCK, st);
         BSE_TRY(kx_go(g, x, st));
