@@ -474,16 +474,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
     return g.DR + 2 * g.E * (plus ? pr.x : max(pr.y, 0)) + (g.b0 + (plus ? v : v - g.nb)) * g.no;
   };
   const int nvec = pr.y >= 0 ? 2 * g.nb : g.nb;
-  for (int i = tid; i < RS * 16 * N; i += 256) {
-    const int n = i % N, e = i0 * 16 + i / N, v = (n >> 4) * 8 + (n & 7);
-    double x = 0.0;
-    if (e < no2 && v < nvec) {
-      int s1, s2;
-      const double* d = vec(v, &s1, &s2) + (n & 8 ? g.E : 0);
-      x = d[e / g.no * s1 + e % g.no * s2];
-      if ((n & 8) && v >= g.nb) x = -x;
+  {
+    const int n = tid % N, v = (n >> 4) * 8 + (n & 7);
+    int s1, s2;
+    const double* d = vec(min(v, nvec - 1), &s1, &s2) + (n & 8 ? g.E : 0);
+    const double f = (n & 8) && v >= g.nb ? -1.0 : 1.0;
+    double x[4];
+    static_assert(RS * N % 64 == 0, "four elements per thread at a time");
+    for (int i = 0; i < RS * 16 * N; i += 4 * 256) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = i0 * 16 + (i + k * 256 + tid) / N;
+        x[k] = d[e < no2 ? e / g.no * s1 + e % g.no * s2 : 0];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = i0 * 16 + (i + k * 256 + tid) / N;
+        dt[i + k * 256 + tid] = e < no2 && v < nvec ? f * x[k] : 0.0;
+      }
     }
-    dt[i] = x;
   }
   __syncthreads();
   d4v acc[RS][NT];
@@ -599,6 +608,7 @@ __global__ __launch_bounds__(256) void lat_kx_sum(LatKx g, int N, double* __rest
     const int e = minus ? b * g.no + a : a * g.no + b, panel = (e >> 4) / g.RS;
     const long long o = (h * rows + e) * N + blockIdx.z * 16 + n;
     const int nf = (g.S - panel * g.RS + g.cl - 1) / g.cl;
+#pragma unroll 4
     for (int i = 0; i < nf; ++i) s += g.PF[o + i * step];
 #pragma unroll 4
     for (int i = 0; i <= panel; ++i) s += g.PT[o + i * step];
@@ -728,7 +738,8 @@ __global__ __launch_bounds__(256) void lat_asym(int na, const int2* __restrict__
     const double s = __shfl_down(m, o);
     if (!(s <= m)) m = s;
   }
-  if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(m));
+  const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
+  if ((threadIdx.x & 63) == 0 && bits > *(volatile unsigned long long*)out) atomicMax(out, bits);
 }
 
 // planes of re and im
@@ -800,8 +811,8 @@ KxShape kx_shape(int nh, int S, int nb) {
   };
   x.cl = 4;
   count();
-  if ((long long)nh * x.blocks < 512) x.RS = 4;
-  for (x.cl = 512 / x.RS, count(); x.cl > 4 && (long long)nh * x.blocks < 1024; count()) x.cl /= 2;
+  if ((long long)nh * x.blocks < 2048) x.RS = 4;
+  for (x.cl = 512 / x.RS, count(); x.cl > 4 && (long long)nh * x.blocks < 768; count()) x.cl /= 2;
   return x;
 }
 
