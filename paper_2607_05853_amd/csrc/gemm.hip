@@ -499,6 +499,96 @@ __global__ __launch_bounds__(256) void cgemm_f32_dma64(GemmArgs g) {
   }
 }
 
+// The 64 x 16 tile of cgemm_real with direct-to-LDS operands (the FP32 direct block at n_v <= 4: n_c^2 x n_v^2 entries per
+// pair, K = N_aux): it reads A once and does 4 products per byte, so what bounds it is the memory, and the bytes in flight
+// decide: four 10 KiB stages (16 complex k of 64 rows of A and 16 of B, the chunk swizzle of the 64 x 64 tile), loads three
+// ahead, four blocks per CU.  The products and their order are those of cgemm_real (equal bits).
+template <typename TC>
+__global__ __launch_bounds__(256) void cgemm_f32_dma_n16(GemmArgs g) {
+  constexpr int BM = 64, BN = 16, BK = 16, NS = 4, PER = 3;  // PER: loads per wave and stage
+  constexpr int STAGE = (BM + BN) * BK * 2;                  // floats
+  __shared__ __attribute__((aligned(1024))) float smem[NS * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l4 = lane >> 4, l16 = lane & 15;
+  const int nK = g.K / BK, gyn = (g.M + BM - 1) / BM;
+  long long bl, t;
+  xcd_map(blockIdx.x, gyn, g.batch, bl, t);
+  const int b = (int)bl, m0 = (int)t * BM;
+  // DMA: 8-row blocks 2 wave and 2 wave + 1 of A, block wave % 2 of B (twice, with the same data, for equal counts);
+  // lane -> row lane / 8, stored chunk lane % 8, which holds source chunk (lane % 8) ^ ((row / 2) % 8); rows past the
+  // edge re-load a valid row (never stored)
+  const float* src[PER];
+  int ldo[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int rb = u < 2 ? 2 * wave + u : (wave & 1), r = 8 * rb + (lane >> 3);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    if (u < 2) {
+      const int row = m0 + r < g.M ? m0 + r : m0;
+      src[u] = (const float*)g.A + 2 * off_of(g.a_tab, g.a_tab_pb, g.a_sb, g.a_si, b, g.M, row) + 4 * c;
+      ldo[u] = 8 * rb * BK * 2;
+    } else {
+      const int col = r < g.N ? r : 0;
+      src[u] = (const float*)g.B + 2 * off_of(g.b_tab, g.b_tab_pb, g.b_sb, g.b_sj, b, g.N, col) + 4 * c;
+      ldo[u] = (BM + 8 * rb) * BK * 2;
+    }
+  }
+  auto issue = [&](int kt) {
+    if (kt >= nK) return;
+    float* st = smem + (kt % NS) * STAGE;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      __builtin_amdgcn_global_load_lds((const void*)(src[u] + 2 * BK * kt),
+                                       (__attribute__((address_space(3))) void*)(st + ldo[u]), 16, 0, 0);
+  };
+  // real k = 4 kk + l4 of a row of A; of B the component that a real or imaginary output column takes with it
+  const int comp = (l4 & 1) != (lane & 1) ? 1 : 0;
+  const float fa = (l4 & 1) && g.conjA ? -1.f : 1.f;
+  const float fb = ((l4 & 1) && !(lane & 1) ? -1.f : 1.f) * (comp && g.conjB ? -1.f : 1.f);
+  const int row = wave * 16 + l16;
+  f4v acc[2] = {f4v{0, 0, 0, 0}, f4v{0, 0, 0, 0}};
+#pragma unroll
+  for (int kt = 0; kt < NS - 1; ++kt) issue(kt);
+  for (int kt = 0; kt < nK; ++kt) {
+    // stage kt has landed (the loads of up to two later ones may be in flight) and every wave is done with stage
+    // kt - 1, whose slot the next issue overwrites
+    if (kt + 2 < nK)
+      vm_lds_barrier<2 * PER>();
+    else if (kt + 1 < nK)
+      vm_lds_barrier<PER>();
+    else
+      vm_lds_barrier<0>();
+    issue(kt + NS - 1);
+    const float* sa = smem + (kt % NS) * STAGE;
+    const float* sb = sa + BM * BK * 2;
+#pragma unroll
+    for (int kk = 0; kk < BK / 2; ++kk) {
+      const float a = fa * sa[row * BK * 2 + 4 * (kk ^ ((row >> 1) & 7)) + l4];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int col = j * 8 + (l16 >> 1);
+        const float bv = fb * sb[col * BK * 2 + 4 * (kk ^ ((col >> 1) & 7)) + (l4 & 2) + comp];
+        acc[j] = mma16(a, bv, acc[j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int m = m0 + wave * 16 + 4 * l4 + q;
+    if (m >= g.M) continue;
+    const long long ro = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, m);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = j * 8 + (l16 >> 1);
+      if (col >= g.N) continue;
+      TC* o = (TC*)g.C + 2 * (ro + (long long)col * g.c_sj) + (lane & 1);
+      double v = g.alpha * (double)acc[j][q];
+      if (g.beta) v += (double)*o;
+      *o = (TC)v;
+    }
+  }
+}
+
 // ----------------------------------------------------------------------------
 // BF16x3 kernel (c64 inputs, split into bf16 hi/lo when staged to LDS)
 // ----------------------------------------------------------------------------
@@ -2454,6 +2544,16 @@ bse_status run_real(const GemmArgs& g, hipStream_t st) {
         hipLaunchKernelGGL((cgemm_f32_dma64<0, 1, TC>), grid, block, 0, st, g);
       else
         hipLaunchKernelGGL((cgemm_f32_dma64<0, 0, TC>), grid, block, 0, st, g);
+      BSE_CHECK_LAUNCH();
+      return BSE_OK;
+    }
+  }
+  if constexpr (sizeof(T) == 4) {
+    // 16 columns or fewer and a K that fills the stages (8x8x8, n_c 8, n_v 4, N_aux 256: 7.8 -> 4.5 ms, 4.9 TB/s)
+    const long long tiles = (long long)((g.M + 63) / 64) * g.batch;
+    if (pick(g) == SH_NARROW_N && g.K % 16 == 0 && g.K >= 64 && dma_ok(g) && tiles < (1LL << 31) &&
+        wide_tiles_enabled()) {
+      hipLaunchKernelGGL(cgemm_f32_dma_n16<TC>, dim3((unsigned)tiles), dim3(256), 0, st, g);
       BSE_CHECK_LAUNCH();
       return BSE_OK;
     }
