@@ -234,28 +234,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 // ----------------------------------------------------------------------------
 // FP32, large tiles: interleaved c64 operands staged straight into LDS, 32x32x2 MFMA
 // ----------------------------------------------------------------------------
-// The wide tile (128 x 256 complex, eight waves of 64 x 64, three 48 KiB LDS stages of 16 complex k, the
-// ping-pong schedule of wide_tile_kloop) for FP32 plans, whose operands are interleaved complex64.  An LDS
-// row holds the 16 k of one operand row (128 bytes, eight 16-byte chunks of two complex values); chunk c of
-// row r is stored at c ^ ((r / 2) % 8), so the 16-byte fragment reads of 32 consecutive rows spread over
-// the banks.  A lane of half h (lane / 32) reads chunk 2 g + h for k group g (four complex k), i.e. k =
-// 4 g + 2 h + m for m = 0, 1 in its two complex values; one 32x32x2 product per (g, m) then sums the k of both
-// halves, the same split for A and B.  Each complex k step is four real products with FP32 accumulation:
+// Tiles of 64 x 128 complex, four waves of 32 x 64, two 24 KiB LDS stages of 16 complex k, three blocks per CU, for
+// FP32 plans, whose operands are interleaved complex64.  An LDS row holds the 16 k of one operand row (128 bytes, eight
+// 16-byte chunks of two complex values); chunk c of row r is stored at c ^ ((r / 2) % 8), so the 16-byte fragment reads
+// of 32 consecutive rows spread over the banks.  A lane of half h (lane / 32) reads chunk 2 g + h for k group g (four
+// complex k), i.e. k = 4 g + 2 h + m for m = 0, 1 in its two complex values; one 32x32x2 product per (g, m) then sums
+// the k of both halves, the same split for A and B.  Each complex k step is four real products with FP32 accumulation:
 //   Cr += Ar Br - Ai Bi,  Ci += Ar Bi + Ai Br   (conj A / conj B negate Ai / Bi).
-// 256 FP32 products per k step per wave (8192 matrix-core cycles), so the 48 KiB of operands per stage are
-// far from limiting.  The result is written from the registers (each row of 32 lanes is 256 contiguous bytes).
-constexpr int FW_BM = 128, FW_BN = 256, FW_BK = 16, FW_NS = 3;
+// 128 FP32 products per k step per wave (8192 matrix-core cycles) leave the operands far from limiting; what a product of
+// few k (the pair densities, K = N_ao) pays for is its start and its stores, which the other blocks of the CU hide: one
+// 128 x 256 tile per CU took 3.7 and 12.7 ms for the pair densities of the 8x8x8 workload (N_ao 64, N_aux 256, n_v 4,
+// n_c 8), these 3.0 and 10.6 (104 TFLOP/s; 115 without the stores); its W step (K = 256) 8.8 -> 8.5 (130).  The result
+// is written from the registers (each row of 32 lanes is 256 contiguous bytes).
+constexpr int FW_BM = 64, FW_BN = 128, FW_BK = 16, FW_NS = 2;
 constexpr int FW_STAGE = (FW_BM + FW_BN) * FW_BK * 2;  // floats per stage
-constexpr size_t FW_LDS = (size_t)FW_NS * FW_STAGE * sizeof(float);  // 144 KiB
 
 template <int CJA, int CJB, typename TC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void cgemm_f32_dma_w(GemmArgs g) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void cgemm_f32_dma_w(GemmArgs g) {
   constexpr int BM = FW_BM, BN = FW_BN, BK = FW_BK, NS = FW_NS, STAGE = FW_STAGE;
-  constexpr int RBLK = (BM + BN) / 8;  // 8-row DMA blocks per stage: 16 of A, 32 of B
-  extern __shared__ __attribute__((aligned(1024))) float smem_f[];
-  float* smem = smem_f;
+  constexpr int RBLK = (BM + BN) / 8;  // 8-row DMA blocks per stage: 8 of A, 16 of B
+  // one array: with two the compiler waits for the loads into the one before it reads the other
+  __shared__ __attribute__((aligned(1024))) float smem[NS * STAGE + 2 * BM];
+  // offsets of the result's rows: read one by one behind the products, a table's latency per row costs a quarter of a
+  // K of 64
+  long long* const crow = reinterpret_cast<long long*>(smem + NS * STAGE);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave >> 1, wn = wave & 1;
   const int h = lane >> 5, l32 = lane & 31;
   const int nK = g.K / BK;
   const int gxn = (g.N + BN - 1) / BN, gyn = (g.M + BM - 1) / BM;
@@ -265,13 +269,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int b = (int)bl;
   int m0, n0;
   tile_of(t, gxn, gyn, BM, BN, m0, n0);
-  // DMA: block rb (of 48) -> wave rb % 8; lane -> row 8 (rb') + lane / 8, stored chunk lane % 8, which holds
+  if (tid < BM && m0 + tid < g.M) crow[tid] = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, m0 + tid);
+  // DMA: block rb (of 24) -> wave rb % 4; lane -> row 8 (rb') + lane / 8, stored chunk lane % 8, which holds
   // source chunk (lane % 8) ^ ((row / 2) % 8); rows past the edge re-load a valid row (never stored)
-  const float* src[RBLK / 8];
-  int ldo[RBLK / 8];
+  const float* src[RBLK / 4];
+  int ldo[RBLK / 4];
 #pragma unroll
-  for (int u = 0; u < RBLK / 8; ++u) {
-    const int rb = wave + 8 * u;
+  for (int u = 0; u < RBLK / 4; ++u) {
+    const int rb = wave + 4 * u;
     const bool isA = rb < BM / 8;
     const int r = 8 * (isA ? rb : rb - BM / 8) + (lane >> 3);
     const int c = (lane & 7) ^ ((r >> 1) & 7);
@@ -289,33 +294,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kt >= nK) return;
     float* st = smem + (kt % NS) * STAGE;
 #pragma unroll
-    for (int u = 0; u < RBLK / 8; ++u)
+    for (int u = 0; u < RBLK / 4; ++u)
       __builtin_amdgcn_global_load_lds((const void*)(src[u] + 2 * BK * kt),
                                        (__attribute__((address_space(3))) void*)(st + ldo[u]), 16, 0, 0);
   };
-  f16v accR[2][2], accI[2][2];
+  f16v accR[2], accI[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        accR[i][j][r] = 0.f;
-        accI[i][j][r] = 0.f;
-      }
+    for (int r = 0; r < 16; ++r) {
+      accR[j][r] = 0.f;
+      accI[j][r] = 0.f;
+    }
   issue(0);
-  issue(1);
-  f4v a[2][4], bb[2][4];
+  f4v a[4], bb[2][4];
   auto frags = [&](int kt) {
     const float* sa = smem + (kt % NS) * STAGE;
     const float* sb = sa + BM * BK * 2;
+    const int row = wm * 32 + l32;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = wm * 64 + i * 32 + l32;
-#pragma unroll
-      for (int gk = 0; gk < 4; ++gk)
-        a[i][gk] = *reinterpret_cast<const f4v*>(sa + row * BK * 2 + 4 * ((2 * gk + h) ^ ((row >> 1) & 7)));
-    }
+    for (int gk = 0; gk < 4; ++gk)
+      a[gk] = *reinterpret_cast<const f4v*>(sa + row * BK * 2 + 4 * ((2 * gk + h) ^ ((row >> 1) & 7)));
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = wn * 64 + j * 32 + l32;
@@ -330,65 +329,49 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const float ar = a[i][gk][2 * m];
-          const float ai = CJA ? -a[i][gk][2 * m + 1] : a[i][gk][2 * m + 1];
+        for (int f = 0; f < 4; ++f)  // Ar Br, Ar Bi, -Ai Bi, Ai Br: no product waits for the one before
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            const float br = bb[j][gk][2 * m];
+            const float ar = a[gk][2 * m], br = bb[j][gk][2 * m];
+            const float ai = CJA ? -a[gk][2 * m + 1] : a[gk][2 * m + 1];
             const float bi = CJB ? -bb[j][gk][2 * m + 1] : bb[j][gk][2 * m + 1];
-            accR[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, br, accR[i][j], 0, 0, 0);
-            accR[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(-ai, bi, accR[i][j], 0, 0, 0);
-            accI[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, bi, accI[i][j], 0, 0, 0);
-            accI[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, br, accI[i][j], 0, 0, 0);
+            f16v& acc = f == 0 || f == 2 ? accR[j] : accI[j];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f < 2 ? ar : f == 2 ? -ai : ai, f == 0 || f == 3 ? br : bi, acc, 0,
+                                                       0, 0);
           }
-        }
   };
-  // ping-pong as in wide_tile_kloop (six loads per wave per stage)
-  auto bar = [&](int n) {
-    if (n >= 2)
-      vm_lds_barrier<12>();
-    else if (n == 1)
-      vm_lds_barrier<6>();
-    else
-      vm_lds_barrier<0>();
-  };
-  auto last = [&](int kt) { return kt < nK - 1 ? kt : nK - 1; };
-  const bool late = wave >= 4;
-  if (late) bar(last(1) - 0);
   for (int kt = 0; kt < nK; ++kt) {
-    bar(last(kt + 1) - kt);
-    issue(kt + 2);
+    vm_lds_barrier<0>();  // stage kt has landed, and every wave has read stage kt - 1, whose slot is filled next
+    issue(kt + 1);
     frags(kt);
-    if (late)
-      bar(last(kt + 2) - (kt + 1));
-    else
-      bar(last(kt + 2) - kt);
     mma();
   }
-  if (!late) bar(0);
   // result: register r of a 32 x 32 tile holds row 8 (r / 4) + 4 h + r % 4, column l32
+  const bool plain = g.alpha == 1.0 && !g.beta;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int r = 0; r < 16; ++r) {
+    const int lr = wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+    if (m0 + lr >= g.M) continue;
+    const long long ro = crow[lr];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (row >= g.M) continue;
-      const long long ro = off_of(g.c_tab, g.c_tab_pb, g.c_sb, g.c_si, b, g.M, row);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 64 + j * 32 + l32;
-        if (col >= g.N) continue;
-        TC* o = (TC*)g.C + 2 * (ro + (long long)col * g.c_sj);
-        double vr = g.alpha * (double)accR[i][j][r], vi = g.alpha * (double)accI[i][j][r];
-        if (g.beta) {
-          vr += (double)o[0];
-          vi += (double)o[1];
-        }
-        o[0] = (TC)vr;
-        o[1] = (TC)vi;
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + wn * 64 + j * 32 + l32;
+      if (col >= g.N) continue;
+      TC* o = (TC*)g.C + 2 * (ro + (long long)col * g.c_sj);
+      if (plain) {
+        o[0] = (TC)accR[j][r];
+        o[1] = (TC)accI[j][r];
+        continue;
       }
+      double vr = g.alpha * (double)accR[j][r], vi = g.alpha * (double)accI[j][r];
+      if (g.beta) {
+        vr += (double)o[0];
+        vi += (double)o[1];
+      }
+      o[0] = (TC)vr;
+      o[1] = (TC)vi;
     }
+  }
 }
 
 // The same products on 64 x 64 tiles for small per-pair matrices (the FP32 direct block T = M_c P^T has
@@ -2509,17 +2492,17 @@ bool wide_tiles_enabled();
 template <typename TC>
 bse_status launch_f32_wide(const GemmArgs& g, hipStream_t st) {
   const long long tiles = (long long)((g.N + FW_BN - 1) / FW_BN) * ((g.M + FW_BM - 1) / FW_BM) * g.batch;
-  const dim3 grid((unsigned)tiles), block(512);
-  auto go = [&](auto kern) -> bse_status {
-    BSE_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FW_LDS));
-    hipLaunchKernelGGL(kern, grid, block, FW_LDS, st, g);
-    BSE_CHECK_LAUNCH();
-    return BSE_OK;
-  };
-  if (g.conjA && g.conjB) return go(cgemm_f32_dma_w<1, 1, TC>);
-  if (g.conjA) return go(cgemm_f32_dma_w<1, 0, TC>);
-  if (g.conjB) return go(cgemm_f32_dma_w<0, 1, TC>);
-  return go(cgemm_f32_dma_w<0, 0, TC>);
+  const dim3 grid((unsigned)tiles), block(256);
+  if (g.conjA && g.conjB)
+    hipLaunchKernelGGL((cgemm_f32_dma_w<1, 1, TC>), grid, block, 0, st, g);
+  else if (g.conjA)
+    hipLaunchKernelGGL((cgemm_f32_dma_w<1, 0, TC>), grid, block, 0, st, g);
+  else if (g.conjB)
+    hipLaunchKernelGGL((cgemm_f32_dma_w<0, 1, TC>), grid, block, 0, st, g);
+  else
+    hipLaunchKernelGGL((cgemm_f32_dma_w<0, 0, TC>), grid, block, 0, st, g);
+  BSE_CHECK_LAUNCH();
+  return BSE_OK;
 }
 
 template <typename T, typename TC>
@@ -2528,7 +2511,7 @@ bse_status run_real(const GemmArgs& g, hipStream_t st) {
   if constexpr (sizeof(T) == 4) {
     // FP32 products with enough rows and columns for the wide tile (direct-to-LDS operands)
     const long long tiles = (long long)((g.N + FW_BN - 1) / FW_BN) * ((g.M + FW_BM - 1) / FW_BM) * g.batch;
-    if (g.M >= FW_BM && g.N >= FW_BN && g.K % FW_BK == 0 && dma_ok(g) && tiles < (1LL << 31) &&
+    if (g.M >= 128 && g.N >= 256 && g.K % FW_BK == 0 && dma_ok(g) && tiles < (1LL << 31) &&
         wide_tiles_enabled())
       return launch_f32_wide<TC>(g, st);
     // small per-pair products with a long K (the direct block): 64 x 64 tiles, one per batch entry, where
