@@ -5,7 +5,7 @@
 // 7 x 7 x 7.  One axis is summed after the other, so an 8x8x8 grid on a 5x5x5 box takes 10 complex products
 // per output instead of 125 and the sums are bound by reading the input and writing the output once.
 // At 8x8x8 on 5x5x5 with N_aux = 256 (668 MB in and out, 0.14 ms at the 4.4-5.1 TB/s of a large copy) the
-// spread takes 0.175 ms and the gather 0.233 ms; the phase table and FP64 GEMM took 0.86 and 0.88 ms.  Nothing
+// spread takes 0.145-0.175 ms and the gather 0.188 ms (0.233 with the loads of a step only); the phase table and FP64 GEMM took 0.86 and 0.88 ms.  Nothing
 // is copied from the host or allocated: a 4x4x4 interpolation at N_aux = 64 takes 12 us against 43.
 #include "bse_internal.h"
 #include "fourier.h"
@@ -237,9 +237,10 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
 }
 
 // Gather.  A thread owns one e (te per block, rows of 16 te bytes) and one q1 of a round of 256 / te: it reads
-// each input once and sums the last two axes into D[R2][R3] in registers, two q2 at a time (16 loads in flight,
-// each phase read serves two).  The R1 axis is then summed over the round's q1 through LDS, one R2 at a time;
-// rounds after the first add to the outputs the same thread wrote before.
+// each input once and sums the last two axes into D[R2][R3] in registers, two q2 and four q3 at a time (each phase
+// read serves two products, the next step's eight loads are in flight).  The R1 axis is then summed over the round's
+// q1 through LDS, one R2 at a time, with the first loads of the block's next round or tile in flight; rounds after the
+// first add to the outputs the same thread wrote before.
 // Output: c128 rows of E, or re and im planes of E each ([R][2][E]) when planar.
 template <int NS>
 __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, const double* __restrict__ in,
@@ -252,34 +253,56 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
   double2* const p1 = X + nq * NS * te;
   double2* const p2 = p1 + n1 * FT_MAXR;
   double2* const p3 = p2 + n2 * NS;
+  long long e = (long long)blockIdx.x * te + el;  // of the tile in hand, which starts at e - el < E
+  int i0 = 0;
+  const int nk = (n3 + 3) / 4, steps = (n2 + 1) / 2 * nk;
+  const double2* g;
+  bool on;  // the thread has a column in this round
+  auto place = [&](long long e, int i0) {
+    on = i0 + ql < n1 && e < E;
+    g = reinterpret_cast<const double2*>(in) + (long long)(on ? i0 + ql : 0) * n2 * n3 * E + (on ? e : 0);
+  };
+  double2 u[2][4], v[2][4];
+  auto load = [&](int o, int s) {
+    const int j = 2 * (s / nk), k0 = 4 * (s % nk);
+    const double2* ga = g + (long long)j * n3 * E;
+    const double2* gb = j + 1 < n2 ? ga + (long long)n3 * E : ga;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const long long at = (long long)min(k0 + k, n3 - 1) * E;
+      u[o][k] = ga[at];
+      v[o][k] = gb[at];
+    }
+  };
+  place(e, i0);
+  if (on) load(0, 0);
   ft_phases<NS>(a, sign, tab, p1, p2, p3);
-  const long long e = (long long)blockIdx.x * te + el;
-  for (int i0 = 0; i0 < n1; i0 += nq) {
-    const int i1 = i0 + ql;
+  while (e - el < E) {
     Z D[NS][NS];
 #pragma unroll
     for (int y = 0; y < NS; ++y)
 #pragma unroll
       for (int z = 0; z < NS; ++z) D[y][z] = Z{0.0, 0.0};
-    if (i1 < n1 && e < E) {
-      const double2* g = reinterpret_cast<const double2*>(in) + (long long)i1 * n2 * n3 * E + e;
-      for (int j = 0; j < n2; j += 2) {
-        const bool two = j + 1 < n2;
-        Z C0[NS], C1[NS];
+    if (on) {
+      Z C0[NS], C1[NS];
+      auto step = [&](int o, int s) {
+        const int j = 2 * (s / nk), k0 = 4 * (s % nk);
+        if (k0 == 0) {
 #pragma unroll
-        for (int z = 0; z < NS; ++z) C0[z] = C1[z] = Z{0.0, 0.0};
-        const double2* ga = g + (long long)j * n3 * E;
-        const double2* gb = two ? ga + (long long)n3 * E : ga;
-#pragma unroll 8
-        for (int k = 0; k < n3; ++k) {
-          const double2 u = ga[(long long)k * E], v = gb[(long long)k * E];
+          for (int z = 0; z < NS; ++z) C0[z] = C1[z] = Z{0.0, 0.0};
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (k0 + k >= n3) break;
 #pragma unroll
           for (int z = 0; z < NS; ++z) {
-            const double2 p = p3[k * NS + z];
-            fma_z(C0[z], p, Z{u.x, u.y});
-            fma_z(C1[z], p, Z{v.x, v.y});
+            const double2 p = p3[(k0 + k) * NS + z];
+            fma_z(C0[z], p, Z{u[o][k].x, u[o][k].y});
+            fma_z(C1[z], p, Z{v[o][k].x, v[o][k].y});
           }
         }
+        if (k0 + 4 < n3) return;
+        const bool two = j + 1 < n2;
         if (!two) {
 #pragma unroll
           for (int z = 0; z < NS; ++z) C1[z] = Z{0.0, 0.0};
@@ -293,8 +316,19 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
             fma_z(D[y][z], pb, C1[z]);
           }
         }
+      };
+      for (int s = 0; s < steps; s += 2) {
+        load(1, min(s + 1, steps - 1));
+        step(0, s);
+        if (s + 1 >= steps) break;
+        if (s + 2 < steps) load(0, s + 2);
+        step(1, s + 1);
       }
     }
+    const bool same = i0 + nq < n1;
+    const long long e2 = same ? e : e + (long long)gridDim.x * te;
+    place(e2, same ? i0 + nq : 0);
+    if (on) load(0, 0);
     const int live = min(nq, n1 - i0);
 #pragma unroll
     for (int y = 0; y < NS; ++y) {
@@ -320,6 +354,8 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
         *im = i0 ? *im + w * s.y : w * s.y;
       }
     }
+    e = e2;
+    i0 = same ? i0 + nq : 0;
   }
 }
 
@@ -378,7 +414,8 @@ bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long
   const int te = E >= 32 * 512 ? 32 : 16;
   const int bs = 256;
   const size_t lds = 16 * ((size_t)(bs / te) * ns * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ns);
-  const dim3 grid((unsigned)((E + te - 1) / te)), block(bs);
+  // two blocks per CU (their registers allow no more), each over its share of the tiles
+  const dim3 grid((unsigned)std::min<long long>(512, (E + te - 1) / te)), block(bs);
   if (ns <= 3)
     hipLaunchKernelGGL(ft_gather<3>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
   else if (ns <= 5)
