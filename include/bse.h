@@ -238,7 +238,10 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
  * W(R) from W_q and checks that at most 256 R with components up to 3 give it back to 1e-14 (a
  * W_q interpolated from a coarse mesh of up to 7 points per axis); the sum over k'
  * then separates and its work grows with n_R nb instead of N_k^2.  Taken where
- * that needs less work; 0 otherwise.  Host pointer. */
+ * that needs less work; 0 otherwise.  Host pointer.  With W_q Hermitian such a
+ * plan keeps one n_ao^2 x n_ao^2 kernel per pair (R, -R), half of it stored
+ * (8 n_ao^4 bytes), where these take at most 16 GiB, a fifth of the free memory
+ * and BSE_WORKSPACE_GB, and less time than contracting C^mu and W(R) anew. */
 bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R);
 
 /* Device bytes held by the plan (copies, halves and workspaces). */

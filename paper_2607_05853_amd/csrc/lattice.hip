@@ -11,10 +11,14 @@
 //   Y(k)_cv    = (E_c - E_v) X - (1/N_k) sum_ss' conj(psi_c(k)_s') psi_v(k)_s F(k)_ss'
 // Its work grows with N_R n_b instead of N_k^2.  The exchange term is a change of V at R = 0,
 //   t^nu = sum_tt' C^nu_tt' D(0)_tt' = sum_t U^nu_tt(0),   V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu.
-// All three contractions are FP64 matrix-core GEMMs on planar (re, im) operands.  One application, pair route ->
-// this one: 8x8x8, N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors 83.7 -> 38.3 ms (2.15 TFLOP of matrix work at
-// 56 TFLOP/s in the three GEMMs; a large FP64 library product reaches 72 on this card); 5x6x7, N_ao 30, N_aux 90,
-// 27 R, 5 vectors 2.19 -> 0.39 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors 0.305 -> 0.086 ms (nine launches).
+// Where they fit, the plan keeps the kernels
+//   K(R)_ss',tt' = sum_munu C^mu_ts W(R)_munu C^nu_s't',   F(R) = K(R) D(R)
+// instead (exchange in K(0)): 16 N_ao^4 bytes per R, of which Hermiticity and W(-R) = W(R)^T leave a quarter, read
+// once per eight vectors, in place of (16 N_aux N_ao^3 + 4 N_aux^2 N_ao^2) n_b operations per R.  One application,
+// pair route -> three contractions -> kernels: 8x8x8, N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors (8.5 GB of
+// kernels, 26 ms to make) 83.7 -> 38.2 -> 3.7 ms; 5x6x7, N_ao 30, N_aux 90, 27 R, 5 vectors (95 MB) 2.19 -> 0.33 ->
+// 0.113 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors (8 MB) 0.305 -> 0.073 -> 0.036 ms.  The contractions remain for
+// kernels beyond 16 GiB or a fifth of the free memory, W_q that are not Hermitian, and where they are less work.
 #include "bse_internal.h"
 #include "fourier.h"
 #include "mfma_common.h"
@@ -437,7 +441,9 @@ struct LatKx {
 // turned in LDS, with the rows' vectors (in LDS); the sums of its rows stay in registers over all its column tiles,
 // those of its columns over its row tiles.  Eight vectors fill the 16 columns of the FP64 instruction with real and
 // imaginary parts, so a tile of 4 KiB is 16 NT instructions of 64 cycles: a CU that runs them back to back takes
-// 16 / NT bytes per cycle, where its share of the memory's rate is 8 to 9.
+// 16 / NT bytes per cycle, where its share of the memory's rate is 8 to 9.  8x8x8 workload, 8 vectors (NT = 2): 8.5 GB
+// of kernels, 1.3 GB of sums and 0.135 TFLOP in 3.1 ms; matrix cores busy 60 % of it, the rest being the turn through
+// LDS, the columns' vectors and the block's start and end (1.1 ms with all loads from a cache).
 template <int RS, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_kx(LatKx g) {
   constexpr int N = 16 * NT, TS = 18;
