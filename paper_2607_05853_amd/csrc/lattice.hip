@@ -4,21 +4,23 @@
 // sum over k' of the direct term separates:
 //   D(k)_tt'   = sum_v'c' conj(psi_v'(k)_t) psi_c'(k)_t' X(k)_c'v'
 //   D(R)       = sum_k exp(2 pi i k.R) D(k)
+//   G^nu_ts    = sum_mu C^mu_ts W(R)_munu           per R, real W
 //   U^nu_ts'   = sum_t' C^nu_s't' D(R)_tt'          per R
-//   V^mu_ts'   = sum_nu W(R)_munu U^nu_ts'          per R, real W
-//   F(R)_ss'   = sum_mu,t C^mu_ts V^mu_ts'          per R
+//   F(R)_ss'   = sum_nu,t G^nu_ts U^nu_ts'          per R
 //   F(k)       = sum_R exp(-2 pi i k.R) F(R)
 //   Y(k)_cv    = (E_c - E_v) X - (1/N_k) sum_ss' conj(psi_c(k)_s') psi_v(k)_s F(k)_ss'
-// Its work grows with N_R n_b instead of N_k^2.  The exchange term is a change of V at R = 0,
-//   t^nu = sum_tt' C^nu_tt' D(0)_tt' = sum_t U^nu_tt(0),   V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu.
+// Its work grows with N_R n_b instead of N_k^2.  The exchange term is a change of F at R = 0,
+//   t^nu = sum_tt' C^nu_tt' D(0)_tt' = sum_t U^nu_tt(0),   F(0)_ss' -= alpha sum_munu C^mu_s's Vbar_munu t^nu.
 // Where they fit, the plan keeps the kernels
 //   K(R)_ss',tt' = sum_munu C^mu_ts W(R)_munu C^nu_s't',   F(R) = K(R) D(R)
 // instead (exchange in K(0)): 16 N_ao^4 bytes per R, of which Hermiticity and W(-R) = W(R)^T leave a quarter, read
-// once per eight vectors, in place of (16 N_aux N_ao^3 + 4 N_aux^2 N_ao^2) n_b operations per R.  One application,
-// pair route -> three contractions -> kernels: 8x8x8, N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors (8.5 GB of
-// kernels, 26 ms to make) 83.7 -> 38.2 -> 3.7 ms; 5x6x7, N_ao 30, N_aux 90, 27 R, 5 vectors (95 MB) 2.19 -> 0.33 ->
-// 0.113 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors (8 MB) 0.305 -> 0.073 -> 0.036 ms.  The contractions remain for
-// kernels beyond 16 GiB or a fifth of the free memory, W_q that are not Hermitian, and where they are less work.
+// once per eight vectors, in place of 16 N_aux N_ao^3 n_b + 4 N_aux^2 N_ao^2 operations per R.  One application,
+// pair route -> contractions -> kernels: 8x8x8, N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors (8.5 GB of
+// kernels, 26 ms to make) 83.7 -> 23.3 -> 3.6 ms; N_ao 96, 4 vectors (no room for kernels) 102 -> 46 ms; 5x6x7, N_ao 30,
+// N_aux 90, 27 R, 5 vectors (95 MB) 2.19 -> 0.111 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors (8 MB) 0.305 -> 0.034 ms.
+// W(R) is contracted with C^mu again in every application (G, one vector's worth of work in a batched product) as G of
+// all R takes as much memory as U.  The contractions remain for kernels beyond 16 GiB or a fifth of the free memory, W_q
+// that are not Hermitian, and where they are less work.
 #include "bse_internal.h"
 #include "fourier.h"
 #include "mfma_common.h"
@@ -33,7 +35,7 @@ namespace bse {
 struct Lattice {
   FtArgs ax;                 // the active R on the dense mesh, unit weights
   int nR = 0, r0 = 0;        // r0: index of R = 0
-  double* Wr = nullptr;      // [nR][n_aux][n_aux]
+  double* Wr = nullptr;      // [nR][n_aux][n_aux], with kernels W(R), else W(R)^T
   // constants with padded rows: n_aux n_ao doubles is often a power of two, whose rows all start in one L2 channel
   long long ldc = 0;
   double* C1 = nullptr;      // [2][t'][ldc]: (nu, s') = C^nu_s't'
@@ -42,7 +44,7 @@ struct Lattice {
   double* D = nullptr;       // c128 [Nk][n_ao][nbc][n_ao], later F(k) as [Nk][nbc][n_ao][n_ao]
   double* DR = nullptr;      // [nR][2][n_ao][nbc][n_ao]
   double* U = nullptr;       // [rc][n_ao][nbc][2][n_aux][n_ao]
-  double* V = nullptr;       // same
+  double* G = nullptr;       // [rc][2][s][ldc]: (nu, t) = G^nu_ts
   double* F = nullptr;       // [split][nR][nbc][2][n_ao][n_ao]
   long long f_doubles = 0;
   double* t = nullptr;       // c128 [n_aux][nbc]
@@ -442,7 +444,7 @@ struct LatKx {
 // those of its columns over its row tiles.  Eight vectors fill the 16 columns of the FP64 instruction with real and
 // imaginary parts, so a tile of 4 KiB is 16 NT instructions of 64 cycles: a CU that runs them back to back takes
 // 16 / NT bytes per cycle, where its share of the memory's rate is 8 to 9.  8x8x8 workload, 8 vectors (NT = 2): 8.5 GB
-// of kernels, 1.3 GB of sums and 0.135 TFLOP in 3.1 ms; matrix cores busy 60 % of it, the rest being the turn through
+// of kernels, 1.3 GB of sums and 0.135 TFLOP in 3.1 ms; matrix cores busy 66 % of it, the rest being the turn through
 // LDS, the columns' vectors and the block's start and end (1.1 ms with all loads from a cache).
 template <int RS, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lat_kx(LatKx g) {
@@ -654,44 +656,41 @@ __global__ __launch_bounds__(64) void lat_ex_t(int na, int no, int nbc, const do
   }
 }
 
-// V^mu_tt(0) -= alpha sum_nu Vbar_munu t^nu; block (mu, b).  DIRECT: t summed here from U (small n_aux n_ao, one
-// launch less), the waves sharing the diagonal
-template <bool DIRECT>
-__global__ __launch_bounds__(256) void lat_ex_v(int na, int no, int nbc, double alpha, const double* __restrict__ vbar,
-                                                const double* __restrict__ U0, const double* __restrict__ t,
-                                                double* __restrict__ V0) {
-  __shared__ double2 red[4];
-  const int mu = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long pl = (long long)na * no;
+// u^mu = alpha sum_nu Vbar_munu t^nu, block (mu, b) of one wave
+__global__ __launch_bounds__(64) void lat_ex_u(int na, int nbc, double alpha, const double* __restrict__ vbar,
+                                               const double* __restrict__ t, double* __restrict__ u) {
+  const int mu = blockIdx.x, b = blockIdx.y;
   double2 s = {0.0, 0.0};
-  if constexpr (DIRECT) {
-    for (int nu = lane; nu < na; nu += 64) {
-      const double* v = vbar + 2 * ((long long)mu * na + nu);
-      double2 x = {0.0, 0.0};
-#pragma unroll 4
-      for (int a = wave; a < no; a += 4) {
-        const double* u = U0 + ((long long)a * nbc + b) * 2 * pl + (long long)nu * no + a;
-        x.x += u[0];
-        x.y += u[pl];
-      }
-      s = cmadd(s, double2{v[0], v[1]}, x);
-    }
-  } else {
-    for (int nu = threadIdx.x; nu < na; nu += 256) {
-      const double* v = vbar + 2 * ((long long)mu * na + nu);
-      s = cmadd(s, double2{v[0], v[1]}, double2{t[2 * (nu * nbc + b)], t[2 * (nu * nbc + b) + 1]});
-    }
+  for (int nu = threadIdx.x; nu < na; nu += 64) {
+    const double* v = vbar + 2 * ((long long)mu * na + nu);
+    s = cmadd(s, double2{v[0], v[1]}, double2{t[2 * (nu * nbc + b)], t[2 * (nu * nbc + b) + 1]});
   }
   wave_sum(s);
-  if (lane == 0) red[wave] = s;
-  __syncthreads();
-  s.x = red[0].x + red[1].x + red[2].x + red[3].x;
-  s.y = red[0].y + red[1].y + red[2].y + red[3].y;
-  for (int a = threadIdx.x; a < no; a += 256) {
-    double* v = V0 + ((long long)a * nbc + b) * 2 * pl + (long long)mu * no + a;
-    v[0] -= alpha * s.x;
-    v[pl] -= alpha * s.y;
+  if (threadIdx.x == 0) {
+    u[2 * (b * na + mu)] = alpha * s.x;
+    u[2 * (b * na + mu) + 1] = alpha * s.y;
   }
+}
+
+// F(0)_ss' -= sum_mu C^mu_s's u^mu, block (64 s', s, b): four waves share the mu
+__global__ __launch_bounds__(256) void lat_ex_f(int na, int no, long long ldc, const double* __restrict__ C1,
+                                                const double* __restrict__ u, double* __restrict__ F0) {
+  __shared__ double2 red[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = blockIdx.y, b = blockIdx.z;
+  const int sp = blockIdx.x * 64 + lane;
+  double2 x = {0.0, 0.0};
+  if (sp < no) {
+    const double* c = C1 + s * ldc + sp;
+    for (int mu = wave; mu < na; mu += 4)
+      x = cmadd(x, double2{c[(long long)mu * no], c[no * ldc + (long long)mu * no]},
+                double2{u[2 * (b * na + mu)], u[2 * (b * na + mu) + 1]});
+  }
+  red[wave][lane] = x;
+  __syncthreads();
+  if (wave || sp >= no) return;
+  double* f = F0 + ((long long)b * 2 * no + s) * no + sp;
+  f[0] -= red[0][lane].x + red[1][lane].x + red[2][lane].x + red[3][lane].x;
+  f[(long long)no * no] -= red[0][lane].y + red[1][lane].y + red[2][lane].y + red[3][lane].y;
 }
 
 // ----------------------------------------------------------------------------
@@ -748,6 +747,20 @@ __global__ __launch_bounds__(256) void lat_asym(int na, const int2* __restrict__
   if ((threadIdx.x & 63) == 0 && bits > *(volatile unsigned long long*)out) atomicMax(out, bits);
 }
 
+// each [na][na] matrix transposed in place, a pair of 16 x 16 tiles per block
+__global__ __launch_bounds__(256) void lat_transpose(int na, double* __restrict__ W) {
+  if (blockIdx.x > blockIdx.y) return;
+  __shared__ double x[16][17], y[16][17];
+  double* w = W + (long long)blockIdx.z * na * na;
+  const int a = threadIdx.x >> 4, b = threadIdx.x & 15, i = blockIdx.x * 16, j = blockIdx.y * 16;
+  const bool u = i + a < na && j + b < na, l = j + a < na && i + b < na;
+  if (u) x[a][b] = w[(long long)(i + a) * na + j + b];
+  if (l) y[a][b] = w[(long long)(j + a) * na + i + b];
+  __syncthreads();
+  if (u) w[(long long)(i + a) * na + j + b] = y[b][a];
+  if (l) w[(long long)(j + a) * na + i + b] = x[b][a];
+}
+
 // planes of re and im
 __global__ void lat_planes(long long n, const double* __restrict__ A, double* __restrict__ P) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
@@ -780,7 +793,7 @@ struct Tmp {
   ~Tmp() { dfree(p); }
 };
 
-// seconds of the matrix work of one application over pairs of k, over nR lattice vectors in three contractions, and over
+// seconds of the matrix work of one application over pairs of k, over nR lattice vectors by contractions, and over
 // kernels K(R); the rates are those of the 8x8x8 workload (N_ao 64, N_aux 256, n_v 4, n_c 8, 125 R, 8 vectors), whose
 // pair route has GEMMs of a few rows per pair
 double secs_pairs(const Plan* p) {
@@ -789,7 +802,7 @@ double secs_pairs(const Plan* p) {
 }
 double secs_gemm(const Plan* p, int nR, int nb) {
   const double na = p->d.n_aux, no = p->d.n_ao;
-  return (double)nb * nR * (16.0 * na * no * no * no + 4.0 * na * na * no * no) / 56e12;
+  return nR * (nb * 16.0 * na * no * no * no + 4.0 * na * na * no * no) / 56e12;
 }
 int kx_tiles(const Plan* p) { return (p->d.n_ao * p->d.n_ao + 15) / 16; }
 size_t kx_bytes(const Plan* p, int nh) { return (size_t)kx_tiles(p) * (kx_tiles(p) + 1) / 2 * 4096 * nh; }
@@ -1091,14 +1104,16 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
     BSE_TRY(plan_alloc(p, (void**)&L->F, 16 * no2 * nbc * (size_t)nR));
     return kernels_build(p, pair, st);
   }
-  const size_t per_r = 32 * (size_t)nc1 * nbc;
-  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / per_r));
+  const size_t u_r = 16 * (size_t)nc1 * nbc, g_r = 16 * (size_t)(no * L->ldc);
+  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / (u_r + g_r)));
   const size_t f1 = 2 * no2 * nbc * (size_t)nR;
   L->f_doubles = (long long)(f1 * (f1 > ((size_t)1 << 22) ? 8 : 32));
-  BSE_TRY(plan_alloc(p, (void**)&L->U, per_r / 2 * L->rc));
-  BSE_TRY(plan_alloc(p, (void**)&L->V, per_r / 2 * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->U, u_r * L->rc));
+  BSE_TRY(plan_alloc(p, (void**)&L->G, g_r * L->rc));
   BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
-  BSE_TRY(plan_alloc(p, (void**)&L->t, 16 * (size_t)na * nbc));
+  BSE_TRY(plan_alloc(p, (void**)&L->t, 32 * (size_t)na * nbc));
+  hipLaunchKernelGGL(lat_transpose, dim3((na + 15) / 16, (na + 15) / 16, nR), dim3(256), 0, st, na, L->Wr);
+  BSE_CHECK_LAUNCH();
   return BSE_OK;
 }
 
@@ -1142,7 +1157,7 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
       BSE_TRY(project(1));
       continue;
     }
-    // split of the last contraction's (t, mu) sum: enough parts for 1024 blocks of its tiles, at least 64 deep
+    // split of the last contraction's (nu, t) sum: enough parts for 1024 blocks of its tiles, at least 64 deep
     const int rc = std::min(L->rc, nR);
     const long long t3 = (long long)((no + 63) / 64) * ((no * w + 127) / 128) * rc;
     const long long cap = std::min<long long>(L->f_doubles / (2 * E * nR), std::max<long long>(1, (long long)no * na / 64));
@@ -1177,38 +1192,24 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
       {
         StageMark sm_(p, BSE_STAGE_WSTEP, st);
         g.M = na;
-        g.N = 2 * no * w * no;
+        g.N = 2 * (int)no2;
         g.K = na;
         g.Z = n;
         g.A = L->Wr + (long long)r * na * na;
         g.lda = na;
         g.a_z = (long long)na * na;
-        g.B = L->U;
+        g.B = L->C1;
         g.kd = na;
         g.rs0 = no;
         g.nd = no;
-        g.cs1 = nu;
-        g.b_z = 2 * nu * no * w;
-        g.C = L->V;
+        g.cs1 = L->ldc;
+        g.C = L->G;
         g.ldc = no;
-        g.cc1 = nu;
-        g.c_z = 2 * nu * no * w;
+        g.cc1 = L->ldc;
+        g.c_z = 2 * no * L->ldc;
         g.nsplit = 1;
         g.klen = na;
         BSE_TRY(lat_gemm_run<false>(g, st));
-      }
-      if (d.alpha != 0.0 && r <= L->r0 && L->r0 < r + n) {
-        StageMark sm_(p, BSE_STAGE_EXCHANGE, st);
-        const long long o = 2 * nu * no * w * (L->r0 - r);
-        if (nu <= 2048) {
-          hipLaunchKernelGGL(lat_ex_v<true>, dim3(na, w), dim3(256), 0, st, na, no, w, d.alpha, p->vbar, L->U + o,
-                             nullptr, L->V + o);
-        } else {
-          hipLaunchKernelGGL(lat_ex_t, dim3(na, w), dim3(64), 0, st, na, no, w, L->U + o, L->t);
-          hipLaunchKernelGGL(lat_ex_v<false>, dim3(na, w), dim3(256), 0, st, na, no, w, d.alpha, p->vbar, nullptr,
-                             L->t, L->V + o);
-        }
-        BSE_CHECK_LAUNCH();
       }
       g = LatGemm{};
       {
@@ -1217,13 +1218,14 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
         g.N = w * no;
         g.K = no * na;
         g.Z = n;
-        g.A = L->C3;
+        g.A = L->G;
         g.lda = L->ldc;
         g.a_ps = no * L->ldc;
-        g.B = L->V;
-        g.kd = na;
-        g.rs0 = no;
-        g.rs1 = 2 * nu * w;
+        g.a_z = 2 * no * L->ldc;
+        g.B = L->U;
+        g.kd = no;
+        g.rs0 = 2 * nu * w;
+        g.rs1 = no;
         g.nd = no;
         g.cs1 = 2 * nu;
         g.b_ps = nu;
@@ -1237,6 +1239,15 @@ bse_status lattice_apply(Plan* p, const double* X, double* Y, int nb, hipStream_
         g.klen = ((no * na + nsplit - 1) / nsplit + 15) / 16 * 16;
         g.c_split = 2 * E * nR;
         BSE_TRY(lat_gemm_run<true>(g, st));
+      }
+      if (d.alpha != 0.0 && r <= L->r0 && L->r0 < r + n) {
+        StageMark sm_(p, BSE_STAGE_EXCHANGE, st);
+        double* const u = L->t + 2 * (size_t)na * L->nbc;
+        hipLaunchKernelGGL(lat_ex_t, dim3(na, w), dim3(64), 0, st, na, no, w, L->U + 2 * nu * no * w * (L->r0 - r), L->t);
+        hipLaunchKernelGGL(lat_ex_u, dim3(na, w), dim3(64), 0, st, na, w, d.alpha, p->vbar, L->t, u);
+        hipLaunchKernelGGL(lat_ex_f, dim3((no + 63) / 64, no, w), dim3(256), 0, st, na, no, L->ldc, L->C1, u,
+                           L->F + 2 * E * L->r0);
+        BSE_CHECK_LAUNCH();
       }
     }
     StageMark sm_(p, BSE_STAGE_TX, st);
