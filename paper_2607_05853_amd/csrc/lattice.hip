@@ -294,10 +294,11 @@ long long tiles(const LatGemm& g, int bm, int bn) {
   return (long long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.Z * g.nsplit;
 }
 
-// Full-size tiles once there are enough of them to hide each other's loads (fewer if the sum is long), small shallow tiles (four to five blocks
-// per CU) below and for operands of few rows: 5x6x7, N_ao 30, N_aux 90 (1782 full-size tiles of the first product):
-// 91 -> 73 us and 90 -> 80 us for the complex products.  The real one takes 96-row tiles where these leave less
-// empty than 128 (N_aux = 90: 142 -> 120 us).
+// Full-size tiles once there are enough of them to hide each other's loads (fewer if the sum is long), small shallow
+// tiles (four to five blocks per CU) below and for operands of few rows: 5x6x7, N_ao 30, N_aux 90, 27 R, 5 vectors (1782
+// full-size tiles of U, as many of F) 267 -> 245 us per application by contractions.  The real product, a tenth of the work, takes
+// 96-row tiles where these leave less empty than 128 (245 us against 250 with 128 or 64 rows), 64 x 64 for few rows or
+// tiles (8x8x8: 22.9 ms with 128 x 128, 23.1 with 64 x 64).
 template <bool CPLX, bool TILED = false>
 bse_status lat_gemm_run(const LatGemm& g, hipStream_t st) {
   auto even = [](long long x) { return (x & 1) == 0; };
