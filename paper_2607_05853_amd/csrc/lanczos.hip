@@ -396,10 +396,11 @@ extern "C" bse_status bse_offset_spectrum(bse_plan* const* plans, const void* co
       set_error("bse_offset_spectrum: NULL plan / start block or non-finite weight at offset " + std::to_string(j));
       return BSE_EINVAL;
     }
-    const bse_dims& a = plans[0]->impl.d;
-    const bse_dims& b = plans[j]->impl.d;
-    if (a.nk[0] != b.nk[0] || a.nk[1] != b.nk[1] || a.nk[2] != b.nk[2] || a.n_ao != b.n_ao || a.nv != b.nv ||
-        a.nc != b.nc || a.n_aux != b.n_aux) {
+    // the sizes as given: BF16x3 plans store n_ao and n_aux rounded up, and only where the copies fit
+    const Plan &p = plans[0]->impl, &o = plans[j]->impl;
+    const bse_dims &a = p.d, &b = o.d;
+    if (a.nk[0] != b.nk[0] || a.nk[1] != b.nk[1] || a.nk[2] != b.nk[2] || a.nv != b.nv || a.nc != b.nc ||
+        p.given_ao != o.given_ao || p.given_aux != o.given_aux) {
       set_error("bse_offset_spectrum: the plans describe different problem sizes");
       return BSE_ESHAPE;
     }
