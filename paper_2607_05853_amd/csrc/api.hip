@@ -413,12 +413,10 @@ __global__ void permute_blocks(const unsigned short* __restrict__ in, unsigned s
   }
 }
 
-}  // namespace
-
-// the q-batch buffers of the direct term, each on its own so that a call after a failed allocation completes the set
+// the q-batch buffers of the direct term
 bse_status pair_workspace(Plan* p) {
   const long long nq = p->qb, Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
-  auto get = [&](void** b, size_t bytes) -> bse_status { return *b ? BSE_OK : plan_alloc(p, b, bytes); };
+  auto get = [&](void** b, size_t bytes) { return plan_alloc(p, b, bytes); };
   BSE_TRY(get(&p->Mv, p->esz * (size_t)(nq * Nk * nv * nv * na)));
   BSE_TRY(get(&p->P, p->esz * (size_t)(nq * Nk * nv * nv * na)));
   if (p->mc_direct) BSE_TRY(get(&p->Mc, p->esz * (size_t)(nq * Nk * nc * nc * na)));
@@ -433,8 +431,6 @@ bse_status pair_workspace(Plan* p) {
   BSE_TRY(get((void**)&p->tab_psi_c, sizeof(long long) * (size_t)(nq * Nk * nc)));
   return get((void**)&p->tab_mc, sizeof(long long) * (size_t)(nq * Nk * nc));
 }
-
-namespace {
 
 // two-centre LRI coefficients as given to plan creation
 struct TwoCentreIn {
@@ -810,10 +806,10 @@ bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const d
     BSE_TRY(plan_alloc(p, (void**)&p->xu, 16 * (size_t)na * max_nb));
   }
   BSE_TRY(plan_alloc(p, (void**)&p->txp, 16 * (size_t)TX_CHUNKS * p->N * max_nb));
+  // also where every application goes over lattice vectors: the gradient needs these buffers and allocates nothing of
+  // its own into a caller's g_Wq, so that its first call can be captured
+  BSE_TRY(pair_workspace(p));
   if (f64 && !tc && p->herm_half) BSE_TRY(lattice_build(p, C, W_q, st));
-  // the pair route's buffers now, unless every application goes over lattice vectors (then its gradient and coupling
-  // block allocate them on first use: 12 GiB less to allocate, 228 ms on memory the driver has yet to clear)
-  if (!lattice_applies(p, max_nb)) BSE_TRY(pair_workspace(p));
   return BSE_OK;
 }
 

@@ -258,7 +258,6 @@ struct StageMark {
 bse_status collect_stage_times(Plan* p);
 
 bse_status plan_alloc(Plan* p, void** ptr, size_t bytes);
-bse_status pair_workspace(Plan* p);  // the q-batch buffers of the direct term, where not yet allocated
 
 // stage launchers (apply.hip)
 bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t st);

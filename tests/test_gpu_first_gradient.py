@@ -1,0 +1,68 @@
+"""The first gradient of a plan into a caller's g_Wq allocates nothing where the plan holds every buffer it needs, so
+that it can be captured into a graph without a call before it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import dense_kmesh, make_problem, random_block
+from tolerances import GRAD_TOL
+
+pytestmark = pytest.mark.gpu
+ENV = "BSE_TEST_FAIL_ALLOC"
+
+
+def T(a, dt=torch.complex128):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(torch.device("cuda:0"), dt)
+
+
+def rel(a, b):
+    return np.abs(a - b).max() / np.abs(b).max()
+
+
+def problem(nv, nc, no, na):
+    p = make_problem(dict(cfg_id=79, coarse=(2, 2, 2), dense=(4, 3, 3), n_ao=no, nv=nv, nc=nc, n_aux=na), 0, "G2")
+    W = O.interpolate_W_matmul(p.W_R, p.R, p.w_R, dense_kmesh(p.nk))
+    X, Y = random_block(p.N, 2, seed=1), random_block(p.N, 2, seed=2)
+    return p, W, X, Y
+
+
+# FP64 over lattice vectors; FP32
+CASES = [("f64", 2, 3, 10, 20), ("f32", 2, 3, 10, 20)]
+
+
+@pytest.mark.parametrize("prec,nv,nc,no,na", CASES)
+def test_first_gradient_allocates_nothing(monkeypatch, prec, nv, nc, no, na):
+    from paper_2607_05853_amd import bse as B
+    p, W, X, Y = problem(nv, nc, no, na)
+    plan = B.plan_from_problem(p, T(W), prec=prec, max_nb=2, conduction="mc" if prec == "bf16x3" else None)
+    monkeypatch.setenv(ENV, "1")
+    g = plan.apply_adjoint(T(Y), T(X), want_WR=False, want_Wq=True)
+    monkeypatch.delenv(ENV)
+    gW = g["W_q"].cpu().numpy()
+    plan.close()
+    e = rel(gW, O.grad_apply(p, W, Y, X)[1])
+    print("[first gradient %s nv %d na %d] %.1e" % (prec, nv, na, e), flush=True)
+    assert e < GRAD_TOL[prec]
+
+
+def test_first_gradient_in_a_graph():
+    from paper_2607_05853_amd import bse as B
+    p, W, X, Y = problem(2, 3, 10, 20)
+    plan = B.plan_from_problem(p, T(W), prec="f64", max_nb=2)
+    assert plan.lattice() > 0
+    x, y = T(X), T(Y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g = plan.apply_adjoint(y, x, want_WR=False, want_Wq=True)
+    for seed in (3, 4, 5):      # new inputs in the captured buffers, eager work between the replays
+        X2 = random_block(p.N, 2, seed=seed)
+        x.copy_(T(X2))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = {k: g[k].clone() for k in ("W_q", "eps")}
+        ref = plan.apply_adjoint(y, x, want_WR=False, want_Wq=True)
+        assert torch.equal(got["W_q"], ref["W_q"]) and torch.equal(got["eps"], ref["eps"])
+        assert rel(got["W_q"].cpu().numpy(), O.grad_apply(p, W, Y, X2)[1]) < GRAD_TOL["f64"]
+    plan.close()
