@@ -826,18 +826,6 @@ __global__ void pad_matrices(long long n, int rows, int cols, int R, int C, int 
   }
 }
 
-// out[i][r][c] = in[i][r][c], c128 [n][rows][cols] <- [n][R][C] with R, C the larger
-__global__ void crop_matrices(long long n, int rows, int cols, int R, int C, const double* __restrict__ in,
-                              double* __restrict__ out) {
-  const long long tot = n * rows * cols;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (long long)gridDim.x * blockDim.x) {
-    const int c = (int)(i % cols), r = (int)((i / cols) % rows);
-    const long long o = ((i / ((long long)cols * rows)) * R + r) * C + c;
-    out[2 * i] = in[2 * o];
-    out[2 * i + 1] = in[2 * o + 1];
-  }
-}
-
 // The sizes a BF16x3 plan stores.  Every k step of the direct-to-LDS kernels is 16 deep, so n_ao and n_aux
 // are rounded up to 16; other sizes ran on the register-staged kernels, which take 1.3 to 5 times as long (BF16x3
 // apply at 6x6x6: N_ao 71, N_aux 159 6.9 ms, 80 and 160 1.7 ms; 40 and 88 2.0 ms, 48 and 96 1.25 ms).  N_ao from 97
@@ -910,30 +898,16 @@ bse_status build_rounded(Plan* p, const bse_dims* d, const double* eps_qp, const
 }  // namespace
 
 bse_status adjoint_buffer(Plan* p, void* g_Wq, double** gq) {
-  *gq = (double*)g_Wq;
-  const size_t na = p->d.n_aux, ga = p->given_aux;
-  if (!*gq || ga != na) {
-    if (!p->gq_acc) BSE_TRY(plan_alloc(p, (void**)&p->gq_acc, 16 * (size_t)p->Nk * na * na));
-    *gq = p->gq_acc;
-  }
-  if (!g_Wq && ga != na && !p->gq_crop) BSE_TRY(plan_alloc(p, (void**)&p->gq_crop, 16 * (size_t)p->Nk * ga * ga));
+  if (!g_Wq && !p->gq_acc)
+    BSE_TRY(plan_alloc(p, (void**)&p->gq_acc, 16 * (size_t)p->Nk * p->given_aux * p->given_aux));
+  *gq = g_Wq ? (double*)g_Wq : p->gq_acc;
   return BSE_OK;
 }
 
-bse_status adjoint_outputs(Plan* p, double* gq, void* g_Wq, void* g_WR, hipStream_t st) {
-  const int na = p->d.n_aux, ga = p->given_aux;
-  if (ga != na) {
-    double* out = g_Wq ? (double*)g_Wq : p->gq_crop;
-    hipLaunchKernelGGL(crop_matrices, dim3(4096), dim3(256), 0, st, (long long)p->Nk, ga, ga, na, na, gq, out);
-    BSE_CHECK_LAUNCH();
-    gq = out;
-  }
-  if (g_WR) {
-    const int nR = (int)p->wR.size();
-    const std::vector<double> q = plan_kfrac(p);
-    BSE_TRY(interp_adjoint(ga, nR, p->R.data(), p->wR.data(), p->Nk, q.data(), gq, (double*)g_WR, st));
-  }
-  return BSE_OK;
+bse_status adjoint_WR(Plan* p, const double* gq, void* g_WR, hipStream_t st) {
+  const std::vector<double> q = plan_kfrac(p);
+  return interp_adjoint(p->given_aux, (int)p->wR.size(), p->R.data(), p->wR.data(), p->Nk, q.data(), gq, (double*)g_WR,
+                        st);
 }
 
 }  // namespace bse
@@ -1262,7 +1236,7 @@ bse_status bse_apply_adjoint(bse_plan* plan, const void* Ybar, const void* X, in
   double* gq = nullptr;
   BSE_TRY(adjoint_buffer(p, g_Wq, &gq));
   BSE_TRY(adjoint_direct(p, (const double*)Ybar, (const double*)X, nb, gq, false, st));
-  return adjoint_outputs(p, gq, g_Wq, g_WR, st);
+  return g_WR ? adjoint_WR(p, gq, g_WR, st) : BSE_OK;
 }
 
 bse_status bse_density_start(const bse_plan* plan, const void* psi, void* P, void* hip_stream) {

@@ -1516,15 +1516,15 @@ bse_status adjoint_gm(Plan* p, int q0, int nq, bool swap, const int* kq, const d
 }
 
 // gWq[q][mu][nu] = -(1/N_k) sum_{(k v' v)} Gv[(k v' v)][mu] Z[(k v' v)][nu] of nq q from batch-local q i0 on
-// (conj(Gv) for the partners, swap)
+// (conj(Gv) for the partners, swap), for the auxiliary functions as given: the added ones have no gradient to return
 bse_status adjoint_gw(Plan* p, int q0, int i0, int nq, bool swap, const int* dst, const __bf16* Z, double* gWq, bool acc,
                       hipStream_t st) {
-  const int Nk = p->Nk, nv = p->d.nv, na = p->d.n_aux;
+  const int Nk = p->Nk, nv = p->d.nv, na = p->d.n_aux, ga = p->given_aux;
   const long long pair_v = (long long)nv * nv * na;
   GemmArgs g;
   g.batch = nq;
-  g.M = na;
-  g.N = na;
+  g.M = ga;
+  g.N = ga;
   g.K = Nk * nv * nv;
   g.A = (const __bf16*)p->Mv + (long long)i0 * Nk * pair_v;
   g.a_sb = (long long)Nk * pair_v;
@@ -1537,10 +1537,10 @@ bse_status adjoint_gw(Plan* p, int q0, int i0, int nq, bool swap, const int* dst
   g.b_sk = na;
   g.b_sj = 1;
   g.b_ps = p->ps_Mv;
-  g.C = dst ? gWq : gWq + 2 * (long long)(q0 + i0) * na * na;
+  g.C = dst ? gWq : gWq + 2 * (long long)(q0 + i0) * ga * ga;
   g.c_bidx = dst ? dst + q0 + i0 : nullptr;
-  g.c_sb = (long long)na * na;
-  g.c_si = na;
+  g.c_sb = (long long)ga * ga;
+  g.c_si = ga;
   g.c_sj = 1;
   g.alpha = -1.0 / (double)Nk;
   g.beta = acc ? 1 : 0;
@@ -1691,9 +1691,10 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
     }
     {  // gWq[q][mu][nu] = -(1/N_k) sum_{(k v' v)} Gv[(k v' v)][mu] Z[(k v' v)][nu]
       GemmArgs g;
+      const int ga = p->given_aux;
       g.batch = nq;
-      g.M = na;
-      g.N = na;
+      g.M = ga;
+      g.N = ga;
       g.K = Nk * nv * nv;
       g.A = p->Mv;
       g.a_sb = (long long)Nk * nv * nv * na;
@@ -1703,9 +1704,9 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
       g.b_sb = (long long)Nk * nv * nv * na;
       g.b_sk = na;
       g.b_sj = 1;
-      g.C = gWq + 2 * (long long)q0 * na * na;
-      g.c_sb = (long long)na * na;
-      g.c_si = na;
+      g.C = gWq + 2 * (long long)q0 * ga * ga;
+      g.c_sb = (long long)ga * ga;
+      g.c_si = ga;
       g.c_sj = 1;
       g.alpha = -1.0 / (double)Nk;
       g.beta = acc ? 1 : 0;

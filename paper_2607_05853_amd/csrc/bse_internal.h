@@ -228,8 +228,7 @@ struct Plan {
   __bf16* adj_G = nullptr;    // pair-symmetric BF16x3 adjoint: G, then G', of adj_q q each ([q][k][c'c][v'v] planes)
   __bf16* adj_Z2 = nullptr;   // its Z' ([qb][Nk][v'v][n_aux] planes, beside Z in P)
   int adj_q = 0;
-  double* gq_acc = nullptr;   // c128 [Nk][n_aux][n_aux]
-  double* gq_crop = nullptr;  // c128 [Nk][given_aux][given_aux] where that is smaller
+  double* gq_acc = nullptr;   // c128 [Nk][given_aux][given_aux]
 
   std::vector<DevBuf> owned;
   size_t bytes = 0;
@@ -267,10 +266,9 @@ bse_status apply_diag(Plan* p, const double* X, double* Y, int nb, hipStream_t s
 bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, double* gWq, bool acc,
                           hipStream_t st);
 bse_status direct_u_b3(Plan* p, int q0, int nq, const int* kq, hipStream_t st);
-// the W(q) and W(R) gradients asked for, from g_W(q) accumulated in the plan's sizes: the caller's buffer (or the
-// plan's) to accumulate in, then the outputs
+// the buffer adjoint_direct fills with g_W(q) (in the given sizes): the caller's or the plan's; and g_W(R) from it
 bse_status adjoint_buffer(Plan* p, void* g_Wq, double** gq);
-bse_status adjoint_outputs(Plan* p, double* gq, void* g_Wq, void* g_WR, hipStream_t st);
+bse_status adjoint_WR(Plan* p, const double* gq, void* g_WR, hipStream_t st);
 bse_status adjoint_eps(Plan* p, const double* Ybar, const double* X, int nb, double* geps, bool acc,
                        hipStream_t st);
 // the application over lattice vectors (lattice.hip): built at plan creation where W_q allows it, chosen per

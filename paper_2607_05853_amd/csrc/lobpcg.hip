@@ -384,7 +384,7 @@ extern "C" bse_status bse_haydock_vjp(bse_plan* plan, const void* basis, const d
     }
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   const long long N = p->N;
-  const int na = p->d.n_aux;
+  const int na = p->given_aux;
   const int chunk = std::min<int>(p->max_nb, n_w);
   const int m = n_steps;
   Work wk;
@@ -440,7 +440,7 @@ extern "C" bse_status bse_haydock_vjp(bse_plan* plan, const void* basis, const d
       BSE_HIP(hipStreamSynchronize(st));
     }
   }
-  if (want_w) BSE_TRY(adjoint_outputs(p, gq, g_Wq, g_WR, st));
+  if (g_WR) BSE_TRY(adjoint_WR(p, gq, g_WR, st));
   return BSE_OK;
 }
 

@@ -27,8 +27,9 @@ def problem(nv, nc, no, na):
     return p, W, X, Y
 
 
-# FP64 over lattice vectors; FP32
-CASES = [("f64", 2, 3, 10, 20), ("f32", 2, 3, 10, 20)]
+# FP64 over lattice vectors; FP32; BF16x3 that stores more auxiliary functions than given, on the general and on the
+# k-major product
+CASES = [("f64", 2, 3, 10, 20), ("f32", 2, 3, 10, 20), ("bf16x3", 2, 3, 10, 20), ("bf16x3", 8, 8, 16, 24)]
 
 
 @pytest.mark.parametrize("prec,nv,nc,no,na", CASES)
