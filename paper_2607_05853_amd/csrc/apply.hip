@@ -1584,22 +1584,48 @@ bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int
   return adjoint_gw(p, q0, i0, nq, swap, dst, (const __bf16*)p->P, gWq, acc, st);
 }
 
+// The buffers of adjoint_paired, allocated on first use.  A plan whose apply forms M_c holds all that the two passes of
+// adjoint_tn_pass need (equal bits): it takes those where the buffers are missing and cannot be had, under stream capture
+// or for want of memory.
+bse_status paired_workspace(Plan* p, hipStream_t st, bool* ok) {
+  const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
+  *ok = true;
+  if (p->Mc && p->adj_G && p->adj_Z2) return BSE_OK;
+  if (p->mc_direct) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) (void)hipGetLastError();
+    if (c != hipStreamCaptureStatusNone) {
+      *ok = false;
+      return BSE_OK;
+    }
+  }
+  if (!p->adj_q) p->adj_q = std::min(p->qb, std::max(1, 256 / nc));  // 256 rows of the pair-density product
+  const long long part = (long long)p->adj_q * Nk, mc = part * nc * nc * na;
+  auto get = [&]() -> bse_status {
+    if (!p->Mc) {
+      BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)mc));
+      p->ps_Mc = mc;
+    }
+    if (!p->adj_G) BSE_TRY(plan_alloc(p, (void**)&p->adj_G, 2 * p->esz * (size_t)(part * nc * nc * nv * nv)));
+    if (!p->adj_Z2) BSE_TRY(plan_alloc(p, (void**)&p->adj_Z2, p->esz * (size_t)p->qb * Nk * nv * nv * na));
+    return BSE_OK;
+  };
+  const bse_status s = get();
+  if (s != BSE_ENOMEM || !p->mc_direct) return s;
+  set_error("");
+  *ok = false;
+  return BSE_OK;
+}
+
 // The pair-symmetric BF16x3 adjoint at n_v = 4: per batch the valence pair densities, then for adj_q q at a time M_c, G, G' and
 // both Z from one pass over M_c, then the two W gradients of the batch.  M_c of a part is enough, so a plan whose
 // apply does not form M_c allocates adj_q q of it on first use instead of a whole batch (8x8x8: 2.1 GB instead of
 // 17.4).  Gradient at the 8x8x8 workload 28.3 -> 23.6 ms.
 bse_status adjoint_paired(Plan* p, const double* Ybar, const double* X, int nb, double* gWq, bool acc, hipStream_t st) {
   const int Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
-  const long long pair_v = (long long)nv * nv * na, pair_c = (long long)nc * nc * na;
+  const long long pair_v = (long long)nv * nv * na;
   const long long nt2 = (long long)nc * nc * nv * nv;
-  if (!p->adj_q) p->adj_q = std::min(p->qb, std::max(1, 256 / nc));  // 256 rows of the pair-density product
   const long long ps_G = (long long)p->adj_q * Nk * nt2;
-  if (!p->Mc) {
-    BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->adj_q * Nk * pair_c));
-    p->ps_Mc = (long long)p->adj_q * Nk * pair_c;
-  }
-  if (!p->adj_G) BSE_TRY(plan_alloc(p, (void**)&p->adj_G, 2 * p->esz * (size_t)ps_G));
-  if (!p->adj_Z2) BSE_TRY(plan_alloc(p, (void**)&p->adj_Z2, p->esz * (size_t)p->qb * Nk * pair_v));
   __bf16* const G2 = p->adj_G + 4 * ps_G;
   for (int q0 = 0; q0 < p->nhalf; q0 += p->qb) {
     const int nq = std::min(p->qb, p->nhalf - q0);
@@ -1633,7 +1659,11 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
   const bool tn = p->split && (nv * nv) % 8 == 0 && p->given_aux % 8 == 0;
-  if (tn && p->herm_half && !p->two_centre && nv == 4) return adjoint_paired(p, Ybar, X, nb, gWq, acc, st);
+  if (tn && p->herm_half && !p->two_centre && nv == 4) {
+    bool ok = false;
+    BSE_TRY(paired_workspace(p, st, &ok));
+    if (ok) return adjoint_paired(p, Ybar, X, nb, gWq, acc, st);
+  }
   if (!p->Mc) BSE_TRY(plan_alloc(p, &p->Mc, p->esz * (size_t)p->qb * Nk * nc * nc * na));
   if (tn && p->herm_half) {
     // pair symmetry of the gradient: with Hermitian C^mu the pairs (k, k - q) of g_W(-q) carry the pair

@@ -67,3 +67,20 @@ def test_first_gradient_in_a_graph():
         assert torch.equal(got["W_q"], ref["W_q"]) and torch.equal(got["eps"], ref["eps"])
         assert rel(got["W_q"].cpu().numpy(), O.grad_apply(p, W, Y, X2)[1]) < GRAD_TOL["f64"]
     plan.close()
+
+
+def test_paired_gradient_without_its_buffers(monkeypatch):
+    # n_v = 4 on the M_c route: the first gradient goes without the buffers of the one-pass form where these cannot be
+    # allocated, with the same bits
+    from paper_2607_05853_amd import bse as B
+    p, W, X, Y = problem(4, 4, 16, 24)
+    plan = B.plan_from_problem(p, T(W), prec="bf16x3", max_nb=2, conduction="mc")
+    for n in ("1", "2"):        # either of the two
+        monkeypatch.setenv(ENV, n)
+        without = plan.apply_adjoint(T(Y), T(X), want_WR=False, want_Wq=True)["W_q"]
+        monkeypatch.delenv(ENV)
+        assert rel(without.cpu().numpy(), O.grad_apply(p, W, Y, X)[1]) < GRAD_TOL["bf16x3"]
+    held = plan.bytes
+    with_ = plan.apply_adjoint(T(Y), T(X), want_WR=False, want_Wq=True)["W_q"]
+    assert plan.bytes > held and torch.equal(with_, without)
+    plan.close()
