@@ -963,10 +963,12 @@ bse_status kernels_build(Plan* p, const std::vector<int2>& pair, hipStream_t st)
 
 }  // namespace
 
+namespace {
+
 // Finds the R set of W_q: W(R) on a box of at most 7 x 7 x 7 around R = 0 by the inverse sum, the R whose matrix is
 // not rounding noise, and a check that they give W_q back to 1e-14 of its largest element (a W_q that is no such sum
-// keeps the pair route).  Called for FP64 plans whose W_q has the pair symmetry, i.e. real W(R).
-bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st) {
+// keeps the pair route).  p->lat stays empty, or is left incomplete, where the plan does not take it.
+bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, bool* taken) {
   const bse_dims& d = p->d;
   const int Nk = p->Nk, na = d.n_aux, no = d.n_ao;
   const long long n2 = (long long)na * na, nc1 = (long long)na * no * no;
@@ -1048,10 +1050,7 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   if (const char* e = std::getenv("BSE_WORKSPACE_GB")) room = (size_t)(std::atof(e) * (double)(1ull << 30));
   bool kernels = 2 * (int)pair.size() - 1 == nR && kx_bytes(p, (nR + 1) / 2) <= std::min(room, budget) &&
                  secs_kernel(p, nR, p->max_nb) < secs_gemm(p, nR, p->max_nb);
-  if (!((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) {
-    lattice_free(p);
-    return BSE_OK;
-  }
+  if (!((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) return BSE_OK;
   BSE_TRY(plan_alloc(p, (void**)&L->Wr, 8 * (size_t)nR * n2));
   BSE_TRY(dmalloc(&idx.p, 4 * (size_t)nR));
   BSE_TRY(dmalloc(&chk.p, 16 * (size_t)nR * n2));
@@ -1066,10 +1065,7 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   BSE_HIP(hipStreamSynchronize(st));
   // |W_q| <= sum_R |W(R)|; the largest W(R) element is a lower bound of max |W_q| up to cancellation, so the
   // comparison with it is the stricter one
-  if (!(off <= 1e-14 * top * std::sqrt((double)nR))) {
-    lattice_free(p);
-    return BSE_OK;
-  }
+  if (!(off <= 1e-14 * top * std::sqrt((double)nR))) return BSE_OK;
   if (kernels) {  // W(-R) = W(R)^T as of a Hermitian W_q
     double asym = 0.0;
     Tmp pr;
@@ -1103,7 +1099,9 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   }
   if (kernels) {
     BSE_TRY(plan_alloc(p, (void**)&L->F, 16 * no2 * nbc * (size_t)nR));
-    return kernels_build(p, pair, st);
+    BSE_TRY(kernels_build(p, pair, st));
+    *taken = true;
+    return BSE_OK;
   }
   const size_t u_r = 16 * (size_t)nc1 * nbc, g_r = 16 * (size_t)(no * L->ldc);
   L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / (u_r + g_r)));
@@ -1115,7 +1113,25 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   BSE_TRY(plan_alloc(p, (void**)&L->t, 32 * (size_t)na * nbc));
   hipLaunchKernelGGL(lat_transpose, dim3((na + 15) / 16, (na + 15) / 16, nR), dim3(256), 0, st, na, L->Wr);
   BSE_CHECK_LAUNCH();
+  *taken = true;
   return BSE_OK;
+}
+
+}  // namespace
+
+// Called for FP64 plans whose W_q has the pair symmetry, i.e. real W(R).
+bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st) {
+  const size_t held = p->owned.size();
+  bool taken = false;
+  const bse_status s = lattice_try(p, C, W_q, st, &taken);
+  if (s == BSE_OK && taken) return BSE_OK;
+  // the plan keeps the pair route, and nothing of this
+  lattice_free(p);
+  for (; p->owned.size() > held; p->owned.pop_back()) {
+    p->bytes -= p->owned.back().bytes;
+    dfree(p->owned.back().p);
+  }
+  return s;
 }
 
 int lattice_size(const Plan* p, int nb) { return lattice_applies(p, nb) ? p->lat->nR : 0; }

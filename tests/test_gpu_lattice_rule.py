@@ -1,0 +1,59 @@
+"""Which FP64 plans apply over lattice vectors, and what they keep when they do not."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import dense_kmesh, make_problem, random_block
+from tolerances import KERNEL_TOL, diag_times, kernel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def T(a, dt=torch.complex128):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(torch.device("cuda:0"), dt)
+
+
+def crystal(dense=(9, 4, 3), coarse=(3, 3, 3), no=12, na=24, **kw):
+    p = make_problem(dict(cfg_id=92, coarse=coarse, dense=dense, n_ao=no, nv=2, nc=3, n_aux=na, **kw), 0, "G2")
+    return p, O.interpolate_W_matmul(p.W_R, p.R, p.w_R, dense_kmesh(p.nk))
+
+
+def symmetric(p, W):
+    """W with W(-q) = conj W(q) and W(q) Hermitian."""
+    n = p.nk
+    neg = np.array([((-i) % n[0] * n[1] + (-j) % n[1]) * n[2] + (-k) % n[2]
+                    for i in range(n[0]) for j in range(n[1]) for k in range(n[2])])
+    W = 0.5 * (W + W[neg].conj())
+    return 0.5 * (W + W.conj().transpose(0, 2, 1))
+
+
+def beyond(p, W, level):
+    """W plus a real symmetric W(R) at R1 = +-4, outside the box, of at most level times the largest element of W."""
+    A = np.random.default_rng(11).uniform(-1, 1, W.shape[1:])
+    c = np.cos(8 * np.pi * dense_kmesh(p.nk)[:, 0])[:, None, None]
+    return W + level * np.maximum(abs(W.real), abs(W.imag)).max() * c * 0.5 * (A + A.T)
+
+
+def check_against_pairs(B, p, W, plan):
+    X = random_block(p.N, 2, seed=3)
+    pairs = B.plan_from_problem(p, T(W), prec="f64", max_nb=2, all_pairs=True)
+    Y, Z = plan.apply(T(X)).cpu().numpy(), pairs.apply(T(X)).cpu().numpy()
+    pairs.close()
+    assert kernel_err(Y, Z, diag_times(p, X)) < KERNEL_TOL["f64"]
+
+
+def test_refused_plan_keeps_nothing():
+    # the R set of both is built and fails its check, one of 27 and one of all 84 R of the box: both plans are then those
+    # of the pair route, to the byte
+    from paper_2607_05853_amd import bse as B
+    p, W = crystal()
+    rng = np.random.default_rng(12)
+    far = symmetric(p, rng.standard_normal(W.shape) + 1j * rng.standard_normal(W.shape))
+    plain, few, all_ = (B.plan_from_problem(p, T(w), prec="f64", max_nb=2) for w in (W, beyond(p, W, 1e-9), far))
+    assert plain.lattice() > 0 and few.lattice() == 0 and all_.lattice() == 0
+    check_against_pairs(B, p, beyond(p, W, 1e-9), few)
+    held = [q.bytes for q in (plain, few, all_)]
+    for q in (plain, few, all_):
+        q.close()
+    assert held[1] == held[2] < held[0]
