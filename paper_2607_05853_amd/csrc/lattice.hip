@@ -1131,7 +1131,9 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
     p->bytes -= p->owned.back().bytes;
     dfree(p->owned.back().p);
   }
-  return s;
+  if (s != BSE_ENOMEM) return s;
+  set_error("");  // too little memory for it: the pair route has its buffers already
+  return BSE_OK;
 }
 
 int lattice_size(const Plan* p, int nb) { return lattice_applies(p, nb) ? p->lat->nR : 0; }

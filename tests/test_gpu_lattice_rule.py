@@ -57,3 +57,33 @@ def test_refused_plan_keeps_nothing():
     for q in (plain, few, all_):
         q.close()
     assert held[1] == held[2] < held[0]
+
+
+@pytest.mark.parametrize("hermitian", [True, False])
+def test_too_little_memory_keeps_the_pair_route(monkeypatch, hermitian):
+    # kernels, or contractions: every allocation of theirs that fails leaves a plan of the pair route
+    from paper_2607_05853_amd import bse as B
+    p, W = crystal()
+    if not hermitian:
+        W = W + 0.1 * abs(W).max() * np.random.default_rng(4).standard_normal(W.shape[1:])
+    refused, fell_back = 0, 0
+    for n in range(1, 100):
+        monkeypatch.setenv("BSE_TEST_FAIL_ALLOC", str(n))
+        try:
+            plan = B.plan_from_problem(p, T(W), prec="f64", max_nb=2)
+        except B.BSEError as e:
+            assert e.status == 3 and not fell_back
+            refused += 1
+            continue
+        finally:
+            monkeypatch.delenv("BSE_TEST_FAIL_ALLOC")
+        if plan.lattice() > 0:
+            plan.close()
+            break
+        fell_back += 1
+        if fell_back % 5 == 1:
+            check_against_pairs(B, p, W, plan)
+        plan.close()
+    print("[lattice memory, hermitian %s] %d allocations of the plan, %d of the lattice" % (hermitian, refused, fell_back),
+          flush=True)
+    assert refused >= 10 and fell_back >= 10
