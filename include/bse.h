@@ -235,10 +235,12 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
 /* *n_R > 0 when bse_apply to nb vectors sums over that many lattice vectors R
  * instead of forming blocks of pairs (k, k'): on BSE_F64 plans with k-independent
  * C^mu, W_q(-q) = conj W_q(q) and without BSE_ALL_PAIRS, plan creation recovers
- * W(R) from W_q and checks that at most 256 R with components up to 3 give it back to 1e-14 (a
- * W_q interpolated from a coarse mesh of up to 7 points per axis); the sum over k'
- * then separates and its work grows with n_R nb instead of N_k^2.  Taken where
- * that needs less work; 0 otherwise.  Host pointer.  With W_q Hermitian such a
+ * W(R) from W_q and checks that at most 256 R with components up to 3 give every
+ * element of it back to 4e-15 of the largest one, its rounding (a W_q interpolated
+ * from a coarse mesh of up to 7 points per axis and at most 256 R); the sum over k'
+ * then separates and its work grows with n_R nb instead of N_k^2.  Any other W_q is
+ * taken as it is, by pairs.  Taken where
+ * that needs less work; 0 otherwise.  Host pointer.  With W_q Hermitian (to the same rounding) such a
  * plan keeps one n_ao^2 x n_ao^2 kernel per pair (R, -R), half of it stored
  * (8 n_ao^4 bytes), where these take at most 16 GiB, a fifth of the free memory
  * and BSE_WORKSPACE_GB, and less time than contracting C^mu and W(R) anew. */

@@ -87,3 +87,15 @@ def test_too_little_memory_keeps_the_pair_route(monkeypatch, hermitian):
     print("[lattice memory, hermitian %s] %d allocations of the plan, %d of the lattice" % (hermitian, refused, fell_back),
           flush=True)
     assert refused >= 10 and fell_back >= 10
+
+
+@pytest.mark.parametrize("level,taken", [(0.0, True), (1e-14, False), (5e-14, False), (1e-12, False)])
+def test_sums_are_taken_to_their_rounding_only(level, taken):
+    # 441 k, 125 R; the part outside the box weighs level, so a plan that dropped it would be off by about level
+    from paper_2607_05853_amd import bse as B
+    p, W = crystal(dense=(9, 7, 7), coarse=(4, 4, 4), no=10, na=20)
+    W = beyond(p, W, level)
+    plan = B.plan_from_problem(p, T(W), prec="f64", max_nb=2)
+    got = plan.lattice()
+    plan.close()
+    assert (got > 0) == taken, got
