@@ -10,6 +10,9 @@ constexpr int FT_MAXR = 7;    // distinct R components per axis
 constexpr int FT_BOX = FT_MAXR * FT_MAXR * FT_MAXR + 1;
 constexpr int FT_MAXNR = 256;
 
+// the larger of two non-negative numbers, a NaN above all: as bits it then passes an atomicMax too
+__device__ __forceinline__ double max_or_nan(double a, double b) { return a > b || a != a ? a : b; }
+
 // the axes of a sum, passed to the kernels by value (no table in device memory): under 4 KiB
 struct FtArgs {
   int n[3], r[3], nR;

@@ -218,19 +218,14 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
           if (j2 != j) c[o1] = float2{(float)s1.x, (float)s1.y};
         } else {
           const double2 r0 = reinterpret_cast<const double2*>(ref)[o0], r1 = reinterpret_cast<const double2*>(ref)[o1];
-          // !(d <= dmax) so that a NaN stays
-          const double d0 = fmax(fabs(s0.x - r0.x), fabs(s0.y - r0.y)), d1 = fmax(fabs(s1.x - r1.x), fabs(s1.y - r1.y));
-          if (!(d0 <= dmax)) dmax = d0;
-          if (!(d1 <= dmax)) dmax = d1;
+          dmax = max_or_nan(dmax, max_or_nan(fabs(s0.x - r0.x), fabs(s0.y - r0.y)));
+          dmax = max_or_nan(dmax, max_or_nan(fabs(s1.x - r1.x), fabs(s1.y - r1.y)));
         }
       }
     }
   }
   if constexpr (MODE == 2) {
-    for (int o = 32; o > 0; o >>= 1) {
-      const double d = __shfl_down(dmax, o);
-      if (!(d <= dmax)) dmax = d;
-    }
+    for (int o = 32; o > 0; o >>= 1) dmax = max_or_nan(dmax, __shfl_down(dmax, o));
     if ((threadIdx.x & 63) == 0)
       atomicMax((unsigned long long*)out, (unsigned long long)__double_as_longlong(fabs(dmax)));
   }

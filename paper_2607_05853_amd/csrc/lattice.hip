@@ -703,13 +703,12 @@ __global__ void lat_absmax(long long n, const double* __restrict__ W, unsigned l
   double mr = 0.0, mi = 0.0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     const double2 v = w[i];
-    if (!(fabs(v.x) <= mr)) mr = fabs(v.x);
-    if (!(fabs(v.y) <= mi)) mi = fabs(v.y);
+    mr = max_or_nan(mr, fabs(v.x));
+    mi = max_or_nan(mi, fabs(v.y));
   }
   for (int o = 32; o > 0; o >>= 1) {
-    const double a = __shfl_down(mr, o), b = __shfl_down(mi, o);
-    if (!(a <= mr)) mr = a;
-    if (!(b <= mi)) mi = b;
+    mr = max_or_nan(mr, __shfl_down(mr, o));
+    mi = max_or_nan(mi, __shfl_down(mi, o));
   }
   if ((threadIdx.x & 63) == 0) {
     atomicMax(&out[2 * blockIdx.y], (unsigned long long)__double_as_longlong(mr));
@@ -740,10 +739,7 @@ __global__ __launch_bounds__(256) void lat_asym(int na, const int2* __restrict__
   x[a][b] = j0 + a < na && i0 + b < na ? v[(long long)(j0 + a) * na + i0 + b] : 0.0;
   __syncthreads();
   double m = i0 + a < na && j0 + b < na ? fabs(w[(long long)(i0 + a) * na + j0 + b] - x[b][a]) : 0.0;
-  for (int o = 32; o > 0; o >>= 1) {
-    const double s = __shfl_down(m, o);
-    if (!(s <= m)) m = s;
-  }
+  for (int o = 32; o > 0; o >>= 1) m = max_or_nan(m, __shfl_down(m, o));
   const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
   if ((threadIdx.x & 63) == 0 && bits > *(volatile unsigned long long*)out) atomicMax(out, bits);
 }
@@ -1026,8 +1022,11 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   BSE_HIP(hipMemcpyAsync(mx.data(), red.p, 16 * (size_t)nbox, hipMemcpyDeviceToHost, st));
   BSE_HIP(hipStreamSynchronize(st));
   double top = 0.0;
-  for (double v : mx) top = std::max(top, v);
-  if (!(top > 0.0) || !std::isfinite(top)) return BSE_OK;
+  for (double v : mx) {
+    if (!std::isfinite(v)) return BSE_OK;
+    top = std::max(top, v);
+  }
+  if (!(top > 0.0)) return BSE_OK;
   std::vector<int32_t> act, ids;
   for (int r = 0; r < nbox; ++r) {
     const bool zero = R[3 * r] == 0 && R[3 * r + 1] == 0 && R[3 * r + 2] == 0;

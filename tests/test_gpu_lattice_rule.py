@@ -99,3 +99,22 @@ def test_sums_are_taken_to_their_rounding_only(level, taken):
     got = plan.lattice()
     plan.close()
     assert (got > 0) == taken, got
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1j * np.nan])
+@pytest.mark.parametrize("n_bad", [1, 40])
+def test_not_a_number_keeps_the_pair_route(bad, n_bad):
+    # one pair of elements among 2 x 10^5, which every later maximum has to keep, and many of them
+    from paper_2607_05853_amd import bse as B
+    p, W = crystal(dense=(9, 7, 7), coarse=(4, 4, 4), no=10, na=20)
+    neg = np.array([((-i) % 9 * 7 + (-j) % 7) * 7 + (-k) % 7 for i in range(9) for j in range(7) for k in range(7)])
+    W = W.copy()
+    for i in range(n_bad):
+        q = 5 + 3 * i
+        for e in ((3, 4), (4, 3)):
+            W[q, e[0], e[1]] = W[neg[q], e[0], e[1]] = bad
+    plan = B.plan_from_problem(p, T(W), prec="f64", max_nb=2)
+    got = plan.lattice()
+    Y = plan.apply(T(random_block(p.N, 2, seed=3))).cpu().numpy()
+    plan.close()
+    assert got == 0 and not np.isfinite(Y).all()
