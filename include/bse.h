@@ -242,8 +242,12 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
  * taken as it is, by pairs.  Taken where
  * that needs less work; 0 otherwise.  Host pointer.  With W_q Hermitian (to the same rounding) such a
  * plan keeps one n_ao^2 x n_ao^2 kernel per pair (R, -R), half of it stored
- * (8 n_ao^4 bytes), where these take at most 16 GiB, a fifth of the free memory
- * and BSE_WORKSPACE_GB, and less time than contracting C^mu and W(R) anew. */
+ * (8 n_ao^4 bytes), where these take at most 16 GiB and less time than
+ * contracting C^mu and W(R) anew.  What either form allocates besides copies of
+ * the inputs stays below a fifth of the memory free at plan creation and below
+ * BSE_WORKSPACE_GB (the contractions take one vector and one R at a time in less);
+ * a plan that finds no room for it forms pairs.  The forms' sums run in different
+ * orders: results agree to FP64 rounding, not bit for bit. */
 bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R);
 
 /* Device bytes held by the plan (copies, halves and workspaces). */

@@ -832,6 +832,12 @@ KxShape kx_shape(int nh, int S, int nb) {
   return x;
 }
 
+// doubles of the partial sums for up to nb vectors
+size_t kx_part(int nh, int S, int nb) {
+  const size_t one = kx_shape(nh, S, 1).doubles(nh, S);
+  return nb > 4 ? std::max(one, kx_shape(nh, S, 8).doubles(nh, S)) : one;
+}
+
 bse_status kx_go(const LatKx& g, const KxShape& x, hipStream_t st) {
   const dim3 grid((unsigned)(g.nh * x.blocks + 7) / 8 * 8);
   if (x.NT == 1 && x.RS == 16)
@@ -949,10 +955,7 @@ bse_status kernels_build(Plan* p, const std::vector<int2>& pair, hipStream_t st)
       k.rows -= tri;
     }
   }
-  size_t part = 0;
-  for (int b : {1, 8})
-    if (b == 1 || L->nbc > 4) part = std::max(part, kx_shape(L->nh, L->S, b).doubles(L->nh, L->S));
-  BSE_TRY(plan_alloc(p, (void**)&L->part, 8 * part));
+  BSE_TRY(plan_alloc(p, (void**)&L->part, 8 * kx_part(L->nh, L->S, L->nbc)));
   BSE_HIP(hipStreamSynchronize(st));
   return BSE_OK;
 }
@@ -1000,8 +1003,8 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
     (void)hipGetLastError();
     return BSE_OK;
   }
-  const size_t budget = std::min<size_t>((size_t)16 << 30, free_b / 5);
-  if (32 * (size_t)nbox * n2 > budget) return BSE_OK;
+  const size_t most = (size_t)16 << 30, fifth = free_b / 5;
+  if (32 * (size_t)nbox * n2 > std::min(most, fifth)) return BSE_OK;
 
   std::vector<double> q = plan_kfrac(p);
   // the inverse sum over the whole box (the kernels' R list is limited to FT_MAXNR: as many R1 at a time as fit)
@@ -1050,9 +1053,18 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
     for (int s = r + 1; s < nR; ++s)
       if (act[3 * r] == -act[3 * s] && act[3 * r + 1] == -act[3 * s + 1] && act[3 * r + 2] == -act[3 * s + 2])
         pair.push_back(int2{r, s});
-  size_t room = budget;
-  if (const char* e = std::getenv("BSE_WORKSPACE_GB")) room = (size_t)(std::atof(e) * (double)(1ull << 30));
-  bool kernels = 2 * (int)pair.size() - 1 == nR && kx_bytes(p, (nR + 1) / 2) <= std::min(room, budget) &&
+  // All that either form allocates besides its copies of the inputs stays below a fifth of the free memory and
+  // BSE_WORKSPACE_GB (below that only at the least the contractions need, one vector and one R at a time); the kernels
+  // alone below 16 GiB, the contractions' buffers too
+  size_t limit = fifth;
+  if (const char* e = std::getenv("BSE_WORKSPACE_GB"))
+    limit = (size_t)std::min((double)limit, std::max(0.0, std::atof(e) * (double)(1ull << 30)));
+  const size_t no2 = (size_t)no * no;
+  const int nh = (int)pair.size();
+  auto kernel_bytes = [&](int b) {  // for b vectors at a time
+    return kx_bytes(p, nh) + 8 * kx_part(nh, kx_tiles(p), b) + 16 * no2 * b * ((size_t)Nk + 2 * (size_t)nR);
+  };
+  bool kernels = 2 * nh - 1 == nR && kx_bytes(p, nh) <= most && kernel_bytes(std::min(8, p->max_nb)) <= limit &&
                  secs_kernel(p, nR, p->max_nb) < secs_gemm(p, nR, p->max_nb);
   if (!((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) return BSE_OK;
   BSE_TRY(plan_alloc(p, (void**)&L->Wr, 8 * (size_t)nR * n2));
@@ -1083,18 +1095,26 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
     BSE_HIP(hipMemcpyAsync(&asym, dmax, 8, hipMemcpyDeviceToHost, st));
     BSE_HIP(hipStreamSynchronize(st));
     kernels = asym <= W_ROUNDING * top;
+    if (!kernels && !(secs_gemm(p, nR, 1) < secs_pairs(p))) return BSE_OK;
   }
   L->ldc = ((long long)na * no + 15) / 16 * 16 + 16;
   BSE_TRY(plan_alloc(p, (void**)&L->C1, 16 * (size_t)(no * L->ldc)));
   BSE_TRY(plan_alloc(p, (void**)&L->C3, 16 * (size_t)(no * L->ldc)));
   hipLaunchKernelGGL(lat_pack_C, dim3(2048), dim3(256), 0, st, na, no, L->ldc, (const double*)C, L->C1, L->C3);
   BSE_CHECK_LAUNCH();
-  // workspaces: all max_nb vectors at once and R in passes of about 4 GiB of U and V, fewer vectors when D(k) and
-  // the R arrays would not fit; 8 partial F(R) for the split of the last contraction, 32 of small ones
-  const size_t no2 = (size_t)no * no;
+  // workspaces: all max_nb vectors at once, and for the contractions R in passes of about 4 GiB of U and G, fewer where
+  // they would not fit; 8 partial F(R) for the split of the last contraction, 32 of small ones
   int nbc = p->max_nb;
-  auto fixed = [&](int b) { return 16 * no2 * b * ((size_t)Nk + 10 * (size_t)nR); };
-  while (nbc > 1 && fixed(nbc) > room / 2) nbc = (nbc + 1) / 2;
+  const size_t room = std::min(most, limit), u1 = 16 * (size_t)nc1, g_r = 16 * (size_t)(no * L->ldc);
+  if (kernels)
+    while (nbc > 8 && kernel_bytes(nbc) > limit) nbc = (nbc + 1) / 2;
+  else
+    while (nbc > 1 && 16 * no2 * nbc * ((size_t)Nk + 10 * (size_t)nR) > room / 2) nbc = (nbc + 1) / 2;
+  const size_t d_bytes = 16 * no2 * nbc * (size_t)(Nk + nR), f1 = 16 * no2 * nbc * (size_t)nR;
+  const size_t f_room = room / 2 > d_bytes ? (room / 2 - d_bytes) / f1 : 0;
+  const size_t copies = std::max<size_t>(1, std::min<size_t>(f_room, f1 > ((size_t)32 << 20) ? 8 : 32));
+  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / (u1 * nbc + g_r)));
+  if (!kernels && d_bytes + copies * f1 + (u1 * nbc + g_r) * L->rc > fifth) return BSE_OK;
   L->nbc = nbc;
   BSE_TRY(plan_alloc(p, (void**)&L->D, 16 * no2 * nbc * (size_t)Nk));
   BSE_TRY(plan_alloc(p, (void**)&L->DR, 16 * no2 * nbc * (size_t)nR));
@@ -1108,11 +1128,8 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
     *taken = true;
     return BSE_OK;
   }
-  const size_t u_r = 16 * (size_t)nc1 * nbc, g_r = 16 * (size_t)(no * L->ldc);
-  L->rc = (int)std::max<size_t>(1, std::min<size_t>(nR, std::min<size_t>((size_t)4 << 30, room / 2) / (u_r + g_r)));
-  const size_t f1 = 2 * no2 * nbc * (size_t)nR;
-  L->f_doubles = (long long)(f1 * (f1 > ((size_t)1 << 22) ? 8 : 32));
-  BSE_TRY(plan_alloc(p, (void**)&L->U, u_r * L->rc));
+  L->f_doubles = (long long)(copies * f1 / 8);
+  BSE_TRY(plan_alloc(p, (void**)&L->U, u1 * nbc * L->rc));
   BSE_TRY(plan_alloc(p, (void**)&L->G, g_r * L->rc));
   BSE_TRY(plan_alloc(p, (void**)&L->F, 8 * (size_t)L->f_doubles));
   BSE_TRY(plan_alloc(p, (void**)&L->t, 32 * (size_t)na * nbc));

@@ -118,3 +118,32 @@ def test_not_a_number_keeps_the_pair_route(bad, n_bad):
     Y = plan.apply(T(random_block(p.N, 2, seed=3))).cpu().numpy()
     plan.close()
     assert got == 0 and not np.isfinite(Y).all()
+
+
+@pytest.mark.parametrize("hermitian", [True, False])
+@pytest.mark.parametrize("mb", [400, 100, 60, 40, 20, 12])
+def test_workspace_limit(monkeypatch, hermitian, mb):
+    # N_ao 24, 512 k, 27 R, 8 vectors: kernels of 38 MB and as many partial sums, or contractions in passes; besides W(R)
+    # and two copies of C (with padded rows) no more than BSE_WORKSPACE_GB is held
+    from paper_2607_05853_amd import bse as B
+    p, W = crystal(dense=(8, 8, 8), no=24, na=48)
+    if not hermitian:
+        W = W + 0.1 * abs(W).max() * np.random.default_rng(4).standard_normal(W.shape[1:])
+    monkeypatch.setenv("BSE_WORKSPACE_GB", "%.9f" % (mb / 1024))
+    monkeypatch.setenv("BSE_QBATCH", "1")
+    cos = np.cos(8 * np.pi * dense_kmesh(p.nk)[:, 0])[:, None, None]   # R1 = +-4 of 8: one more R, beyond the box
+    pairs = B.plan_from_problem(p, T(W + 1e-6 * abs(W).max() * cos * np.eye(48)), prec="f64", max_nb=8)
+    plan = B.plan_from_problem(p, T(W), prec="f64", max_nb=8)
+    R = plan.lattice()
+    assert R == 27 and pairs.lattice() == 0
+    ldc = 48 * 24 + 16
+    held = plan.bytes - pairs.bytes - 8 * R * 48 * 48 - 2 * 16 * 24 * ldc
+    print("[workspace %d MB, hermitian %s] %.1f MB" % (mb, hermitian, held / 2 ** 20), flush=True)
+    X = random_block(p.N, 8, seed=3)
+    Y = plan.apply(T(X)).cpu().numpy()
+    pairs.close(), plan.close()
+    rows = [0, 100, 511]
+    ref = O.apply_H_rows_allpairs(p, W, X, rows)
+    got = np.concatenate([Y[k * 6:(k + 1) * 6] for k in rows])
+    assert kernel_err(got, ref, diag_times(p, X, rows)) < KERNEL_TOL["f64"]
+    assert held < mb * 2 ** 20 + 65536      # the phase tables
