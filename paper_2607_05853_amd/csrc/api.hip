@@ -275,10 +275,10 @@ bool valid_prec(int p) { return p == BSE_F64 || p == BSE_F32 || p == BSE_BF16X3;
 
 hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-// workspace bytes per q of a batch: Gv, P, T, and the conduction pair densities Mc unless the plan is
+// workspace bytes per q of a batch, in the sizes stored: Gv, P, T, and the conduction pair densities Mc unless the plan is
 // split (the BF16x3 apply never forms them; its adjoint allocates them on first use)
 size_t per_q_bytes(const Plan* p) {
-  const long long Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->given_aux;
+  const long long Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
   const size_t tc = p->two_centre ? (size_t)(p->prec == BSE_F64 ? 16 : 8) * 2 * (size_t)(Nk * (nv * nv + nc * nc) * na)
                                   : 0;
   return p->esz * (size_t)(Nk * nv * nv * na * 2 + (p->mc_direct ? Nk * nc * nc * na : 0) + Nk * nc * nc * nv * nv) +

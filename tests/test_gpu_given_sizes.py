@@ -54,3 +54,24 @@ def test_offset_average_refuses_other_sizes(other):
     for q in plans:
         q.close()
     assert e.value.status == ESHAPE
+
+
+@pytest.mark.parametrize("conduction", ["mc", "u"])
+@pytest.mark.parametrize("two_centre", [False, True])
+def test_batch_buffers_stay_below_the_limit(monkeypatch, conduction, two_centre):
+    # 17 auxiliary functions stored as 32: the q-batch buffers are those of the stored sizes, and they keep the limit
+    from paper_2607_05853_amd import bse as B
+    if two_centre and conduction == "u":
+        pytest.skip("two-centre plans form M_cc'")
+    p = make_problem(dict(cfg_id=76, coarse=(2, 2, 2), dense=(4, 4, 4), n_ao=10, nv=2, nc=3, n_aux=17), 0, "G2",
+                     two_centre=two_centre)
+    kw = dict(conduction=None if two_centre else conduction)
+    monkeypatch.setenv("BSE_QBATCH", "1")
+    one = plan_of(B, p, "bf16x3", **kw)
+    monkeypatch.delenv("BSE_QBATCH")
+    monkeypatch.setenv("BSE_WORKSPACE_GB", "%.9f" % (4 / 1024))
+    plan = plan_of(B, p, "bf16x3", **kw)
+    held = plan.bytes - one.bytes       # all but one q of the batch
+    one.close(), plan.close()
+    print("[batch buffers %s two-centre %s] %.2f MB" % (conduction, two_centre, held / 2 ** 20), flush=True)
+    assert held < 4 * 2 ** 20
