@@ -843,7 +843,7 @@ bse_dims rounded_dims(const bse_dims* d) {
 }
 
 // build_plan on the rounded sizes, from zero-padded copies of the inputs; on the sizes as given where they are
-// round, on the other precisions, and where the copies would not fit comfortably
+// round, on the other precisions, and where the copies or the larger plan would not fit
 bse_status build_rounded(Plan* p, const bse_dims* d, const double* eps_qp, const void* psi, const void* C,
                          const TwoCentreIn* tc, const void* Vbar, const void* W_q, bse_prec prec, int max_nb,
                          uint32_t flags, hipStream_t st) {
@@ -855,8 +855,17 @@ bse_status build_rounded(Plan* p, const bse_dims* d, const double* eps_qp, const
   if (!same) {
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
-    const size_t need = 16 * (n_psi + n_c * (tc ? (size_t)tc->nR : 1) + n_w * (Nk + 1));
-    same = need > free_b / 4;
+    const size_t copies = 16 * (n_psi + n_c * (tc ? (size_t)tc->nR : 1) + n_w * (Nk + 1));
+    // the rounded plan beside its copies: W_q, psi, the halves and rho, then the FP64 staging of the halves or the q batch
+    const size_t nv = d->nv, nc = d->nc, per_q = 8 * (size_t)Nk * ((2 * nv * nv + nc * nc) * r.n_aux + nc * nc * nv * nv) +
+                                                 (tc ? 16 * (size_t)Nk * (nv * nv + nc * nc) * r.n_aux : 0);
+    size_t batch = (size_t)12 << 30;
+    if (const char* e = std::getenv("BSE_WORKSPACE_GB")) batch = (size_t)std::max(0.0, std::atof(e) * (double)(1ull << 30));
+    batch = std::max(per_q, std::min(batch, per_q * (size_t)Nk));
+    const size_t staged = 16 * (size_t)Nk * (nv + nc) * r.n_aux * r.n_ao;
+    const size_t held = 8 * n_w * Nk + 32 * n_psi + staged / 2 + 8 * (size_t)Nk * nc * r.n_aux * r.n_ao +
+                        16 * (size_t)Nk * nv * nc * r.n_aux + std::max(batch, std::min<size_t>(staged, (size_t)2 << 30));
+    same = copies > free_b / 4 || (double)copies + (double)held > 0.95 * (double)free_b;
   }
   if (same) return build_plan(p, d, d, eps_qp, psi, C, tc, Vbar, W_q, prec, max_nb, flags, st);
   struct Copy {

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle as O
-from synth import dense_kmesh, make_problem, polarisations
+from synth import dense_kmesh, make_problem, polarisations, random_block
 
 pytestmark = pytest.mark.gpu
 ESHAPE = 2
@@ -75,3 +75,34 @@ def test_batch_buffers_stay_below_the_limit(monkeypatch, conduction, two_centre)
     one.close(), plan.close()
     print("[batch buffers %s two-centre %s] %.2f MB" % (conduction, two_centre, held / 2 ** 20), flush=True)
     assert held < 4 * 2 ** 20
+
+
+def test_plan_that_fits_only_in_the_given_sizes(monkeypatch):
+    # N_ao 97 stored as 128: about 2.5 GB while the plan is made, 1.7 GB in the given sizes, with 2.25 GB free
+    from paper_2607_05853_amd import bse as B
+    p = make_problem(dict(cfg_id=76, coarse=(2, 2, 2), dense=(6, 6, 6), n_ao=97, nv=4, nc=6, n_aux=250), 0, "G2")
+    t = lambda a, dt=torch.complex128: T(a, dt)
+    Wq = B.interpolate_W(T(p.W_R), p.R, p.w_R, dense_kmesh(p.nk))
+    args = (p.nk, p.n_ao, p.nv, p.nc, p.n_aux, t(p.eps_qp, torch.float64), t(p.psi), t(p.C), t(p.Vbar), Wq)
+    X = T(random_block(p.N, 2, seed=1))
+    Y = torch.empty_like(X)
+    monkeypatch.setenv("BSE_WORKSPACE_GB", "0.1")
+    plan = B.Plan(*args, prec="bf16x3", max_nb=2)
+    ref, rounded = plan.apply(X).clone(), plan.bytes
+    plan.close()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    left = int(2.25e9)
+    fill = [torch.empty(torch.cuda.mem_get_info()[0] - left - (1 << 30), dtype=torch.uint8, device="cuda:0")]
+    while torch.cuda.mem_get_info()[0] > left:
+        fill.append(torch.empty(32 << 20, dtype=torch.uint8, device="cuda:0"))
+    plan = B.Plan(*args, prec="bf16x3", max_nb=2)
+    given = plan.bytes
+    print("[given sizes] %.2f GB against %.2f rounded" % (given / 1e9, rounded / 1e9), flush=True)
+    plan.apply(X, out=Y)
+    torch.cuda.synchronize()
+    plan.close()
+    del fill
+    torch.cuda.empty_cache()
+    assert given < 0.9 * rounded
+    assert (Y - ref).abs().max() < 1e-12 * ref.abs().max()
