@@ -19,7 +19,7 @@ struct FtArgs {
   double q[3][FT_MAXQ];       // fractional q of each axis
   short Rv[3][FT_MAXR + 1];   // R components of each axis, ascending
   double w[FT_MAXNR];         // weight of each listed R
-  short map[FT_BOX];          // box slot (R1, R2, R3), the last two axes padded to 3, 5 or 7 -> listed R or -1
+  short map[FT_BOX];          // box slot (R1, R2, R3), the last two axes padded to odd sizes -> listed R or -1
 };
 static_assert(sizeof(FtArgs) <= 3600, "kernel argument");
 

@@ -5,22 +5,23 @@
 // 7 x 7 x 7.  One axis is summed after the other, so an 8x8x8 grid on a 5x5x5 box takes 10 complex products
 // per output instead of 125 and the sums are bound by reading the input and writing the output once.
 // At 8x8x8 on 5x5x5 with N_aux = 256 (668 MB in and out, 0.14 ms at the 4.4-5.1 TB/s of a large copy) the
-// spread takes 0.145-0.175 ms and the gather 0.188 ms (0.233 with the loads of a step only); the phase table and FP64 GEMM took 0.86 and 0.88 ms.  Nothing
-// is copied from the host or allocated: a 4x4x4 interpolation at N_aux = 64 takes 12 us against 43.
+// spread takes 0.145-0.175 ms and the gather 0.188 ms (0.233 with the loads of a step only); the phase table and FP64
+// GEMM took 0.86 and 0.88 ms.  Nothing is copied from the host or allocated: a 4x4x4 interpolation at N_aux = 64 takes
+// 12 us against 43.
 #include "bse_internal.h"
 #include "fourier.h"
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace bse {
 
 namespace {
-// the box of the last two axes as the kernels are instantiated: 3, 5 or 7 on a side
-int ft_square(const FtArgs& a) {
-  const int m = std::max(a.r[1], a.r[2]);
-  return m <= 3 ? 3 : (m <= 5 ? 5 : 7);
-}
+// the box of the last two axes as the kernels are instantiated: each 1, 3, 5 or 7 (with one size for both a plane of R
+// cost up to five times its sums: 12x12x1 q on 7x7x1 R, N_aux 300, spread 526 us with 7 x 7 and 60 with 7 x 1, gather 446
+// and 95; the phase table and GEMM 239 and 202)
+int ft_side(const FtArgs& a, int x) { return a.r[x] / 2 * 2 + 1; }
 }  // namespace
 
 bool ft_axes(FtArgs* a, int n_q, const double* q, int n_R, const int32_t* R, const double* w) {
@@ -62,7 +63,7 @@ bool ft_axes(FtArgs* a, int n_q, const double* q, int n_R, const int32_t* R, con
     a->r[x] = m;
     for (int s = 0; s < m; ++s) a->Rv[x][s] = (short)v[s];
   }
-  const int ns = ft_square(*a);
+  const int ny = ft_side(*a, 1), nz = ft_side(*a, 2);
   for (int s = 0; s < FT_BOX; ++s) a->map[s] = -1;
   for (int r = 0; r < n_R; ++r) {
     int s[3];
@@ -70,7 +71,7 @@ bool ft_axes(FtArgs* a, int n_q, const double* q, int n_R, const int32_t* R, con
       s[x] = 0;
       while (a->Rv[x][s[x]] != R[3 * r + x]) ++s[x];
     }
-    short& slot = a->map[(s[0] * ns + s[1]) * ns + s[2]];
+    short& slot = a->map[(s[0] * ny + s[1]) * nz + s[2]];
     if (slot >= 0) return false;  // a vector listed twice
     slot = (short)r;
     a->w[r] = w ? w[r] : 1.0;
@@ -95,20 +96,18 @@ __device__ __forceinline__ void store_nt(double2* p, const Z v) {
   __builtin_nontemporal_store(dbl2{v.x, v.y}, reinterpret_cast<dbl2*>(p));
 }
 
-// exp(sign 2 pi i q R) of each axis, [q][NS] per axis (columns beyond the axis' R are zero), the three axes after each
-// other in LDS; from a table made once where the caller keeps one (the sines take 2 us of a small sum)
-template <int NS>
-__device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, const double2* __restrict__ tab, double2* p1,
-                                          double2* p2, double2* p3) {
+// exp(sign 2 pi i q R) of each axis, [q][7], [q][ny] and [q][nz] (columns beyond the axis' R are zero), the three axes
+// after each other in LDS; from a table made once where the caller keeps one (the sines take 2 us of a small sum)
+__device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, const double2* __restrict__ tab, int ny, int nz,
+                                          double2* p1) {
   if (tab) {
-    const int n = a.n[0] * FT_MAXR + (a.n[1] + a.n[2]) * NS;
+    const int n = a.n[0] * FT_MAXR + a.n[1] * ny + a.n[2] * nz;
     for (int t = threadIdx.x; t < n; t += blockDim.x) p1[t] = tab[t];
     __syncthreads();
     return;
   }
   for (int x = 0; x < 3; ++x) {
-    double2* p = x == 0 ? p1 : (x == 1 ? p2 : p3);
-    const int ns = x == 0 ? FT_MAXR : NS;
+    const int ns = x == 0 ? FT_MAXR : (x == 1 ? ny : nz);
     for (int t = threadIdx.x; t < a.n[x] * ns; t += blockDim.x) {
       const int i = t / ns, r = t % ns;
       double2 v = {0.0, 0.0};
@@ -117,20 +116,27 @@ __device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, const do
         y -= rint(y);
         sincospi(2.0 * sign * y, &v.y, &v.x);
       }
-      p[t] = v;
+      p1[t] = v;
     }
+    p1 += a.n[x] * ns;
   }
   __syncthreads();
 }
 
+// Few q1 leave rows of threads without one: the pairs of q2 of each q1 are then shared between this many of them (by the
+// spread where there are more than four rows per q1, by the gather from two on: with fewer the sharing costs what it gives).
+__host__ __device__ __forceinline__ int ft_parts(int rows, int n1, int n2) {
+  return std::min(std::max(1, rows / n1), (n2 + 1) / 2);
+}
+
 // Spread.  A block stages in[R][te consecutive e] (weighted) in LDS, the whole tile's loads in flight together
-// and each input read from memory once; a thread owns one e and every (256 / te)-th q1.  For its q1 it sums the
-// R1 axis into A[R2][R3] in registers, then two q2 at a time into B[R3], so that each LDS read of a phase of the
-// last axis serves two outputs.
+// and each input read from memory once; a thread owns one e and every (256 / te)-th q1 (or part of its q2).  For its q1
+// it sums the R1 axis into A[R2][R3] in registers, then two q2 at a time into B[R3], so that each LDS read of a phase of
+// the last axis serves two outputs.
 // MODE 0: c128 out, 1: c64 out, 2: max |sum - ref| (component-wise) into out as a non-negative double's bits.
 // Input: c128 rows of E (planar = 0), or re / im planes per group of `group` elements, [R][E / group][2][group],
 // summed over nsplit partial arrays split_stride apart.
-template <int NS, int MODE>
+template <int NY, int NZ, int MODE>
 __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, const double* __restrict__ in,
                                                  long long E, int planar, long long group, int nsplit,
                                                  long long split_stride, void* __restrict__ out,
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
   double2* const W = ft_lds;  // [nR + 1][te], the last row zero (the box slots without an R)
   double2* const p1 = W + (a.nR + 1) * te;
   double2* const p2 = p1 + n1 * FT_MAXR;
-  double2* const p3 = p2 + n2 * NS;
+  double2* const p3 = p2 + n2 * NY;
   const long long e0 = (long long)blockIdx.x * te;
 #pragma unroll 8
   for (int t = threadIdx.x; t < a.nR * te; t += blockDim.x) {
@@ -162,38 +168,39 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
     W[t] = double2{a.w[r] * v.x, a.w[r] * v.y};
   }
   for (int t = threadIdx.x; t < te; t += blockDim.x) W[a.nR * te + t] = double2{0.0, 0.0};
-  ft_phases<NS>(a, sign, tab, p1, p2, p3);
-  const int el = threadIdx.x % te, qstep = blockDim.x / te;
+  ft_phases(a, sign, tab, NY, NZ, p1);
+  const int el = threadIdx.x % te, qstep = blockDim.x / te, parts = qstep / n1 > 4 ? ft_parts(qstep, n1, n2) : 1;
   const long long e = e0 + el;
   double dmax = 0.0;
-  for (int i1 = threadIdx.x / te; i1 < n1 && e < E; i1 += qstep) {
-    Z A[NS][NS];
+  for (int it = threadIdx.x / te; it < n1 * parts && e < E; it += qstep) {
+    const int i1 = it / parts;
+    Z A[NY][NZ];
 #pragma unroll
-    for (int y = 0; y < NS; ++y)
+    for (int y = 0; y < NY; ++y)
 #pragma unroll
-      for (int z = 0; z < NS; ++z) A[y][z] = Z{0.0, 0.0};
+      for (int z = 0; z < NZ; ++z) A[y][z] = Z{0.0, 0.0};
     for (int x = 0; x < a.r[0]; ++x) {
       const double2 p = p1[i1 * FT_MAXR + x];
-      const short* map = a.map + x * NS * NS;
+      const short* map = a.map + x * NY * NZ;
 #pragma unroll
-      for (int y = 0; y < NS; ++y)
+      for (int y = 0; y < NY; ++y)
 #pragma unroll
-        for (int z = 0; z < NS; ++z) {
-          const int r = map[y * NS + z];
+        for (int z = 0; z < NZ; ++z) {
+          const int r = map[y * NZ + z];
           const double2 v = W[(r < 0 ? a.nR : r) * te + el];
           fma_z(A[y][z], p, Z{v.x, v.y});
         }
     }
-    for (int j = 0; j < n2; j += 2) {
+    for (int j = 2 * (it % parts); j < n2; j += 2 * parts) {
       const int j2 = j + 1 < n2 ? j + 1 : j;
-      Z B0[NS], B1[NS];
+      Z B0[NZ], B1[NZ];
 #pragma unroll
-      for (int z = 0; z < NS; ++z) B0[z] = B1[z] = Z{0.0, 0.0};
+      for (int z = 0; z < NZ; ++z) B0[z] = B1[z] = Z{0.0, 0.0};
 #pragma unroll
-      for (int y = 0; y < NS; ++y) {
-        const double2 pa = p2[j * NS + y], pb = p2[j2 * NS + y];
+      for (int y = 0; y < NY; ++y) {
+        const double2 pa = p2[j * NY + y], pb = p2[j2 * NY + y];
 #pragma unroll
-        for (int z = 0; z < NS; ++z) {
+        for (int z = 0; z < NZ; ++z) {
           fma_z(B0[z], pa, A[y][z]);
           fma_z(B1[z], pb, A[y][z]);
         }
@@ -201,8 +208,8 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
       for (int k = 0; k < n3; ++k) {
         Z s0{0.0, 0.0}, s1{0.0, 0.0};
 #pragma unroll
-        for (int z = 0; z < NS; ++z) {
-          const double2 p = p3[k * NS + z];
+        for (int z = 0; z < NZ; ++z) {
+          const double2 p = p3[k * NZ + z];
           fma_z(s0, p, B0[z]);
           fma_z(s1, p, B1[z]);
         }
@@ -231,35 +238,47 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
   }
 }
 
-// Gather.  A thread owns one e (te per block, rows of 16 te bytes) and one q1 of a round of 256 / te: it reads
-// each input once and sums the last two axes into D[R2][R3] in registers, two q2 and four q3 at a time (each phase
+// R2 of D that go through LDS at a time: all of a small box (fewer barriers: 12x12x1 on 7x7x1, N_aux 300, 118 -> 95 us),
+// one of a larger
+constexpr int ft_turn(int ny, int nz) { return ny * nz <= 9 ? ny : 1; }
+
+// Gather.  A thread owns one e (te per block, rows of 16 te bytes) and one q1 (or part of its q2) of a round of 256 / te:
+// it reads each input once and sums the last two axes into D[R2][R3] in registers, two q2 and four q3 at a time (each phase
 // read serves two products, the next step's eight loads are in flight).  The R1 axis is then summed over the round's
-// q1 through LDS, one R2 at a time, with the first loads of the block's next round or tile in flight; rounds after the
+// q1 through LDS, with the first loads of the block's next round or tile in flight; rounds after the
 // first add to the outputs the same thread wrote before.
 // Output: c128 rows of E, or re and im planes of E each ([R][2][E]) when planar.
-template <int NS>
-__global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, const double* __restrict__ in,
-                                                 long long E, int planar, double* __restrict__ out,
-                                                 const double2* tab) {
+// SPLIT: q2 shared between rows (without it what depends on the part is known, and stays in scalar registers).
+template <int NY, int NZ, bool SPLIT>
+__global__ __launch_bounds__(256, NY * NZ <= 25 ? 2 : 1) void ft_gather(FtArgs a, double sign, int te,
+                                                                        const double* __restrict__ in, long long E,
+                                                                        int planar, double* __restrict__ out,
+                                                                        const double2* tab) {
   extern __shared__ double2 ft_lds[];
   const int n1 = a.n[0], n2 = a.n[1], n3 = a.n[2];
   const int el = threadIdx.x % te, ql = threadIdx.x / te, nq = blockDim.x / te;
-  double2* const X = ft_lds;  // [nq][NS][te], one R2 of D
-  double2* const p1 = X + nq * NS * te;
+  constexpr int YB = ft_turn(NY, NZ);
+  double2* const X = ft_lds;  // [nq][YB][NZ][te], YB R2 of D
+  double2* const p1 = X + nq * YB * NZ * te;
   double2* const p2 = p1 + n1 * FT_MAXR;
-  double2* const p3 = p2 + n2 * NS;
+  double2* const p3 = p2 + n2 * NY;
   long long e = (long long)blockIdx.x * te + el;  // of the tile in hand, which starts at e - el < E
-  int i0 = 0;
-  const int nk = (n3 + 3) / 4, steps = (n2 + 1) / 2 * nk;
+  // row i of a round: q1 i / parts, part i % parts of its q2
+  const int parts = SPLIT ? ft_parts(nq / 2, n1, n2) : 1, rows = n1 * parts;
+  int i0 = 0, part = 0, steps = 0;
+  const int nk = (n3 + 3) / 4;
   const double2* g;
   bool on;  // the thread has a column in this round
   auto place = [&](long long e, int i0) {
-    on = i0 + ql < n1 && e < E;
-    g = reinterpret_cast<const double2*>(in) + (long long)(on ? i0 + ql : 0) * n2 * n3 * E + (on ? e : 0);
+    on = i0 + ql < rows && e < E;
+    const int i = on ? i0 + ql : 0;
+    part = SPLIT ? i % parts : 0;
+    steps = ((n2 + 1) / 2 - part + parts - 1) / parts * nk;
+    g = reinterpret_cast<const double2*>(in) + (long long)(i / parts) * n2 * n3 * E + (on ? e : 0);
   };
   double2 u[2][4], v[2][4];
   auto load = [&](int o, int s) {
-    const int j = 2 * (s / nk), k0 = 4 * (s % nk);
+    const int j = 2 * (part + s / nk * parts), k0 = 4 * (s % nk);
     const double2* ga = g + (long long)j * n3 * E;
     const double2* gb = j + 1 < n2 ? ga + (long long)n3 * E : ga;
 #pragma unroll
@@ -271,27 +290,27 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
   };
   place(e, i0);
   if (on) load(0, 0);
-  ft_phases<NS>(a, sign, tab, p1, p2, p3);
+  ft_phases(a, sign, tab, NY, NZ, p1);
   while (e - el < E) {
-    Z D[NS][NS];
+    Z D[NY][NZ];
 #pragma unroll
-    for (int y = 0; y < NS; ++y)
+    for (int y = 0; y < NY; ++y)
 #pragma unroll
-      for (int z = 0; z < NS; ++z) D[y][z] = Z{0.0, 0.0};
+      for (int z = 0; z < NZ; ++z) D[y][z] = Z{0.0, 0.0};
     if (on) {
-      Z C0[NS], C1[NS];
+      Z C0[NZ], C1[NZ];
       auto step = [&](int o, int s) {
-        const int j = 2 * (s / nk), k0 = 4 * (s % nk);
+        const int j = 2 * (part + s / nk * parts), k0 = 4 * (s % nk);
         if (k0 == 0) {
 #pragma unroll
-          for (int z = 0; z < NS; ++z) C0[z] = C1[z] = Z{0.0, 0.0};
+          for (int z = 0; z < NZ; ++z) C0[z] = C1[z] = Z{0.0, 0.0};
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           if (k0 + k >= n3) break;
 #pragma unroll
-          for (int z = 0; z < NS; ++z) {
-            const double2 p = p3[(k0 + k) * NS + z];
+          for (int z = 0; z < NZ; ++z) {
+            const double2 p = p3[(k0 + k) * NZ + z];
             fma_z(C0[z], p, Z{u[o][k].x, u[o][k].y});
             fma_z(C1[z], p, Z{v[o][k].x, v[o][k].y});
           }
@@ -300,13 +319,13 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
         const bool two = j + 1 < n2;
         if (!two) {
 #pragma unroll
-          for (int z = 0; z < NS; ++z) C1[z] = Z{0.0, 0.0};
+          for (int z = 0; z < NZ; ++z) C1[z] = Z{0.0, 0.0};
         }
 #pragma unroll
-        for (int y = 0; y < NS; ++y) {
-          const double2 pa = p2[j * NS + y], pb = p2[(two ? j + 1 : j) * NS + y];
+        for (int y = 0; y < NY; ++y) {
+          const double2 pa = p2[j * NY + y], pb = p2[(two ? j + 1 : j) * NY + y];
 #pragma unroll
-          for (int z = 0; z < NS; ++z) {
+          for (int z = 0; z < NZ; ++z) {
             fma_z(D[y][z], pa, C0[z]);
             fma_z(D[y][z], pb, C1[z]);
           }
@@ -320,26 +339,29 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
         step(1, s + 1);
       }
     }
-    const bool same = i0 + nq < n1;
+    const bool same = i0 + nq < rows;
     const long long e2 = same ? e : e + (long long)gridDim.x * te;
     place(e2, same ? i0 + nq : 0);
     if (on) load(0, 0);
-    const int live = min(nq, n1 - i0);
+    const int live = min(nq, rows - i0);
 #pragma unroll
-    for (int y = 0; y < NS; ++y) {
-      if (y >= a.r[1]) break;
+    for (int y0 = 0; y0 < NY; y0 += YB) {
+      if (y0 >= a.r[1]) break;
       __syncthreads();
 #pragma unroll
-      for (int z = 0; z < NS; ++z) X[(ql * NS + z) * te + el] = double2{D[y][z].x, D[y][z].y};
+      for (int y = 0; y < YB; ++y)
+#pragma unroll
+        for (int z = 0; z < NZ; ++z) X[((ql * YB + y) * NZ + z) * te + el] = double2{D[y0 + y][z].x, D[y0 + y][z].y};
       __syncthreads();
-      for (int it = ql; it < a.r[0] * a.r[2]; it += nq) {
-        const int x = it / a.r[2], z = it % a.r[2];
-        const int r = a.map[(x * NS + y) * NS + z];
+      const int ny = YB == 1 ? 1 : a.r[1];
+      for (int it = ql; it < a.r[0] * ny * a.r[2]; it += nq) {
+        const int z = it % a.r[2], xy = it / a.r[2], x = xy / ny, y = YB == 1 ? 0 : xy % ny;
+        const int r = a.map[(x * NY + y0 + y) * NZ + z];
         if (r < 0 || e >= E) continue;
         Z s{0.0, 0.0};
         for (int q = 0; q < live; ++q) {
-          const double2 v = X[(q * NS + z) * te + el];
-          fma_z(s, p1[(i0 + q) * FT_MAXR + x], Z{v.x, v.y});
+          const double2 v = X[((q * YB + y) * NZ + z) * te + el];
+          fma_z(s, p1[(i0 + q) / parts * FT_MAXR + x], Z{v.x, v.y});
         }
         const double w = a.w[r];
         double* o = out + 2 * (long long)r * E;
@@ -354,39 +376,30 @@ __global__ __launch_bounds__(256) void ft_gather(FtArgs a, double sign, int te, 
   }
 }
 
-template <int NS>
-__global__ __launch_bounds__(256) void ft_table(FtArgs a, double sign, double2* __restrict__ out) {
+__global__ __launch_bounds__(256) void ft_table(FtArgs a, double sign, int ny, int nz, double2* __restrict__ out) {
   extern __shared__ double2 ft_lds[];
-  double2* const p2 = ft_lds + a.n[0] * FT_MAXR;
-  ft_phases<NS>(a, sign, nullptr, ft_lds, p2, p2 + a.n[1] * NS);
-  const int n = a.n[0] * FT_MAXR + (a.n[1] + a.n[2]) * NS;
+  ft_phases(a, sign, nullptr, ny, nz, ft_lds);
+  const int n = a.n[0] * FT_MAXR + a.n[1] * ny + a.n[2] * nz;
   for (int t = threadIdx.x; t < n; t += blockDim.x) out[t] = ft_lds[t];
 }
 
-template <int NS, int MODE>
-bse_status spread_go(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
-                     int nsplit, long long split_stride, void* out, const double* ref, const double2* tab, hipStream_t st) {
-  // 32 e per block (512-byte rows) while the tile leaves room for two blocks on a CU, 16 for the larger R sets
-  // and while 32 would leave CUs without a block
-  const int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
-  const int bs = 256;
-  const size_t lds = 16 * ((size_t)(a.nR + 1) * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * NS);
-  if (lds > 64 * 1024)
-    BSE_HIP(hipFuncSetAttribute((const void*)ft_spread<NS, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                160 * 1024));
-  hipLaunchKernelGGL((ft_spread<NS, MODE>), dim3((unsigned)((E + te - 1) / te)), dim3(bs), lds, st, a, sign, te, in, E,
-                     planar, group, nsplit, split_stride, out, ref, tab);
-  BSE_CHECK_LAUNCH();
-  return BSE_OK;
-}
-
-template <int NS>
-bse_status spread_ns(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
-                     int nsplit, long long split_stride, int mode, void* out, const double* ref, const double2* tab,
-                     hipStream_t st) {
-  if (mode == 0) return spread_go<NS, 0>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
-  if (mode == 1) return spread_go<NS, 1>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
-  return spread_go<NS, 2>(a, sign, in, E, planar, group, nsplit, split_stride, out, ref, tab, st);
+// go(NY, NZ) with the box of the last two axes as constants
+template <typename F>
+bse_status with_sides(const FtArgs& a, F go) {
+  auto one = [&](auto ny) -> bse_status {
+    switch (ft_side(a, 2)) {
+      case 1: return go(ny, std::integral_constant<int, 1>());
+      case 3: return go(ny, std::integral_constant<int, 3>());
+      case 5: return go(ny, std::integral_constant<int, 5>());
+      default: return go(ny, std::integral_constant<int, 7>());
+    }
+  };
+  switch (ft_side(a, 1)) {
+    case 1: return one(std::integral_constant<int, 1>());
+    case 3: return one(std::integral_constant<int, 3>());
+    case 5: return one(std::integral_constant<int, 5>());
+    default: return one(std::integral_constant<int, 7>());
+  }
 }
 
 }  // namespace
@@ -394,46 +407,57 @@ bse_status spread_ns(const FtArgs& a, double sign, const double* in, long long E
 bse_status ft_spread_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, long long group,
                             int nsplit, long long split_stride, int mode, void* out, const double* ref,
                             hipStream_t st, const double* table) {
-  const int ns = ft_square(a);
   const double2* tab = reinterpret_cast<const double2*>(table);
-  if (ns <= 3) return spread_ns<3>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
-  if (ns <= 5) return spread_ns<5>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
-  return spread_ns<7>(a, sign, in, E, planar, group, nsplit, split_stride, mode, out, ref, tab, st);
+  // 32 e per block (512-byte rows) while the tile leaves room for two blocks on a CU, 16 for the larger R sets
+  // and while 32 would leave CUs without a block
+  const int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
+  const size_t lds = 16 * (size_t)(a.nR + 1) * te + ft_table_bytes(a);
+  const dim3 grid((unsigned)((E + te - 1) / te));
+  return with_sides(a, [&](auto ny, auto nz) -> bse_status {
+    auto go = [&](auto kern) -> bse_status {
+      if (lds > 64 * 1024)
+        BSE_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+      hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, sign, te, in, E, planar, group, nsplit, split_stride, out,
+                         ref, tab);
+      BSE_CHECK_LAUNCH();
+      return BSE_OK;
+    };
+    constexpr int NY = decltype(ny)::value, NZ = decltype(nz)::value;
+    return mode == 0 ? go(ft_spread<NY, NZ, 0>) : mode == 1 ? go(ft_spread<NY, NZ, 1>) : go(ft_spread<NY, NZ, 2>);
+  });
 }
 
 bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long long E, int planar, double* out,
                             hipStream_t st, const double* table) {
-  const int ns = ft_square(a);
   const double2* tab = reinterpret_cast<const double2*>(table);
-  // as the spread: 32 e per block while that leaves every CU two blocks
-  const int te = E >= 32 * 512 ? 32 : 16;
-  const int bs = 256;
-  const size_t lds = 16 * ((size_t)(bs / te) * ns * te + (size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ns);
-  // two blocks per CU (their registers allow no more), each over its share of the tiles
-  const dim3 grid((unsigned)std::min<long long>(512, (E + te - 1) / te)), block(bs);
-  if (ns <= 3)
-    hipLaunchKernelGGL(ft_gather<3>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
-  else if (ns <= 5)
-    hipLaunchKernelGGL(ft_gather<5>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
-  else
-    hipLaunchKernelGGL(ft_gather<7>, grid, block, lds, st, a, sign, te, in, E, planar, out, tab);
-  BSE_CHECK_LAUNCH();
-  return BSE_OK;
+  // as the spread: 32 e per block while that leaves every CU two blocks; 16 where all q1 are then in one round (12x12x12 on
+  // 5x5x5, N_aux 200: 317 -> 262 us); more for fewer than five q1 while 448 blocks are left (1x10x2 on 1x5x3, N_aux 394: 70
+  // us with 32, the GEMM 46, and below that with 256)
+  int te = E >= 32 * 512 && !(a.n[0] > 8 && a.n[0] <= 16) ? 32 : 16;
+  while (te >= 32 && te < 256 && 256 / te >= 2 * a.n[0] && E >= 2 * te * 448) te *= 2;
+  const int ny = ft_side(a, 1), nz = ft_side(a, 2);
+  const size_t lds = 16 * (size_t)256 * ft_turn(ny, nz) * nz + ft_table_bytes(a);
+  return with_sides(a, [&](auto ny, auto nz) -> bse_status {
+    constexpr int NY = decltype(ny)::value, NZ = decltype(nz)::value;
+    // as many blocks as the registers allow on the CUs (two for the boxes of 5 x 5), each over its share of the tiles
+    constexpr int PER_CU = NY * NZ <= 3 ? 4 : NY * NZ <= 9 && NZ < 7 ? 3 : 2;
+    const dim3 grid((unsigned)std::min<long long>(256 * PER_CU, (E + te - 1) / te));
+    if (ft_parts(256 / te / 2, a.n[0], a.n[1]) > 1)
+      hipLaunchKernelGGL((ft_gather<NY, NZ, true>), grid, dim3(256), lds, st, a, sign, te, in, E, planar, out, tab);
+    else
+      hipLaunchKernelGGL((ft_gather<NY, NZ, false>), grid, dim3(256), lds, st, a, sign, te, in, E, planar, out, tab);
+    BSE_CHECK_LAUNCH();
+    return BSE_OK;
+  });
 }
 
 size_t ft_table_bytes(const FtArgs& a) {
-  return 16 * ((size_t)a.n[0] * FT_MAXR + (size_t)(a.n[1] + a.n[2]) * ft_square(a));
+  return 16 * ((size_t)a.n[0] * FT_MAXR + (size_t)a.n[1] * ft_side(a, 1) + (size_t)a.n[2] * ft_side(a, 2));
 }
 
 bse_status ft_table_launch(const FtArgs& a, double sign, double* out, hipStream_t st) {
-  const int ns = ft_square(a);
-  const size_t lds = ft_table_bytes(a);
-  if (ns <= 3)
-    hipLaunchKernelGGL(ft_table<3>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
-  else if (ns <= 5)
-    hipLaunchKernelGGL(ft_table<5>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
-  else
-    hipLaunchKernelGGL(ft_table<7>, dim3(1), dim3(256), lds, st, a, sign, (double2*)out);
+  hipLaunchKernelGGL(ft_table, dim3(1), dim3(256), ft_table_bytes(a), st, a, sign, ft_side(a, 1), ft_side(a, 2),
+                     (double2*)out);
   BSE_CHECK_LAUNCH();
   return BSE_OK;
 }
