@@ -2754,7 +2754,7 @@ bse_status cgemm_split(const GemmArgs& g, bool a_split, bool b_split, bool c_spl
       BSE_CHECK_LAUNCH();
       return BSE_OK;
     }
-    if (!c_split && g.M > 64 && g.N <= 64) {  // taller per-pair products: 128 x 64 tiles
+    if (!c_split && g.M > 64 && g.N <= 64 && wide_tiles_enabled()) {  // taller per-pair products: 128 x 64 tiles
       const long long tiles = (long long)((g.M + 127) / 128) * g.batch;
       if (tiles < (1LL << 31)) {
         auto go = [&](auto kern) -> bse_status {
