@@ -247,7 +247,9 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
  * the inputs stays below a fifth of the memory free at plan creation and below
  * BSE_WORKSPACE_GB (the contractions take one vector and one R at a time in less);
  * a plan that finds no room for it forms pairs.  The forms' sums run in different
- * orders: results agree to FP64 rounding, not bit for bit. */
+ * orders: results agree to FP64 rounding, not bit for bit.  BSE_LATTICE=0 in the
+ * environment at plan creation keeps the pairs, BSE_LATTICE=contract takes
+ * the contractions whatever they cost. */
 bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R);
 
 /* Device bytes held by the plan (copies, halves and workspaces). */

@@ -35,6 +35,7 @@ namespace bse {
 struct Lattice {
   FtArgs ax;                 // the active R on the dense mesh, unit weights
   int nR = 0, r0 = 0;        // r0: index of R = 0
+  bool forced = false;       // taken for every block of vectors (BSE_LATTICE)
   double* Wr = nullptr;      // [nR][n_aux][n_aux], with kernels W(R), else W(R)^T
   // constants with padded rows: n_aux n_ao doubles is often a power of two, whose rows all start in one L2 channel
   long long ldc = 0;
@@ -863,6 +864,7 @@ void lattice_free(Plan* p) {
 // 1.5 times because its GEMMs of a few rows per pair run at 33 TFLOP/s (8x8x8 workload) against 56 here
 bool lattice_applies(const Plan* p, int nb) {
   if (!p->lat) return false;
+  if (p->lat->forced) return true;
   const int nR = p->lat->nR;
   return (p->lat->K ? secs_kernel(p, nR, nb) : secs_gemm(p, nR, nb)) < secs_pairs(p);
 }
@@ -976,6 +978,11 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   const bse_dims& d = p->d;
   const int Nk = p->Nk, na = d.n_aux, no = d.n_ao;
   const long long n2 = (long long)na * na, nc1 = (long long)na * no * no;
+  // BSE_LATTICE in the environment at plan creation: 0 keeps the pair route, contract takes the contractions whatever
+  // they cost (to time and compare)
+  const char* const form = std::getenv("BSE_LATTICE");
+  if (form && form[0] == '0') return BSE_OK;
+  const bool forced = form && form[0] == 'c';
   if (lds_outer(p) > 64 * 1024 || lds_project(p) > 64 * 1024 || na > 3000) return BSE_OK;
   std::vector<int32_t> R;
   int lo[3], hi[3];
@@ -996,7 +1003,7 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   // worth looking at only if a small set would win for one vector
   {
     const int few = std::min(nbox, 7);
-    if (std::min(secs_gemm(p, few, 1), secs_kernel(p, few, 1)) > secs_pairs(p)) return BSE_OK;
+    if (!forced && std::min(secs_gemm(p, few, 1), secs_kernel(p, few, 1)) > secs_pairs(p)) return BSE_OK;
   }
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
@@ -1045,6 +1052,7 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   p->lat = L;
   L->ax = ax;
   L->nR = nR;
+  L->forced = forced;
   for (int r = 0; r < nR; ++r)
     if (act[3 * r] == 0 && act[3 * r + 1] == 0 && act[3 * r + 2] == 0) L->r0 = r;
   // the R in pairs, R = 0 first
@@ -1064,9 +1072,9 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   auto kernel_bytes = [&](int b) {  // for b vectors at a time
     return kx_bytes(p, nh) + 8 * kx_part(nh, kx_tiles(p), b) + 16 * no2 * b * ((size_t)Nk + 2 * (size_t)nR);
   };
-  bool kernels = 2 * nh - 1 == nR && kx_bytes(p, nh) <= most && kernel_bytes(std::min(8, p->max_nb)) <= limit &&
+  bool kernels = !forced && 2 * nh - 1 == nR && kx_bytes(p, nh) <= most && kernel_bytes(std::min(8, p->max_nb)) <= limit &&
                  secs_kernel(p, nR, p->max_nb) < secs_gemm(p, nR, p->max_nb);
-  if (!((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) return BSE_OK;
+  if (!forced && !((kernels ? secs_kernel(p, nR, 1) : secs_gemm(p, nR, 1)) < secs_pairs(p))) return BSE_OK;
   BSE_TRY(plan_alloc(p, (void**)&L->Wr, 8 * (size_t)nR * n2));
   BSE_TRY(dmalloc(&idx.p, 4 * (size_t)nR));
   BSE_TRY(dmalloc(&chk.p, 16 * (size_t)nR * n2));
