@@ -30,6 +30,23 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 CONDUCTION = None  # BF16x3 conduction route ("mc", "u" or the plan's choice)
+
+
+class pair_form:
+    """Plans created inside form blocks of pairs (k, k') at every precision: F_apply counts that evaluation, and FP64 plans
+    would otherwise sum over lattice vectors, whose rate on F_apply means nothing."""
+
+    def __enter__(self):
+        self.old = os.environ.get("BSE_LATTICE")
+        os.environ["BSE_LATTICE"] = "0"
+
+    def __exit__(self, *exc):
+        if self.old is None:
+            del os.environ["BSE_LATTICE"]
+        else:
+            os.environ["BSE_LATTICE"] = self.old
+
+
 PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "bf16x3": 2516.6 / 3.0}
 METRIC = "BSE H\u00b7X GFLOP/s & %MFMA peak, mixed vs FP64 at \u22641e-5 rel. spectrum error"
 # default workload of each mode
@@ -208,8 +225,9 @@ def spectrum_mode(args):
 
     def step(prec, timing=False):
         Wq = B.interpolate_W(d_WR, p.R, p.w_R, kq)
-        plan = B.Plan(p.nk, p.n_ao, p.nv, p.nc, p.n_aux, d_eps, d_psi, d_C, d_V, Wq, alpha=p.alpha,
-                      prec=prec, max_nb=nb, conduction=CONDUCTION if prec == "bf16x3" else None)
+        with pair_form():
+            plan = B.Plan(p.nk, p.n_ao, p.nv, p.nc, p.n_aux, d_eps, d_psi, d_C, d_V, Wq, alpha=p.alpha,
+                          prec=prec, max_nb=nb, conduction=CONDUCTION if prec == "bf16x3" else None)
         plan.set_R(p.R, p.w_R)
         if timing:
             plan.set_timing(True)
@@ -394,7 +412,8 @@ def apply_mode(args):
             (pr, time.time() - t, plan.bytes / 2**30, plan.pairs, plan.conduction))
         return plan
 
-    plan = make_plan(prec)
+    with pair_form():
+        plan = make_plan(prec)
     for _ in range(args.warmup):
         plan.apply(X, out=Y)
     sync()
@@ -462,21 +481,36 @@ def apply_mode(args):
     prec_rec = {prec: {"apply_s": dt, "GFLOP_s": value}}
     speedup = None
     if not args.no_f64 and prec != "f64":
-        plan = make_plan("f64")
-        Y64 = torch.empty_like(X)
-        plan.set_timing(True)
-        plan.stage_times()
-        sync()
-        t0 = time.time()
-        plan.apply(X, out=Y64)
-        sync()
-        t64 = time.time() - t0
-        st64 = {k: round(v[0], 1) for k, v in plan.stage_times().items() if v[1] > 0}
-        plan.close()
-        del plan
-        torch.cuda.empty_cache()
-        log("f64 apply %.2f s" % t64)
+        def apply_f64():
+            plan = make_plan("f64")
+            out = torch.empty_like(X)
+            n_R = plan.lattice()
+            if n_R:
+                plan.apply(X, out=out)   # a fraction of a second: timed warm
+            plan.set_timing(True)
+            plan.stage_times()
+            sync()
+            t0 = time.time()
+            plan.apply(X, out=out)
+            sync()
+            t = time.time() - t0
+            st = {k: round(v[0], 1) for k, v in plan.stage_times().items() if v[1] > 0}
+            plan.close()
+            del plan
+            torch.cuda.empty_cache()
+            log("f64 apply %.2f s (%s)" % (t, "%d lattice vectors" % n_R if n_R else "pairs"))
+            return out, t, st, n_R
+
+        with pair_form():
+            Y64, t64, st64, _ = apply_f64()
         prec_rec["f64"] = {"apply_s": t64, "GFLOP_s": Fa / t64 / 1e9, "stage_ms": st64}
+        # what an FP64 plan takes by itself: the sum over lattice vectors, another evaluation than the one F_apply counts
+        YL, tL, stL, n_R = apply_f64()
+        if n_R:
+            prec_rec["f64_lattice"] = {"apply_s": tL, "n_R": n_R, "stage_ms": stL,
+                                       "kernel_rel_err_vs_f64_pairs": ((YL - Y64).abs().max() /
+                                                                       (Y64 - DX).abs().max()).item()}
+        del YL
         speedup = t64 / dt
         acc["kernel_rel_err_vs_f64_gpu"] = ((Y - Y64).abs().max() / (Y64 - DX).abs().max()).item()
         if orc is not None:
@@ -570,8 +604,9 @@ def precision_mode(config, m):
     Yref = Sref = None
     for prec in ["f64", "bf16x3", "f32"]:
         Wq = B.interpolate_W(W_R, p.R, p.w_R, kq)
-        plan = B.Plan(p.nk, p.n_ao, p.nv, p.nc, p.n_aux, eps, T(p.psi), T(p.C), T(p.Vbar), Wq, alpha=p.alpha,
-                      prec=prec, max_nb=nb, conduction=CONDUCTION if prec == "bf16x3" else None)
+        with pair_form():
+            plan = B.Plan(p.nk, p.n_ao, p.nv, p.nc, p.n_aux, eps, T(p.psi), T(p.C), T(p.Vbar), Wq, alpha=p.alpha,
+                          prec=prec, max_nb=nb, conduction=CONDUCTION if prec == "bf16x3" else None)
         del Wq
         torch.cuda.synchronize()
         t0 = time.time()
