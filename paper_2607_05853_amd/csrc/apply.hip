@@ -1547,6 +1547,7 @@ bse_status adjoint_gw(Plan* p, int q0, int i0, int nq, bool swap, const int* dst
   return cgemm_split(g, true, true, false, true, st);
 }
 
+// (the gradients' products cover the auxiliary functions as given, like their results)
 // One q batch of the k-major BF16x3 adjoint: Z = Gm conj(Mc) (or, for the partner, Z' = G' Mc) written
 // pre-split into P, then g_W of the batch's q = -(1/N_k) sum over pairs of Gv^T Z (conj(Gv)^T Z'), stored
 // at the W-gradient index given by dst (plan-order q -> dense-mesh q) or at q0 + i without a table
@@ -1561,7 +1562,7 @@ bse_status adjoint_tn_pass(Plan* p, int q0, int i0, int nq, bool swap, const int
     GemmArgs g;
     g.batch = nq * Nk;
     g.M = nv * nv;
-    g.N = na;
+    g.N = p->given_aux;
     g.K = nc * nc;
     g.A = G;
     g.a_sb = nt2;
@@ -1654,7 +1655,7 @@ bse_status adjoint_paired(Plan* p, const double* Ybar, const double* X, int nb, 
 bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, double* gWq, bool acc,
                           hipStream_t st) {
   const bse_dims& d = p->d;
-  const int Nk = p->Nk, nv = d.nv, nc = d.nc, na = d.n_aux;
+  const int Nk = p->Nk, nv = d.nv, nc = d.nc, na = d.n_aux, ga = p->given_aux;
   const Arith ar = arith_of(p->prec);
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
@@ -1702,7 +1703,7 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
       GemmArgs g;
       g.batch = nq * Nk;
       g.M = nv * nv;
-      g.N = na;
+      g.N = ga;
       g.K = nc * nc;
       g.A = p->T;
       g.a_sb = (long long)nc * nc * nv * nv;
@@ -1714,14 +1715,13 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
       g.b_sj = 1;
       g.conjB = 1;
       g.C = p->P;
-      g.c_sb = (long long)nv * nv * na;
-      g.c_si = na;
+      g.c_sb = (long long)nv * nv * ga;
+      g.c_si = ga;
       g.c_sj = 1;
       BSE_TRY(cgemm(g, ar, f64, f64, st));
     }
     {  // gWq[q][mu][nu] = -(1/N_k) sum_{(k v' v)} Gv[(k v' v)][mu] Z[(k v' v)][nu]
       GemmArgs g;
-      const int ga = p->given_aux;
       g.batch = nq;
       g.M = ga;
       g.N = ga;
@@ -1731,8 +1731,8 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
       g.a_si = 1;
       g.a_sk = na;
       g.B = p->P;
-      g.b_sb = (long long)Nk * nv * nv * na;
-      g.b_sk = na;
+      g.b_sb = (long long)Nk * nv * nv * ga;
+      g.b_sk = ga;
       g.b_sj = 1;
       g.C = gWq + 2 * (long long)q0 * ga * ga;
       g.c_sb = (long long)ga * ga;
