@@ -542,12 +542,18 @@ __global__ __launch_bounds__(256) void direct_tx_restaged(int Nk, int nq, int q0
   }
 }
 
-// LDS bytes of direct_tx_restaged, 0 beyond its largest instance
+// LDS bytes of direct_tx_restaged, 0 beyond its largest instance and where direct_tx_mfma is faster: with one block per CU
+// and one column of tiles (n_c n_v = 90, 8 vectors, 6x6x6: 2.77 ms against 2.48), and for an even n_c n_v on the instance
+// of most registers while direct_tx_mfma fits three times (70 and 16: 2.14 against 1.95)
 size_t tx_restaged_lds(int nt, int nb) {
   const int RT = (nt + 15) / 16, CT = (2 * nb + 15) / 16;
   if (nt * nt > 256 * 36 || nt * nb > 256 * 8 || RT * CT > 32) return 0;
   const int KG = ((2 * nt + 3) / 4 + 3) / 4 * 4;
-  return sizeof(float) * (size_t)(16 * (RT + CT)) * (4 * KG + 4);
+  const size_t lds = sizeof(float) * (size_t)(16 * (RT + CT)) * (4 * KG + 4);
+  if (lds > 80 * 1024 && CT == 1) return 0;
+  const bool most = nt > 64 && (nt * nb > 1024 || RT * CT > 16);
+  if (most && nt % 2 == 0 && 8 * (nt * nt + nt * nb) <= 160 * 1024 / 3) return 0;
+  return lds;
 }
 
 bse_status launch_tx_restaged(dim3 grid, size_t sh, int nt, hipStream_t st, int Nk, int nq, int q0, int nv, int nc,
@@ -560,9 +566,15 @@ bse_status launch_tx_restaged(dim3 grid, size_t sh, int nt, hipStream_t st, int 
     BSE_CHECK_LAUNCH();
     return BSE_OK;
   };
+  // by the registers they leave: one instance for everything beyond 512 elements of X or 64 transitions ran one block per
+  // CU, slower than direct_tx_mfma (6x6x6, T.X in us, direct_tx_mfma / one instance / these: 60 transitions and 16 vectors
+  // 1192 / 1538 / 742, 72 and 8 1388 / 1892 / 1138, 30 and 20 580 / 648 / 287)
   if (nt * nt <= 256 * 4 && nx <= 512 && tiles <= 8) return go(direct_tx_restaged<4, 2, 2>);
   if (nt * nt <= 256 * 16 && nx <= 512 && tiles <= 8) return go(direct_tx_restaged<16, 2, 2>);
+  if (nt * nt <= 256 * 16 && nx <= 1024 && tiles <= 8) return go(direct_tx_restaged<16, 4, 2>);
+  if (nt * nt <= 256 * 16 && tiles <= 16) return go(direct_tx_restaged<16, 8, 4>);
   if (nt * nt <= 256 * 16) return go(direct_tx_restaged<16, 8, 8>);
+  if (nx <= 1024 && tiles <= 16) return go(direct_tx_restaged<36, 4, 4>);
   return go(direct_tx_restaged<36, 8, 8>);
 }
 
