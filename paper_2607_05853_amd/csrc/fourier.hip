@@ -124,10 +124,9 @@ __device__ __forceinline__ void ft_phases(const FtArgs& a, double sign, const do
 }
 
 // Few q1 leave rows of threads without one: the pairs of q2 of each q1 are then shared between this many of them (by the
-// spread where there are more than four rows per q1, by the gather from two on: with fewer the sharing costs what it gives).
-__host__ __device__ __forceinline__ int ft_parts(int rows, int n1, int n2) {
-  return std::min(std::max(1, rows / n1), (n2 + 1) / 2);
-}
+// spread where there are more than four rows per q1, by the gather for fewer than four q1: with more the sharing costs what
+// it gives).
+int ft_parts(int rows, int n1, int n2) { return std::min(std::max(1, rows / n1), (n2 + 1) / 2); }
 
 // Spread.  A block stages in[R][te consecutive e] (weighted) in LDS, the whole tile's loads in flight together
 // and each input read from memory once; a thread owns one e and every (256 / te)-th q1 (or part of its q2).  For its q1
@@ -137,7 +136,7 @@ __host__ __device__ __forceinline__ int ft_parts(int rows, int n1, int n2) {
 // Input: c128 rows of E (planar = 0), or re / im planes per group of `group` elements, [R][E / group][2][group],
 // summed over nsplit partial arrays split_stride apart.
 template <int NY, int NZ, int MODE>
-__global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, const double* __restrict__ in,
+__global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, int parts, const double* __restrict__ in,
                                                  long long E, int planar, long long group, int nsplit,
                                                  long long split_stride, void* __restrict__ out,
                                                  const double* __restrict__ ref, const double2* tab) {
@@ -169,11 +168,11 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
   }
   for (int t = threadIdx.x; t < te; t += blockDim.x) W[a.nR * te + t] = double2{0.0, 0.0};
   ft_phases(a, sign, tab, NY, NZ, p1);
-  const int el = threadIdx.x % te, qstep = blockDim.x / te, parts = qstep / n1 > 4 ? ft_parts(qstep, n1, n2) : 1;
+  const int el = threadIdx.x % te, qstep = blockDim.x / te;
   const long long e = e0 + el;
   double dmax = 0.0;
   for (int it = threadIdx.x / te; it < n1 * parts && e < E; it += qstep) {
-    const int i1 = it / parts;
+    const int i1 = parts == 1 ? it : it / parts, part = parts == 1 ? 0 : it % parts;
     Z A[NY][NZ];
 #pragma unroll
     for (int y = 0; y < NY; ++y)
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(256) void ft_spread(FtArgs a, double sign, int te, 
           fma_z(A[y][z], p, Z{v.x, v.y});
         }
     }
-    for (int j = 2 * (it % parts); j < n2; j += 2 * parts) {
+    for (int j = 2 * part; j < n2; j += 2 * parts) {
       const int j2 = j + 1 < n2 ? j + 1 : j;
       Z B0[NZ], B1[NZ];
 #pragma unroll
@@ -250,7 +249,7 @@ constexpr int ft_turn(int ny, int nz) { return ny * nz <= 9 ? ny : 1; }
 // Output: c128 rows of E, or re and im planes of E each ([R][2][E]) when planar.
 // SPLIT: q2 shared between rows (without it what depends on the part is known, and stays in scalar registers).
 template <int NY, int NZ, bool SPLIT>
-__global__ __launch_bounds__(256, NY * NZ <= 25 ? 2 : 1) void ft_gather(FtArgs a, double sign, int te,
+__global__ __launch_bounds__(256, NY * NZ <= 25 ? 2 : 1) void ft_gather(FtArgs a, double sign, int te, int shared,
                                                                         const double* __restrict__ in, long long E,
                                                                         int planar, double* __restrict__ out,
                                                                         const double2* tab) {
@@ -264,7 +263,7 @@ __global__ __launch_bounds__(256, NY * NZ <= 25 ? 2 : 1) void ft_gather(FtArgs a
   double2* const p3 = p2 + n2 * NY;
   long long e = (long long)blockIdx.x * te + el;  // of the tile in hand, which starts at e - el < E
   // row i of a round: q1 i / parts, part i % parts of its q2
-  const int parts = SPLIT ? ft_parts(nq / 2, n1, n2) : 1, rows = n1 * parts;
+  const int parts = SPLIT ? shared : 1, rows = n1 * parts;
   int i0 = 0, part = 0, steps = 0;
   const int nk = (n3 + 3) / 4;
   const double2* g;
@@ -409,16 +408,18 @@ bse_status ft_spread_launch(const FtArgs& a, double sign, const double* in, long
                             hipStream_t st, const double* table) {
   const double2* tab = reinterpret_cast<const double2*>(table);
   // 32 e per block (512-byte rows) while the tile leaves room for two blocks on a CU, 16 for the larger R sets
-  // and while 32 would leave CUs without a block
-  const int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
+  // and while 32 would leave CUs without a block; more where q1 and the pairs of q2 are fewer than the rows of threads
+  int te = (a.nR <= 128 && E >= 32 * 512) ? 32 : 16;
+  while (te >= 32 && te < 256 && 256 / te >= a.n[0] * (a.n[1] + 1) && E >= 2 * te * 448 && (a.nR + 1) * te <= 1536) te *= 2;
   const size_t lds = 16 * (size_t)(a.nR + 1) * te + ft_table_bytes(a);
   const dim3 grid((unsigned)((E + te - 1) / te));
+  const int parts = 256 / te / a.n[0] > 4 ? ft_parts(256 / te, a.n[0], a.n[1]) : 1;
   return with_sides(a, [&](auto ny, auto nz) -> bse_status {
     auto go = [&](auto kern) -> bse_status {
       if (lds > 64 * 1024)
         BSE_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-      hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, sign, te, in, E, planar, group, nsplit, split_stride, out,
-                         ref, tab);
+      hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, sign, te, parts, in, E, planar, group, nsplit, split_stride,
+                         out, ref, tab);
       BSE_CHECK_LAUNCH();
       return BSE_OK;
     };
@@ -442,10 +443,11 @@ bse_status ft_gather_launch(const FtArgs& a, double sign, const double* in, long
     // as many blocks as the registers allow on the CUs (two for the boxes of 5 x 5), each over its share of the tiles
     constexpr int PER_CU = NY * NZ <= 3 ? 4 : NY * NZ <= 9 && NZ < 7 ? 3 : 2;
     const dim3 grid((unsigned)std::min<long long>(256 * PER_CU, (E + te - 1) / te));
-    if (ft_parts(256 / te / 2, a.n[0], a.n[1]) > 1)
-      hipLaunchKernelGGL((ft_gather<NY, NZ, true>), grid, dim3(256), lds, st, a, sign, te, in, E, planar, out, tab);
+    const int parts = a.n[0] < 4 ? ft_parts(256 / te / 2, a.n[0], a.n[1]) : 1;
+    if (parts > 1)
+      hipLaunchKernelGGL((ft_gather<NY, NZ, true>), grid, dim3(256), lds, st, a, sign, te, parts, in, E, planar, out, tab);
     else
-      hipLaunchKernelGGL((ft_gather<NY, NZ, false>), grid, dim3(256), lds, st, a, sign, te, in, E, planar, out, tab);
+      hipLaunchKernelGGL((ft_gather<NY, NZ, false>), grid, dim3(256), lds, st, a, sign, te, 1, in, E, planar, out, tab);
     BSE_CHECK_LAUNCH();
     return BSE_OK;
   });

@@ -31,7 +31,7 @@ def box(*r):
 CASES = [((3, 5, 4), (2, y, z), 6) for y in (1, 2, 3, 4, 5, 6, 7) for z in (1, 3, 4, 7)]
 CASES += [((1, 9, 2), (1, 5, 2), 350), ((1, 3, 1), (1, 2, 1), 350), ((2, 7, 1), (2, 7, 1), 350), ((3, 4, 2), (3, 1, 2), 182),
           ((4, 5, 3), (3, 5, 1), 182), ((9, 2, 3), (5, 1, 3), 182), ((17, 3, 1), (7, 3, 1), 182), ((1, 24, 1), (1, 7, 1), 9),
-          ((1, 1, 1), (1, 1, 1), 350), ((5, 1, 6), (3, 1, 5), 20)]
+          ((1, 1, 1), (1, 1, 1), 350), ((1, 2, 8), (1, 2, 7), 350), ((2, 1, 3), (2, 1, 3), 350), ((5, 1, 6), (3, 1, 5), 20)]
 
 
 @pytest.mark.parametrize("n,r,na", CASES)
