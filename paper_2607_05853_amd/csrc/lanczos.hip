@@ -295,7 +295,9 @@ extern "C" bse_status bse_haydock_spectrum(bse_plan* plan, const void* P, int32_
       dfree(stp);
     }
   } B;
-  if (basis_out) {
+  // the recurrence reads the basis 16 bytes at a time: a caller's buffer aligned to its doubles only is filled at the end
+  const bool in_place = basis_out && (reinterpret_cast<uintptr_t>(basis_out) & 15) == 0;
+  if (in_place) {
     B.basis = (double*)basis_out;
   } else {
     BSE_TRY(dmalloc((void**)&B.basis, 16 * (size_t)nb * m * N));
@@ -370,6 +372,8 @@ extern "C" bse_status bse_haydock_spectrum(bse_plan* plan, const void* P, int32_
                        1.0 / (M_PI * (double)p->Nk), B.dS);
     BSE_CHECK_LAUNCH();
   }
+  if (basis_out && !in_place)
+    BSE_HIP(hipMemcpyAsync(basis_out, B.basis, 16 * (size_t)nb * m * N, hipMemcpyDeviceToDevice, st));
   BSE_HIP(hipMemcpyAsync(S, B.dS, 8 * (size_t)nb * n_w, hipMemcpyDeviceToHost, st));
   BSE_HIP(hipMemcpyAsync(a, B.da, 8 * (size_t)nb * m, hipMemcpyDeviceToHost, st));
   BSE_HIP(hipMemcpyAsync(b, B.db, 8 * (size_t)nb * (m + 1), hipMemcpyDeviceToHost, st));
