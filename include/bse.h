@@ -310,7 +310,8 @@ bse_status bse_density_start(const bse_plan* plan, const void* psi, void* P, voi
  * nb independent Haydock chains (Lanczos with full re-orthogonalisation by
  * classical Gram-Schmidt done twice) from the start vectors P, in FP64:
  *   b_0 = |p|, q_1 = p / b_0;  w = A q_j;  a_j = Re q_j^H w;
- *   w -= a_j q_j + b_{j-1} q_{j-1};  w -= Q (Q^H w) twice;  b_j = |w|;
+ *   w -= Q (Q^H w) twice, the first time with the three-term part
+ *   a_j q_j + b_{j-1} q_{j-1} in it;  b_j = |w|;
  *   breakdown when b_j <= 1e-12 max(|a_1|, .., |a_j|, b_1, .., b_{j-1}) (the
  *   chain's own scale of A, so the test does not depend on |p|; the chain
  *   stops, steps_done = j);
@@ -440,7 +441,11 @@ bse_status bse_full_spectrum(bse_plan* plan, const void* P, int32_t nb, int32_t 
  * Stage timing (tracing): when enabled, HIP events are recorded on the call's
  * stream around every stage launched by bse_apply / bse_apply_adjoint /
  * bse_haydock_spectrum, and bse_plan_stage_times() synchronises on them and
- * returns accumulated milliseconds and launch counts per stage.
+ * returns accumulated milliseconds and launch counts per stage.  An application
+ * over lattice vectors (bse_plan_lattice) uses some of them: PAIRDENS_V for D(k)
+ * and D(R), DBLOCK for the products with K(R) or the last contraction, TX for F(k)
+ * and Y, and where it contracts PAIRDENS_C for C^mu D(R), WSTEP for C^mu W(R) and
+ * EXCHANGE; it launches neither TABLES nor DIAG.
  * ------------------------------------------------------------------------- */
 typedef enum {
     BSE_STAGE_PAIRDENS_V = 0, /* valence pair densities M_vv' from the halves (1 kernel)    */

@@ -19,8 +19,9 @@
 // kernels, 26 ms to make) 83.7 -> 23.3 -> 3.6 ms; N_ao 96, 4 vectors (no room for kernels) 102 -> 46 ms; 5x6x7, N_ao 30,
 // N_aux 90, 27 R, 5 vectors (95 MB) 2.19 -> 0.111 ms; 4x4x4, N_ao 16, N_aux 64, 3 vectors (8 MB) 0.305 -> 0.034 ms.
 // W(R) is contracted with C^mu again in every application (G, one vector's worth of work in a batched product) as G of
-// all R takes as much memory as U.  The contractions remain for kernels beyond 16 GiB or a fifth of the free memory, W_q
-// that are not Hermitian, and where they are less work.
+// all R takes as much memory as U.  The contractions remain for kernels beyond 16 GiB, or beyond a fifth of the free memory
+// with their buffers, W_q that are not Hermitian, and where they are less work.  The pair route remains for every W_q that is
+// no such sum to its rounding, and where neither form finds memory.
 #include "bse_internal.h"
 #include "fourier.h"
 #include "mfma_common.h"
@@ -860,8 +861,8 @@ void lattice_free(Plan* p) {
   p->lat = nullptr;
 }
 
-// Whether an application to nb vectors goes over R: by the matrix work of the two routes, the pair route counted
-// 1.5 times because its GEMMs of a few rows per pair run at 33 TFLOP/s (8x8x8 workload) against 56 here
+// Whether an application to nb vectors goes over R: by the matrix work of the two routes at the rates above (the launches
+// are not counted: six to ten here, ten and more per batch of q there)
 bool lattice_applies(const Plan* p, int nb) {
   if (!p->lat) return false;
   if (p->lat->forced) return true;
