@@ -117,6 +117,13 @@ bse_status plan_alloc(Plan* p, void** ptr, size_t bytes) {
   return BSE_OK;
 }
 
+void plan_release(Plan* p, size_t held) {
+  for (; p->owned.size() > held; p->owned.pop_back()) {
+    p->bytes -= p->owned.back().bytes;
+    dfree(p->owned.back().p);
+  }
+}
+
 namespace {
 
 // ---------------------------------------------------------------------------
@@ -413,10 +420,12 @@ __global__ void permute_blocks(const unsigned short* __restrict__ in, unsigned s
   }
 }
 
-// the q-batch buffers of the direct term
+}  // namespace
+
+// the q-batch buffers of the direct term, those not yet there
 bse_status pair_workspace(Plan* p) {
   const long long nq = p->qb, Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
-  auto get = [&](void** b, size_t bytes) { return plan_alloc(p, b, bytes); };
+  auto get = [&](void** b, size_t bytes) -> bse_status { return *b ? BSE_OK : plan_alloc(p, b, bytes); };
   BSE_TRY(get(&p->Mv, p->esz * (size_t)(nq * Nk * nv * nv * na)));
   BSE_TRY(get(&p->P, p->esz * (size_t)(nq * Nk * nv * nv * na)));
   if (p->mc_direct) BSE_TRY(get(&p->Mc, p->esz * (size_t)(nq * Nk * nc * nc * na)));
@@ -431,6 +440,8 @@ bse_status pair_workspace(Plan* p) {
   BSE_TRY(get((void**)&p->tab_psi_c, sizeof(long long) * (size_t)(nq * Nk * nc)));
   return get((void**)&p->tab_mc, sizeof(long long) * (size_t)(nq * Nk * nc));
 }
+
+namespace {
 
 // two-centre LRI coefficients as given to plan creation
 struct TwoCentreIn {
@@ -807,9 +818,22 @@ bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const d
   }
   BSE_TRY(plan_alloc(p, (void**)&p->txp, 16 * (size_t)TX_CHUNKS * p->N * max_nb));
   // also where every application goes over lattice vectors: the gradient needs these buffers and allocates nothing of
-  // its own into a caller's g_Wq, so that its first call can be captured
-  BSE_TRY(pair_workspace(p));
-  if (f64 && !tc && p->herm_half) BSE_TRY(lattice_build(p, C, W_q, st));
+  // its own into a caller's g_Wq, so that its first call can be captured.  Only where they find no memory are such plans
+  // made without, and the gradient tries again.
+  const bool over_R = f64 && !tc && p->herm_half;
+  const size_t held = p->owned.size();
+  const bse_status pairs = pair_workspace(p);
+  if (pairs != BSE_OK) {
+    if (pairs != BSE_ENOMEM || !over_R) return pairs;
+    plan_release(p, held);
+    p->Mv = p->P = p->Mc = p->T = nullptr;
+    p->tab_psi_v = p->tab_mv = p->tab_psi_c = p->tab_mc = nullptr;
+  }
+  if (over_R) BSE_TRY(lattice_build(p, C, W_q, st));
+  if (pairs != BSE_OK) {
+    if (!lattice_applies(p, max_nb)) return pair_workspace(p);
+    set_error("");
+  }
   return BSE_OK;
 }
 

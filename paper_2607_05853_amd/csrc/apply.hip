@@ -1339,6 +1339,7 @@ bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t
   // n_v = n_c = 8 with N_aux a multiple of 256 on the M_cc' route: the W step and the direct block run as one
   // kernel and P stays on chip (same result as the two GEMMs below)
   const bool fused = p->fused_wt && fused_wstep_enabled();
+  BSE_TRY(pair_workspace(p));
   for (int q0 = 0; q0 < nqt; q0 += p->qb) {
     const int nq = (nqt - q0) < p->qb ? (nqt - q0) : p->qb;
     BSE_TRY(form_pair_densities(p, q0, nq, p->mc_direct, kq, st, p->split));
@@ -1672,6 +1673,7 @@ bse_status adjoint_direct(Plan* p, const double* Ybar, const double* X, int nb, 
   const bool f64 = p->prec == BSE_F64;
   // BF16x3 with 8-aligned n_v^2 and N_aux: every operand pre-split, both reductions on the k-major kernel
   const bool tn = p->split && (nv * nv) % 8 == 0 && p->given_aux % 8 == 0;
+  BSE_TRY(pair_workspace(p));
   if (tn && p->herm_half && !p->two_centre && nv == 4) {
     bool ok = false;
     BSE_TRY(paired_workspace(p, st, &ok));

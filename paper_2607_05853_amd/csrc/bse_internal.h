@@ -257,6 +257,8 @@ struct StageMark {
 bse_status collect_stage_times(Plan* p);
 
 bse_status plan_alloc(Plan* p, void** ptr, size_t bytes);
+void plan_release(Plan* p, size_t held);  // frees the buffers after the first `held`
+bse_status pair_workspace(Plan* p);       // the q-batch buffers of the direct term, where not yet allocated
 
 // stage launchers (apply.hip)
 bse_status apply_direct(Plan* p, const double* X, double* Y, int nb, hipStream_t st);

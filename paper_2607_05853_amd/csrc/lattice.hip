@@ -1158,12 +1158,9 @@ bse_status lattice_build(Plan* p, const void* C, const void* W_q, hipStream_t st
   if (s == BSE_OK && taken) return BSE_OK;
   // the plan keeps the pair route, and nothing of this
   lattice_free(p);
-  for (; p->owned.size() > held; p->owned.pop_back()) {
-    p->bytes -= p->owned.back().bytes;
-    dfree(p->owned.back().p);
-  }
+  plan_release(p, held);
   if (s != BSE_ENOMEM) return s;
-  set_error("");  // too little memory for it: the pair route has its buffers already
+  set_error("");  // too little memory for it
   return BSE_OK;
 }
 
