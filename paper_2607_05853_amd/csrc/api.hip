@@ -722,6 +722,7 @@ bse_status build_plan(Plan* p, const bse_dims* d, const bse_dims* given, const d
       std::memcpy(&wmax, &hout[1], 8);
       std::memcpy(&hmax, &hout[2], 8);
       use = dmax <= 1e-12 * wmax;
+      p->w_max = wmax;
       // the coupling block's transpose relation D_B(k', k) = D_B(k, k')^T needs W(-q) = W(q)^T as well,
       // i.e. (with the relation above) a Hermitian W(q)
       p->b_pairs = use && hmax <= 1e-12 * wmax;

@@ -214,6 +214,7 @@ struct Plan {
   double* fra = nullptr;
   double* frb = nullptr;
 
+  double w_max = 0.0;         // largest real or imaginary part in W_q (pair-symmetric plans)
   Lattice* lat = nullptr;     // the application over lattice vectors (FP64 plans whose W_q is a short sum over R)
 
   // exchange / misc workspaces (FP64)

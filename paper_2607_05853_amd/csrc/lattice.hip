@@ -1018,8 +1018,8 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   // the inverse sum over the whole box (the kernels' R list is limited to FT_MAXNR: as many R1 at a time as fit)
   Tmp box, red, idx, chk;
   BSE_TRY(dmalloc(&box.p, 16 * (size_t)nbox * n2));
-  BSE_TRY(dmalloc(&red.p, 8 * (2 * (size_t)nbox + 3)));
-  BSE_TRY(zero_fill(red.p, 8 * (2 * (size_t)nbox + 3), st));
+  BSE_TRY(dmalloc(&red.p, 8 * (2 * (size_t)nbox + 1)));
+  BSE_TRY(zero_fill(red.p, 8 * (2 * (size_t)nbox + 1), st));
   const int slab = nbox / (hi[0] - lo[0] + 1), per = FT_MAXNR / slab * slab;
   const std::vector<double> w(nbox, 1.0 / Nk);
   for (int i = 0; i < nbox; i += per) {
@@ -1085,13 +1085,10 @@ bse_status lattice_try(Plan* p, const void* C, const void* W_q, hipStream_t st, 
   BSE_CHECK_LAUNCH();
   double* const dmax = (double*)red.p + 2 * (size_t)nbox;
   BSE_TRY(ft_spread_launch(ax, 1.0, (const double*)chk.p, n2, 0, 1, 1, 0, 2, dmax, (const double*)W_q, st));
-  hipLaunchKernelGGL(lat_absmax, dim3(2048, 1), dim3(256), 0, st, n2 * Nk, (const double*)W_q,
-                     (unsigned long long*)dmax + 1);
-  BSE_CHECK_LAUNCH();
-  double off[3] = {};  // the largest difference, the largest real and imaginary part of W_q
-  BSE_HIP(hipMemcpyAsync(off, dmax, 24, hipMemcpyDeviceToHost, st));
+  double off = 0.0;
+  BSE_HIP(hipMemcpyAsync(&off, dmax, 8, hipMemcpyDeviceToHost, st));
   BSE_HIP(hipStreamSynchronize(st));
-  if (!(off[0] <= W_ROUNDING * std::max(off[1], off[2]))) return BSE_OK;
+  if (!(off <= W_ROUNDING * p->w_max)) return BSE_OK;
   if (kernels) {  // W(-R) = W(R)^T as of a Hermitian W_q
     double asym = 0.0;
     Tmp pr;
