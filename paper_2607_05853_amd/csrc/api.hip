@@ -422,8 +422,8 @@ __global__ void permute_blocks(const unsigned short* __restrict__ in, unsigned s
 
 }  // namespace
 
-// the q-batch buffers of the direct term, those not yet there; up to 4 GiB in one allocation (4x4x4 FP64 plan 1.6 ms with
-// eight, 1.3 with one), so that a card short of memory needs no larger piece than it has
+// the q-batch buffers of the direct term, those not yet there; up to 4 GiB in one allocation (4x4x4 FP64 plan: 1.6 ms with
+// eight, 1.3 with one), larger ones apart, where the allocations no longer show
 bse_status pair_workspace(Plan* p) {
   const long long nq = p->qb, Nk = p->Nk, nv = p->d.nv, nc = p->d.nc, na = p->d.n_aux;
   std::vector<std::pair<void**, size_t>> list;
