@@ -239,8 +239,8 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
  * element of it back to 4e-15 of the largest one, its rounding (a W_q interpolated
  * from a coarse mesh of up to 7 points per axis and at most 256 R); the sum over k'
  * then separates and its work grows with n_R nb instead of N_k^2.  Any other W_q is
- * taken as it is, by pairs.  Taken where
- * that needs less work; 0 otherwise.  Host pointer.  With W_q Hermitian (to the same rounding) such a
+ * taken as it is, by pairs.  The lattice vectors are taken where that needs less
+ * work; 0 otherwise.  Host pointer.  With W_q Hermitian to the same rounding such a
  * plan keeps one n_ao^2 x n_ao^2 kernel per pair (R, -R), half of it stored
  * (8 n_ao^4 bytes), where these take at most 16 GiB and less time than
  * contracting C^mu and W(R) anew.  What either form allocates besides copies of
@@ -248,8 +248,8 @@ bse_status bse_plan_frag(const bse_plan* plan, int32_t* frag);
  * BSE_WORKSPACE_GB (the contractions take one vector and one R at a time in less);
  * a plan that finds no room for it forms pairs.  The forms' sums run in different
  * orders: results agree to FP64 rounding, not bit for bit.  BSE_LATTICE=0 in the
- * environment at plan creation keeps the pairs, BSE_LATTICE=contract takes
- * the contractions whatever they cost. */
+ * environment at plan creation keeps the pairs, BSE_LATTICE=contract takes the
+ * contractions whatever they cost. */
 bse_status bse_plan_lattice(const bse_plan* plan, int32_t nb, int32_t* n_R);
 
 /* Device bytes held by the plan (copies, halves and workspaces). */
